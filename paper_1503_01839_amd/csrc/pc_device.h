@@ -233,6 +233,41 @@ PC_HD uint64_t pc_isqrt_wide(uint64_t hi, uint64_t lo)
     return r;
 }
 
+// The sieve's bitmap keeps only the integers prime to 30 (2, 3 and 5 always
+// belong to the wheel): 8 bits, one byte, for every 30 integers.  With the
+// offset d of an integer from a multiple of 30, bit 8 (d / 30) + i stands for
+// the i-th of the residues 1, 7, 11, 13, 17, 19, 23, 29; for those residues
+// that is floor(4 d / 15).
+#define PC_W30_MASK 0x208A2882u            // bit r set: r < 30 is prime to 30
+#define PC_W30_RES 0x1D1713110D0B0701ull   // the residues, a byte each
+#define PC_W30_GAPS 0x26424246u            // residue i + 1 less residue i, a nibble each
+
+// integers covered by a segment of 2^log2s bits
+PC_HD uint64_t pc_seg_span(uint32_t log2s) { return 15ull << (log2s - 2); }
+
+// residue i
+PC_HD uint32_t pc_w30_res(uint32_t i) { return (uint32_t)(PC_W30_RES >> (8 * i)) & 255u; }
+
+// integers prime to 30 among 0 .. d, d < 2^27
+PC_HD uint32_t pc_w30_le(uint32_t d)
+{
+    const uint32_t q = d / 30u, r = d - 30u * q;
+    return 8u * q + (uint32_t)__builtin_popcount(PC_W30_MASK & ((2u << r) - 1u));
+}
+
+// the bit of d, d prime to 30, d < 2^21: the fraction of 4 d / 15 is then
+// between 1/15 and 14/15, and the fp32 product is off by less than 1/16
+PC_HD uint32_t pc_w30_bit(uint32_t d) { return (uint32_t)((float)d * (4.0f / 15.0f)); }
+
+// the integer of a bit
+PC_HD uint32_t pc_w30_int(uint32_t bit) { return 30u * (bit >> 3) + pc_w30_res(bit & 7u); }
+
+// the least j' >= j prime to 30, 0 <= j <= 30
+PC_HD uint32_t pc_w30_next(uint32_t j)
+{
+    return j < 30u ? j + (uint32_t)__builtin_ctz(PC_W30_MASK >> j) : 31u;
+}
+
 // Integer square and cube roots, exact (used by the host planner).
 PC_HD uint64_t pc_isqrt(uint64_t n)
 {

@@ -457,9 +457,10 @@ void ensure_wheel(uint32_t c)
     for (uint32_t i = 1; i <= c; i++) {
         Q *= kFirstPrimes[i];
         phiQ *= kFirstPrimes[i] - 1;
-        if (i >= 2)
+        if (i >= 4)
             period *= kFirstPrimes[i];
     }
+    period *= 8; // bits: one byte per 30 integers
     uint32_t words = (period + 64) / 32 + 2;
     ensure(T.pattern[c], words * 4, "wheel pattern");
     ensure(T.phitab[c], (size_t)Q * 4, "wheel phi table");
@@ -854,19 +855,20 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     Q.ncol = Q.nb + 1;
     Q.kx = (uint32_t)kx;
 
-    // Rows of the sieve: nA one-wavefront segments of 2*SA integers covering
+    // Rows of the sieve: nA one-wavefront segments of spanA integers covering
     // the leaf-dense low end up to about hot_span * y, then nB workgroup
-    // segments of 2*S integers, together covering [0, z].
-    const uint64_t S = 1ull << K.seg_log2, SA = 1ull << K.hot_log2;
+    // segments of spanB integers, together covering [0, z].
+    const uint64_t S = 1ull << K.seg_log2;
+    const uint64_t spanA = pc_seg_span(K.hot_log2), spanB = pc_seg_span(K.seg_log2);
     uint64_t nA = 0;
     if (K.hot_span) {
         const uint64_t uA = std::min<uint64_t>(z + 1, K.hot_span * y);
-        nA = (uA + 2 * SA - 1) / (2 * SA);
+        nA = (uA + spanA - 1) / spanA;
     }
-    const uint64_t baseB = nA * 2 * SA;
-    const uint64_t nB = baseB > z ? 0 : (z - baseB) / (2 * S) + 1;
+    const uint64_t baseB = nA * spanA;
+    const uint64_t nB = baseB > z ? 0 : (z - baseB) / spanB + 1;
     const uint64_t nseg = nA + nB;
-    Q.sieve_end = baseB + nB * 2 * S;
+    Q.sieve_end = baseB + nB * spanB;
     Q.nseg = nseg;
     g_ev_used = 0;
 
@@ -973,7 +975,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     // p_b <= isqrt(x / lo_r), and the first row stores every column.
     std::vector<uint32_t> rowlen(nseg);
     for (uint64_t r = 0; r < nseg; r++)
-        rowlen[r] = row_len(x, c, Q.nb, r < nA ? r * 2 * SA : baseB + (r - nA) * 2 * S);
+        rowlen[r] = row_len(x, c, Q.nb, r < nA ? r * spanA : baseB + (r - nA) * spanB);
     // windows of rows within the carry budget (cells of cnt and w, or of cnt
     // and the carries, plus the P2 column's per-row words)
     const uint64_t per_cell = K.two_pass ? 12 : 8, per_row = K.two_pass ? 12 : 8;
@@ -1049,14 +1051,19 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     uint64_t ntiles_total = 0;
     uint64_t *cin = ptr<uint64_t>(B.carry_a), *cout = ptr<uint64_t>(B.carry_b);
     const int bflag = K.batch ? 0 : 0x100;
-    for (uint64_t wi = 0; wi < nwin; wi++) {
+    if (c < 3) { // y < 5: the bitmap needs 2, 3 and 5 in the wheel; z < 32 here
+        ev_sieve.push_back(
+            timed([&] { hipck(pc_launch_sieve_tiny(T, Q, g_stream), "sieve"); }));
+        ntiles_total = 1;
+    }
+    for (uint64_t wi = 0; wi < (c < 3 ? 0 : nwin); wi++) {
         // seeded windows need nothing from each other: they run last to first
         const uint64_t w = K.seeded ? nwin - 1 - wi : wi;
         const uint64_t r0 = win_start[w], r1 = win_start[w + 1], rows = r1 - r0;
         if (K.seeded && w > 0) {
             // the window's carries on their own: every integer below its first
             // one, phi(lo - 1, c + j) in column j (Section 4)
-            const uint64_t lo_w = r0 < nA ? r0 * 2 * SA : baseB + (r0 - nA) * 2 * S;
+            const uint64_t lo_w = r0 < nA ? r0 * spanA : baseB + (r0 - nA) * spanB;
             const uint32_t nrec = seed_rec_cols(lo_w - 1, c, Q.nb);
             ev_seed.push_back(timed([&] {
                 hipck(pc_launch_seed(T, c, lo_w - 1, Q.nb, nrec, g_T.pi_limit,
@@ -1083,7 +1090,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
             const uint64_t b0 = std::max(r0, nA);
             const uint64_t hot_end = std::max<uint64_t>(64 * y, z / 32);
             const uint64_t plan_end =
-                hot_end <= baseB ? b0 : std::min(r1, nA + (hot_end - baseB) / (2 * S) + 1);
+                hot_end <= baseB ? b0 : std::min(r1, nA + (hot_end - baseB) / spanB + 1);
             plan_tiles(T, Q, K, K.seg_log2, baseB, nA, b0, r1 - b0, std::max(b0, plan_end),
                        tiles_b);
         }
@@ -1350,7 +1357,9 @@ struct BatchQuery {
     uint64_t x, y, a, kx, bmax, z, nseg;
     uint32_t c, nb, ncol;
     size_t idx; // position in the caller's array
-    uint64_t bytes() const { return nseg * ncol * 8; }
+    // what admission to a round counts for the query: 8 bytes for every
+    // sieving prime per 2^19 integers of [0, z], an upper bound on its counts
+    uint64_t bytes() const { return (z / (1ull << 19) + 1) * ncol * 8; }
 };
 
 constexpr uint32_t kBatchLog2S = 18; // 32 KiB segments
@@ -1473,7 +1482,7 @@ void plan_round(const std::vector<BatchQuery> &R, RoundPlan &P)
         uint64_t off = 0;
         P.roff.push_back(0);
         for (uint64_t r = 0; r < b.nseg; r++) {
-            off += row_len(b.x, b.c, b.nb, r * (2ull << kBatchLog2S));
+            off += row_len(b.x, b.c, b.nb, r * pc_seg_span(kBatchLog2S));
             P.roff.push_back(off);
         }
         P.cells[i] = off;
@@ -1528,7 +1537,6 @@ void round_queries(const std::vector<BatchQuery> &R, const RoundPlan &P, char *b
                    const uint64_t *roff, const pc_tables &T, std::vector<pc_query> &Qv)
 {
     const uint32_t nq = (uint32_t)R.size();
-    const uint64_t S = 1ull << kBatchLog2S;
     pc_sums *sums = reinterpret_cast<pc_sums *>(base + P.o_sums);
     Qv.assign(nq, pc_query{});
     for (uint32_t i = 0; i < nq; i++) {
@@ -1583,7 +1591,7 @@ void round_queries(const std::vector<BatchQuery> &R, const RoundPlan &P, char *b
         Q.sums = sums + i;
         Q.carry = nullptr;
         Q.nseg = b.nseg;
-        Q.sieve_end = b.nseg * 2 * S;
+        Q.sieve_end = b.nseg * pc_seg_span(kBatchLog2S);
     }
 }
 
@@ -1772,7 +1780,7 @@ std::vector<BatchQuery> query_params(const uint64_t *xs, size_t n, const QueryYs
         b.c = (uint32_t)std::min<uint64_t>(kWheelC, b.a);
         b.nb = b.bmax > b.c ? (uint32_t)(b.bmax - b.c) : 0;
         b.ncol = b.nb + 1;
-        b.nseg = b.z / (2ull << kBatchLog2S) + 1;
+        b.nseg = b.z / pc_seg_span(kBatchLog2S) + 1;
         b.idx = i;
         *amax = std::max(*amax, b.a);
         big.push_back(b);

@@ -27,10 +27,11 @@ struct pc_tables {
     const double *rcpd;     // rcpd[k] = 1/p_k correctly rounded, k <= n_recip
     const uint2 *pitab;     // pi table, see pc_pi_lookup
     const int32_t *mulpf;   // mu(n)*lpf(n) for n <= ymax; INT32_MAX at n = 1; 0 if mu = 0
-    const uint32_t *pattern; // odd-only pre-sieve bits for p_2..p_c, period pattern_bits (+64 bits)
+    const uint32_t *pattern; // pre-sieve bits for p_4..p_c (8 bits per 30 integers), period
+                            // pattern_bits (+64 bits)
     const uint32_t *phitab; // phi(r, c) for r < Q_c
     const uint32_t *wres;   // the residues r < Q_c prime to p_1..p_c, ascending (phi(Q_c, c) of them)
-    uint32_t pattern_bits;  // prod_{2 <= i <= c} p_i
+    uint32_t pattern_bits;  // 8 prod_{4 <= i <= c} p_i
     uint32_t Qc;            // prod_{1 <= i <= c} p_i
     uint32_t phiQ;          // phi(Q_c, c)
     float rphiQ;            // 1 / phi(Q_c, c)
@@ -51,7 +52,7 @@ struct pc_query {
     uint32_t kx;            // pi(isqrt(x))
     const uint64_t *Xb;     // Xb[b] = floor(x / p_b) modulo 2^64, 1-based, b <= a
     uint32_t *Xbh;          // its high word (above 2^64; null: every X_b < 2^64)
-    uint64_t sieve_end;     // the sieve covers [0, sieve_end): segments * 2S integers
+    uint64_t sieve_end;     // the sieve covers [0, sieve_end): segments * pc_seg_span
     uint64_t nseg;          // segments (rows of cnt and wgt when the query has one window)
     const ulonglong2 *Ub;   // Ub[b].x <= u of every hard leaf of b <= Ub[b].y, and Ub[b].y is
                             // also >= that bound for every later sieving prime (x > y: none)
@@ -148,7 +149,7 @@ struct pc_sieve_args {
     uint32_t ntiles;
     uint32_t pad;
     uint64_t seg0;          // first segment of the window: row = seg - seg0
-    uint64_t lo_base;       // segment seg starts at lo_base + (seg - seg_base) * 2S
+    uint64_t lo_base;       // segment seg starts at lo_base + (seg - seg_base) * pc_seg_span
     uint64_t seg_base;
     pc_s128 *part_hard;     // per tile; null: added to the tile's query sums instead
     pc_s128 *part_p2;       // per tile (null as part_hard)
@@ -202,6 +203,9 @@ hipError_t pc_launch_seg_split(const pc_tables &T, const pc_query &Q, uint32_t s
 // Sieve and carry scan.
 hipError_t pc_launch_sieve(const pc_sieve_args &A, uint32_t seg_log2, uint32_t wg, int mode,
                            hipStream_t s);
+// The hard leaves and P2 lookups of a query with c < 3 (y < 5, z < 32), into
+// the query's sums.
+hipError_t pc_launch_sieve_tiny(const pc_tables &T, const pc_query &Q, hipStream_t s);
 // The carries of one window: per sieving column an exclusive scan of the
 // staircase rows (decoupled look-back over chunks of rows), and the same for
 // the P2 column (cntP, one workgroup).  Workgroup tickets run chunk by chunk;

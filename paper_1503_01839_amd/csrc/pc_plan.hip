@@ -42,7 +42,7 @@ __global__ __launch_bounds__(PL_T) void k_seg_work(pc_tables TB, pc_query Q, uin
 {
     __shared__ uint64_t scr[PL_T / 64];
     const uint64_t seg = seg0 + blockIdx.x;
-    const uint64_t lo = lo_base + ((seg - seg_base) << (LOG2_S + 1)), hi = lo + (2ull << LOG2_S);
+    const uint64_t lo = lo_base + (seg - seg_base) * pc_seg_span(LOG2_S), hi = lo + pc_seg_span(LOG2_S);
     const uint64_t rhi = pc_recip(hi), rlo = lo ? pc_recip(lo) : 0;
     uint64_t s = 0;
     for (uint32_t col = threadIdx.x; col < Q.nb; col += PL_T)
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(PL_T) void k_seg_split(pc_tables TB, pc_query Q, co
     __shared__ uint64_t scr[PL_T / 64];
     const uint4 h = hot[blockIdx.x]; // x = segment, y = tiles K, z = offset, w = unused
     const uint64_t seg = h.x;
-    const uint64_t lo = lo_base + ((seg - seg_base) << (LOG2_S + 1)), hi = lo + (2ull << LOG2_S);
+    const uint64_t lo = lo_base + (seg - seg_base) * pc_seg_span(LOG2_S), hi = lo + pc_seg_span(LOG2_S);
     const uint64_t rhi = pc_recip(hi), rlo = lo ? pc_recip(lo) : 0;
     // total, then boundaries where the running work crosses j * total / K
     uint64_t tot = 0;

@@ -3,8 +3,12 @@
 // term (Sections 2.3 and 3 of the paper; the counters, blocks and per-prime
 // running values phi(m_min, b) that Section 3 and Section 4 describe).
 //
-// Layout.  A segment holds S odd integers as an LDS bitmap: bit i <-> the
-// integer seg*2S + 2i + 1 (p_1 = 2 is implicit).  Column j < nb stands for the
+// Layout.  A segment holds S integers prime to 30 as an LDS bitmap: 8 bits,
+// one byte, for every 30 integers (pc_w30_*; 2, 3 and 5 belong to every wheel
+// of c >= 3 primes), so that 2^18 bits span 983 040 integers where an odd-only
+// bitmap spans 524 288: fewer segments, so fewer visits of a sieving prime to
+// a segment, fewer gather rounds and a longer run of multiples per visit (one
+// pi(10^18): 49.9 -> 39.7 ms per launch).  Column j < nb stands for the
 // sieving prime b = c + 1 + j (p_{c+1} .. p_bmax, bmax = pi(isqrt z)); column
 // nb is the state after every sieving prime is crossed.  For every
 // (segment, column) the kernel records
@@ -19,7 +23,7 @@
 // instead of a count pass and a leaf pass; PC_MODE_COUNT / PC_MODE_LEAVES run
 // the two-pass form for cross-checking).
 //
-// Crossing p_b clears every odd multiple k p_b, k >= 1, including p_b itself:
+// Crossing p_b clears every multiple k p_b, k >= 1, including p_b itself:
 // phi(u, b) counts integers coprime to p_1..p_b, so p_b must go (unlike a
 // prime sieve).  Per column the workgroup first answers the leaves, then
 // crosses.  Columns are processed in order; for primes with p^3 >= hi (every
@@ -39,6 +43,9 @@
 #endif
 
 
+// four words of the bitmap read at once
+typedef uint32_t pc_quad __attribute__((ext_vector_type(4), may_alias));
+
 // Waves per SIMD that the LDS footprint of k_sieve<LOG2_S, T, CH> allows on a
 // CU (160 KiB of LDS, at most 8 waves per SIMD); the kernel asks the compiler
 // to fit its registers to that many, so a code change cannot silently cost a
@@ -49,10 +56,10 @@ template <int LOG2_S, int T, int CH> constexpr uint32_t pc_sieve_gcap()
 }
 template <int LOG2_S, int T, int CH> constexpr int pc_sieve_waves_per_simd()
 {
-    constexpr long S = 1l << LOG2_S, NW = S / 32, NWP = NW + NW / 16, NBLK = S >> 9;
+    constexpr long S = 1l << LOG2_S, NW = S / 32, NBLK = S >> 9;
     constexpr long NWV = T / 64;
     constexpr long KMAX = 64; // gathered columns per round (g_rc, g_rm)
-    constexpr long lds = 4 * (NWP + 16) + 4 * (NBLK + 1) + 4 * pc_sieve_gcap<LOG2_S, T, CH>() +
+    constexpr long lds = 4 * (NW + 16) + 4 * (NBLK + 1) + 4 * pc_sieve_gcap<LOG2_S, T, CH>() +
                          2 * KMAX * NWV + 8 * KMAX + 24 * CH + 16 * (CH / 64) + 8 + 8 * NWV +
                          16 * NWV;
     constexpr long wg = 163840 / lds;
@@ -66,34 +73,39 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
 {
     static_assert(CH == T, "one lane per column of a chunk");
     static_assert(T % 64 == 0, "wavefront multiples");
-    constexpr uint32_t S = 1u << LOG2_S;   // odd integers (bits) per segment
+    constexpr uint32_t S = 1u << LOG2_S;   // integers prime to 30 (bits) per segment
+    constexpr uint32_t SPAN = S / 8 * 30;  // integers it covers
     constexpr uint32_t NW = S / 32;        // 32-bit words
-    constexpr uint32_t NWP = NW + NW / 16; // padded: one spare word after every 16
     constexpr uint32_t BL = 9;             // 512-bit counting blocks (16 words)
     constexpr uint32_t NBLK = S >> BL;
     constexpr uint32_t NWV = T / 64;
     constexpr uint32_t BPT = NBLK / T; // counting blocks per thread
     static_assert(NBLK % T == 0 && BPT >= 1 && BPT <= 2, "every thread counts one or two blocks");
     constexpr uint32_t RS = S / NWV;   // bits of the region a wavefront owns
+    constexpr uint32_t RSB = RS / 8, RSI = RSB * 30; // its bytes, the integers it covers
     constexpr uint32_t RSL = LOG2_S - (NWV == 1 ? 0 : NWV == 2 ? 1 : NWV == 4 ? 2 : NWV == 8 ? 3 : 4);
     static_assert((1u << RSL) == RS && RS == 64 * BPT * 512, "a region is 64 threads' blocks");
     constexpr uint32_t GCAP = pc_sieve_gcap<LOG2_S, T, CH>(); // gathered leaf items
     constexpr uint32_t LIGHT = GCAP / 4; // more leaf items: the column is answered workgroup-wide
-    constexpr uint32_t XB_P = RS / 32;   // p >= XB_P: at most 32 multiples in a wave's region
+    // p >= XB_P: at most 112 consecutive multipliers k reach a wave's region, so
+    // at most 31 of its multiples there are prime to 30
+    constexpr uint32_t XB_P = RSI / 112 + 1;
     constexpr uint32_t KMAX = 64;         // columns per gather round (as in pc_sieve_waves_per_simd)
     static_assert(GCAP < 2048 && LIGHT < 2048, "gathered-column fields");
     static_assert(GCAP >= 64 * NWV, "64 slots of gbuf per wave in a heavy column");
 
-    // Word w of the segment lives at bm[w + w/16]: the 16 words of a counting
-    // block are contiguous and consecutive blocks start 17 words apart, so the
-    // threads of a wavefront walking their own blocks hit distinct banks.
-    __shared__ uint32_t bm[NWP + 16];  // 16 spare words: a query at q = S reads past the end
+    // Word w of the segment is bm[w]; no padding, so a crossing's address is
+    // its byte offset with two bits masked.  Threads that count their own
+    // blocks read them 16 bytes at a time, each starting at another 16 bytes of
+    // its block (rot), which keeps a wavefront's reads on distinct banks.
+    __shared__ __attribute__((aligned(16))) uint32_t bm[NW + 16]; // 16 spare words: a query at
+                                                                  // q = S reads past the end
     __shared__ uint32_t pre[NBLK + 1]; // prefix of the block counts; or a gather round's table
     __shared__ uint32_t gbuf[GCAP];    // gathered leaves: k << 22 | q << 2 | (mu(m) > 0) << 1 | 1
     __shared__ uint16_t g_rc[KMAX * NWV]; // each wave's region count at gathered column k
     __shared__ uint32_t g_rm[2 * KMAX];   // regions that hold a leaf of gathered column k (2 rounds)
     __shared__ uint32_t c_p[CH];       // p_b
-    __shared__ uint32_t c_i0[CH];      // bit of the first multiple in the segment, S if none
+    __shared__ uint32_t c_rem[CH];     // (lo / 30) mod p_b
     __shared__ uint32_t c_ls[CH];      // first leaf item (m, or index of the prime m)
     __shared__ uint32_t c_lc[CH];      // leaf items; PC_CAND: items are candidates (pc_wheel_m)
     __shared__ uint32_t c_new[CH];     // integers first removed by p_b in this segment
@@ -142,8 +154,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return;
     }
     const uint64_t seg = tile.seg;
-    const uint64_t lo = A.lo_base + ((seg - A.seg_base) << (LOG2_S + 1));
-    const uint64_t hi = lo + (2ull << LOG2_S);
+    const uint64_t lo = A.lo_base + (seg - A.seg_base) * SPAN;
+    const uint64_t hi = lo + SPAN;
+    const uint64_t lob = lo / 30; // the segment's first byte (lo is a multiple of 30)
     const uint64_t row = seg - A.seg0;
     const pc_query &Q = A.Qs[tile.q];
     // this row's cells of cnt / wgt: columns [0, r_len) from r_off on (a
@@ -160,12 +173,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     const uint64_t rhi = pc_recip(hi);
     const uint64_t rlo = lo ? pc_recip(lo) : 0;
     const uint32_t ncol = Q.ncol;
-#define BW(w) bm[(w) + ((w) >> 4)]
 
-    // --- pre-sieved state: the wheel pattern (p_2..p_c already crossed) ---
+    // --- pre-sieved state: the wheel pattern (p_4..p_c already crossed) ---
     {
         const uint32_t P = TB.pattern_bits;
-        const uint32_t g0 = (uint32_t)((lo >> 1) % P);
+        const uint32_t g0 = (uint32_t)((8 * lob) % P);
         const uint32_t step = (32u * T) % P; // from word w to word w + T
         uint32_t off = (uint32_t)(((uint64_t)g0 + 32u * tid) % P);
         for (uint32_t w = tid; w < NW; w += T) {
@@ -173,7 +185,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             uint32_t v = TB.pattern[wi] >> sh;
             if (sh)
                 v |= TB.pattern[wi + 1] << (32 - sh);
-            BW(w) = v;
+            bm[w] = v;
             off += step;
             if (off >= P)
                 off -= P;
@@ -183,20 +195,49 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         g_rm[tid] = 0;
     __syncthreads();
 
+    // Thread tid's 16 BPT words, in quads of four; the step-th quad it reads is
+    // step ^ rot, so that 16 consecutive threads read 16 distinct quads of the
+    // banks at a time.
+    constexpr uint32_t QPT = 4 * BPT;
+    const uint32_t rot = BPT == 1 ? (tid >> 2) & 3u : (tid >> 1) & 7u;
+    const pc_quad *const bmq = reinterpret_cast<const pc_quad *>(bm) + tid * QPT;
+    auto quad_count = [&](uint32_t step) -> uint32_t {
+        const pc_quad v = bmq[step ^ rot];
+        return (uint32_t)(__builtin_popcount(v.x) + __builtin_popcount(v.y) +
+                          __builtin_popcount(v.z) + __builtin_popcount(v.w));
+    };
+    // unsieved integers in each quarter (of 128 BPT bits) of thread tid's words
+    auto quarter_counts = [&](uint32_t (&qs)[4]) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            qs[k] = quad_count(k * BPT);
+            if (BPT > 1)
+                qs[k] += quad_count(k * BPT + 1);
+        }
+        // what was read k-th is quarter k ^ (rot / BPT): put back in order
+        const uint32_t r = rot / BPT;
+        auto swap_if = [](bool s, uint32_t &a, uint32_t &b) {
+            const uint32_t t = s ? b : a;
+            b = s ? a : b;
+            a = t;
+        };
+        swap_if(r & 1u, qs[0], qs[1]);
+        swap_if(r & 1u, qs[2], qs[3]);
+        swap_if(r & 2u, qs[0], qs[2]);
+        swap_if(r & 2u, qs[1], qs[3]);
+    };
     // unsieved integers in each of the blocks thread tid counts
     auto block_counts = [&](uint32_t (&cnt)[BPT]) -> uint32_t {
-        uint32_t s = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < BPT; k++) {
-            const uint32_t base = (tid * BPT + k) * 17;
-            uint32_t c = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < 16; i++)
-                c += (uint32_t)__builtin_popcount(bm[base + i]);
-            cnt[k] = c;
-            s += c;
+        if constexpr (BPT == 1) {
+            cnt[0] = quad_count(0) + quad_count(1) + quad_count(2) + quad_count(3);
+            return cnt[0];
+        } else {
+            uint32_t qs[4];
+            quarter_counts(qs);
+            cnt[0] = qs[0] + qs[1];
+            cnt[1] = qs[2] + qs[3];
+            return cnt[0] + cnt[1];
         }
-        return s;
     };
     // pre[] = exclusive prefix of the unsieved counts of the blocks; returns
     // the segment total.  Every thread must call it; it ends with a barrier.
@@ -215,26 +256,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
         return tot;
     };
-    // unsieved integers among the bits of q's block below q: the block's 16
-    // words are read unconditionally and masked, so the reads issue together
-    auto in_block = [&](uint32_t q) -> uint32_t {
-        const uint32_t base = (q >> BL) * 17;
-        const uint32_t nw = (q >> 5) & 15, r = q & 31;
-        const uint32_t part = (1u << r) - 1;
-        uint32_t s = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < 16; k++) {
-            const uint32_t m = k < nw ? ~0u : (k == nw ? part : 0u);
-            s += (uint32_t)__builtin_popcount(bm[base + k] & m);
-        }
-        return s;
-    };
     // unsieved integers of q's block on q's side: below q when q lies in the
     // block's lower half (*up false), at or above q otherwise; eight words
     auto half_count = [&](uint32_t q, bool *up) -> uint32_t {
         const uint32_t nw = (q >> 5) & 15, part = (1u << (q & 31)) - 1;
         *up = nw >= 8;
-        const uint32_t base = (q >> BL) * 17 + (*up ? 8u : 0u), k0 = *up ? 8u : 0u;
+        const uint32_t base = (q >> BL) * 16 + (*up ? 8u : 0u), k0 = *up ? 8u : 0u;
         const uint32_t below = *up ? 0u : ~0u, at = *up ? ~part : part, above = ~below;
         uint32_t s = 0;
 #pragma unroll
@@ -250,41 +277,37 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         const uint32_t s = half_count(q, &up), blk = q >> BL;
         return up ? pre[blk + 1] - s : pre[blk] + s;
     };
-    // A wave's own blocks with finer sums (one block per thread): the block's
-    // unsieved count, and in *pk the prefix counts of its first one, two and
-    // three quarters of 128 bits (10 bits each).
+    // A thread's own words with finer sums: their unsieved count, and in *pk
+    // the prefix counts of the first one, two and three quarters (10 bits
+    // each: at most 768).
     auto block_counts_q = [&](uint32_t *pk) -> uint32_t {
-        const uint32_t base = tid * 17;
         uint32_t qs[4];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; k++) {
-            uint32_t c = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < 4; i++)
-                c += (uint32_t)__builtin_popcount(bm[base + 4 * k + i]);
-            qs[k] = c;
-        }
+        quarter_counts(qs);
         const uint32_t p1 = qs[0], p2 = p1 + qs[1], p3 = p2 + qs[2];
         *pk = p1 | (p2 << 10) | (p3 << 20);
         return p3 + qs[3];
     };
-    // unsieved integers of q's block below q, from the block's quarter
-    // prefixes pk and total tb: two words of q's quarter are read, the ones
-    // on q's side (up from the quarter's start, or down from its end)
+    // unsieved integers below q among the words of the thread that counts q's
+    // block, from their quarter prefixes pk and total tb: the half of q's
+    // quarter on q's side is read (up from the quarter's start, or down from
+    // its end)
+    constexpr uint32_t QW = 4 * BPT, HW = QW / 2; // words of a quarter, of half of one
     auto quarter_count = [&](uint32_t q, uint32_t pk, uint32_t tb) -> uint32_t {
-        const uint32_t off = q & 511u, qq = off >> 7, w = (off >> 5) & 3u;
+        const uint32_t w = (q >> 5) & (QW - 1), qq = (q >> 5) / QW & 3u;
         const uint32_t part = (1u << (q & 31u)) - 1u; // bits below q in its word
         const uint32_t below = qq ? (pk >> (10u * (qq - 1u))) & 1023u : 0u;
         const uint32_t through = qq < 3u ? (pk >> (10u * qq)) & 1023u : tb;
-        const bool low = w < 2u;
-        const uint32_t a0 = (q >> BL) * 17u + qq * 4u + (low ? 0u : 2u);
-        const uint32_t v0 = bm[a0], v1 = bm[a0 + 1];
-        if (low) // words [0, w) of the quarter and the part of w below q
-            return below + (uint32_t)__builtin_popcount(v0 & (w == 0u ? part : ~0u)) +
-                   (uint32_t)__builtin_popcount(v1 & (w == 1u ? part : 0u));
-        // the quarter less the rest of w and the words after it
-        return through - (uint32_t)__builtin_popcount(v0 & (w == 2u ? ~part : 0u)) -
-               (uint32_t)__builtin_popcount(v1 & (w == 2u ? ~0u : ~part));
+        const bool up = w >= HW;
+        const uint32_t *const v = bm + ((q >> 5) & ~(QW - 1)) + (up ? HW : 0u);
+        const uint32_t wh = up ? w - HW : w; // q's word in the half
+        uint32_t lt = 0, all = 0;            // bits of the half below q, all of them
+#pragma unroll
+        for (uint32_t k = 0; k < HW; k++) {
+            const uint32_t b = v[k];
+            lt += (uint32_t)__builtin_popcount(b & (k < wh ? ~0u : k == wh ? part : 0u));
+            all += (uint32_t)__builtin_popcount(b);
+        }
+        return up ? through - (all - lt) : below + lt;
     };
 
     uint32_t total = build_pre();
@@ -295,6 +318,42 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t R0 = wv * RS, R1 = R0 + RS;
     uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[R1 >> BL] - pre[R0 >> BL]));
+    // floor(e / p), e < 2^27, quotient < 2^17: the fp32 reciprocal rp of p puts
+    // the estimate within one of it, one step corrects it
+    auto small_quot = [](uint32_t e, uint32_t p, float rp) -> uint32_t {
+        uint32_t q = (uint32_t)((float)e * rp);
+        const int32_t r = (int32_t)(e - q * p);
+        if (r < 0)
+            q--;
+        else if (r >= (int32_t)p)
+            q++;
+        return q;
+    };
+    // The lane's part of a crossing (cross_k): res(i), i = lane mod 8, and for
+    // each residue g the byte floor(res(g) res(i) / 30) << 3 | its bit
+    const uint32_t l_res = pc_w30_res(lane & 7u);
+    uint32_t l_tab0 = 0, l_tab1 = 0;
+#pragma unroll
+    for (uint32_t g = 0; g < 8; g++) {
+        const uint32_t v = pc_w30_res(g) * l_res, e = v / 30u;
+        const uint32_t byte = e << 3 | (v - 30u * e) * 17u >> 6;
+        if (g < 4)
+            l_tab0 |= byte << (8 * g);
+        else
+            l_tab1 |= byte << (8 * (g - 4));
+    }
+    // unsieved integers of this wave's region below bit q of the segment (in:
+    // q lies in the region), from the lanes' counts c0, their exclusive
+    // prefix pe and quarter prefixes pq
+    auto region_count = [&](bool in, uint32_t q, uint32_t pe, uint32_t c0, uint32_t pq) -> uint32_t {
+        const int32_t src = in ? (int32_t)((q - R0) / (512 * BPT)) : 0;
+        uint32_t c = (uint32_t)__shfl((int)pe, src, 64);
+        const uint32_t tb = (uint32_t)__shfl((int)c0, src, 64);
+        const uint32_t pk = (uint32_t)__shfl((int)pq, src, 64);
+        if (in)
+            c += quarter_count(q, pk, tb);
+        return c;
+    };
     unsigned long long nleaf = 0;      // hard leaves answered by this thread
     int64_t acc_local = 0;             // sum of -mu(m) * in-segment count (hard leaves)
     int64_t acc_p2 = 0;                // sum of in-segment counts (P2 terms)
@@ -325,7 +384,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         *ok = u >= lo && u < hi;
         if (!*ok) // cannot happen if the m range is right
             atomicOr(A.err, 2);
-        return (uint32_t)((u - lo + 1) >> 1);
+        return *ok ? pc_w30_le((uint32_t)(u - lo)) : 0u;
     };
 
     const uint32_t col_lo = tile.col_lo, col_hi = tile.col_hi;
@@ -345,18 +404,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const uint64_t p = TB.primes[b];
             const uint64_t rp = TB.recip[b];
             c_p[j] = (uint32_t)p;
-            uint64_t first;
-            if (lo <= p) {
-                first = p;
-            } else {
-                uint64_t m = pc_div(lo, p, rp) * p;
-                if (m < lo)
-                    m += p;
-                if ((m & 1) == 0)
-                    m += p;
-                first = m;
-            }
-            c_i0[j] = first < hi ? (uint32_t)((first - lo - 1) >> 1) : S;
+            c_rem[j] = (uint32_t)(lob - pc_div(lob, p, rp) * p);
             large = (pc_u128)p * p * p >= hi;
             uint32_t ls = 0, lc = 0;
             // every hard leaf of b and of the later primes lies below ub.y
@@ -390,11 +438,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         const uint32_t jend = s_first_skip;
         const uint32_t first_large = BATCH ? min(s_first_large, jend) : jend;
 
-        // For 64 columns from cg0 on (one column per lane): p, the first
-        // multiple of p at or above R0 and the number of its multiples in
-        // [R0, R1), computed together; v_rem collects each column's removals
-        // in its lane and goes to c_new once per 64 columns.
-        uint32_t cg0 = 0x80000000u, v_f = 0, v_p = 1, v_nm = 0, v_rem = 0; // j - cg0 >= 64: reload
+        // For 64 columns from cg0 on (one column per lane): p, the region's
+        // first byte modulo p (v_r), and the first multiple of p in the region
+        // prime to 30, v_j p - 30 v_r integers from its start (v_d; RSI or
+        // more: none), computed together; v_rem collects each column's
+        // removals in its lane and goes to c_new once per 64 columns.  With
+        // k0 = floor(first byte / p), the multiple's multiplier is 30 k0 + v_j,
+        // v_j <= 31.
+        uint32_t cg0 = 0x80000000u, v_p = 1, v_r = 0, v_j = 0, v_d = RSI, v_rem = 0;
+            // (j - cg0 >= 64: reload)
         auto flush_removed = [&]() {
             if (v_rem)
                 atomicAdd(&c_new[cg0 + lane], v_rem);
@@ -406,65 +458,72 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 flush_removed();
                 cg0 = j;
                 v_p = 1;
-                v_nm = 0;
-                v_f = 0;
+                v_r = 0;
+                v_j = 0;
+                v_d = RSI;
                 if (j + lane < jend) {
-                    const uint32_t i0 = c_i0[j + lane], p = c_p[j + lane];
-                    // floor(e / p) for e < 2^20: the fp32 reciprocal puts the
-                    // estimate within one of the quotient, one step corrects it
+                    const uint32_t p = c_p[j + lane];
+                    const uint32_t e = c_rem[j + lane] + wv * RSB;
                     const float rp = __builtin_amdgcn_rcpf((float)p);
-                    auto quot = [&](uint32_t e) -> uint32_t {
-                        uint32_t q = (uint32_t)((float)e * rp);
-                        const int32_t r = (int32_t)(e - q * p);
-                        if (r < 0)
-                            q--;
-                        else if (r >= (int32_t)p)
-                            q++;
-                        return q;
-                    };
-                    uint32_t f = i0;
-                    if (i0 < R0) {
-                        const uint32_t d = R0 - i0, r = d - quot(d) * p;
-                        f = R0 + (r ? p - r : 0);
-                    }
+                    const uint32_t r = e - small_quot(e, p, rp) * p;
+                    // the least multiplier that reaches the region: ceil(30 r / p)
+                    const uint32_t r30 = 30u * r, q = small_quot(r30, p, rp);
                     v_p = p;
-                    v_f = f;
-                    v_nm = f < R1 ? quot(R1 - 1 - f) + 1 : 0;
+                    v_r = r;
+                    v_j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
+                    v_d = v_j * p - r30;
                 }
             }
         };
-        // cross column cg0 + k, which has nm > 0 multiples in this wave's
-        // region, one lane per multiple
-        auto cross_k = [&](int32_t k, uint32_t nm) {
+        // Cross column cg0 + k, which has a multiple in this wave's region.
+        // Lane (i, t) = (lane mod 8, lane / 8) takes the multipliers
+        // 30 (k0 + t + 8 s) + res(i), s = 0, 1, ...: byte
+        // (t + 8 s) p + floor(p res(i) / 30) - v_r of the region, always the
+        // same bit of it, so its multiples lie 8 p bytes (2 p words) apart at
+        // one bit of their words.  With p = 30 a + res(g), floor(p res(i) / 30)
+        // = a res(i) + floor(res(g) res(i) / 30), which comes with the bit from
+        // byte g of the lane's table.
+        auto cross_k = [&](int32_t k) {
             PC_EV(0);
-            const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)v_f, k);
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)v_p, k);
-            // a lane's multiples lie 64 p bits apart, a multiple of 32: they
-            // all sit at the same bit of their words, 2 p words apart
-            const uint32_t bit = f + lane * p;
-            const uint32_t sh = bit & 31, keep = ~(1u << sh), wstep = 2 * p;
-            uint32_t w = bit >> 5;
-            auto clear = [&](uint32_t wd) -> uint32_t {
-                const uint32_t old = __hip_atomic_fetch_and(&BW(wd), keep, __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+            const int32_t r = __builtin_amdgcn_readlane((int)v_r, k);
+            const uint32_t a = p / 30u, g = ((p - 30u * a) * 17u) >> 6; // g: the residue's number
+            const uint32_t eb = __builtin_amdgcn_perm(l_tab1, l_tab0, 0x0c0c0c00u | g);
+            // byte offset from the region's start (negative or past its end: none)
+            int32_t at = (int32_t)((lane >> 3) * p + l_res * a + (eb >> 3)) - r;
+            const uint32_t sh = ((uint32_t)at << 3 | (eb & 7u)) & 31u, keep = ~(1u << sh);
+            const int32_t step = (int32_t)(8u * p);
+            char *const rb = reinterpret_cast<char *>(bm) + wv * RSB;
+            auto clear = [&](int32_t o) -> uint32_t {
+                const uint32_t old =
+                    __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(rb + (o & ~3)), keep,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 return (old >> sh) & 1u;
             };
-            uint32_t removed = 0;
-            const uint32_t full = nm >> 6; // rounds in which every lane has a multiple
-            if (full) {
-                uint32_t hits = 0, t = 0;
-                for (; t + 2 <= full; t += 2, w += 2 * wstep) // two clears in flight
-                    hits += clear(w) + clear(w + wstep);
-                if (t < full) {
-                    hits += clear(w);
-                    w += wstep;
+            auto masked = [&]() -> uint32_t { // a round some of whose lanes may lie outside
+                bool hit = false;
+                if ((uint32_t)at < RSB)
+                    hit = clear(at) != 0;
+                at += step;
+                return (uint32_t)__builtin_popcountll(__ballot(hit));
+            };
+            uint32_t removed = masked();
+            // Round s: -p < byte - s step < step.  From s = 1 on no lane lies
+            // below the region, and none past its end while (s + 1) step <= RSB.
+            int32_t top = 2 * step; // of the next round
+            if (top <= (int32_t)RSB) {
+                uint32_t hits = 0;
+                for (; top + step <= (int32_t)RSB; top += 2 * step, at += 2 * step)
+                    hits += clear(at) + clear(at + step); // two clears in flight
+                if (top <= (int32_t)RSB) {
+                    hits += clear(at);
+                    at += step;
+                    top += step;
                 }
-                removed = pc_wave_sum_u32(hits);
+                removed += pc_wave_sum_u32(hits);
             }
-            bool hit = false;
-            if (lane < (nm & 63))
-                hit = clear(w) != 0;
-            removed += (uint32_t)__builtin_popcountll(__ballot(hit));
+            for (; top - step < (int32_t)(RSB + p); top += step)
+                removed += masked();
             rc -= removed;
             if (lane == (uint32_t)k)
                 v_rem = removed;
@@ -472,9 +531,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         auto cross_region = [&](uint32_t j) {
             ensure_group(j);
             const int32_t k = (int32_t)(j - cg0);
-            const uint32_t nm = (uint32_t)__builtin_amdgcn_readlane((int)v_nm, k);
-            if (nm)
-                cross_k(k, nm);
+            if ((uint32_t)__builtin_amdgcn_readlane((int)v_d, k) < RSI)
+                cross_k(k);
         };
         // Large columns [ja, jb) of the cached group (every one at or past
         // first_large, with p >= XB_P) crossed in this wave's region in one
@@ -488,24 +546,40 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         // below them of the earlier columns.
         auto xbatch = [&](uint32_t ja, uint32_t jb, uint32_t es0, uint32_t es1) {
             const uint32_t col = cg0 + lane;
-            const uint32_t nm = col >= ja && col < jb ? v_nm : 0u;
-            const uint32_t f = v_f, p = v_p;
-            // n = lo + 2 bit + 1 >= p^2  <=>  bit >= tb;  n = p  <=>  bit = ip
-            const uint64_t p2 = (uint64_t)p * p;
-            const uint32_t tb = p2 <= lo ? 0u : (uint32_t)min<uint64_t>(S, (p2 - lo - 1) >> 1);
-            const uint32_t ip = lo <= p ? (uint32_t)((p - lo - 1) >> 1) : S;
-            uint32_t cm = 0; // credited multiples: bit i <-> f + i p
-            for (uint32_t i = 0; __ballot(i < nm); i++)
-                if (i < nm) {
-                    const uint32_t bit = f + i * p;
-                    if (((BW(bit >> 5) >> (bit & 31)) & 1u) && (bit >= tb || bit == ip))
-                        cm |= 1u << i;
-                }
+            const uint32_t p = v_p, d0 = col >= ja && col < jb ? v_d : RSI;
+            const uint32_t *const rw = bm + wv * (RS / 32);
+            // the gaps between multipliers from the first one on, a nibble each
+            const uint32_t gi = (v_j * 17u >> 6) & 7u; // (v_j = 31 is residue 1 again: 0)
+            const uint32_t gap0 = __builtin_amdgcn_alignbit(PC_W30_GAPS, PC_W30_GAPS, 4u * gi);
+            // n = rlo + d >= p^2  <=>  d >= tb;  n = p  <=>  d = ip
+            const uint64_t p2 = (uint64_t)p * p, rlo = lo + wv * RSI;
+            const uint32_t tb = p2 <= rlo ? 0u : (uint32_t)min<uint64_t>(RSI, p2 - rlo);
+            const uint32_t ip = rlo <= p ? (uint32_t)(p - rlo) : RSI;
+            uint32_t cm = 0; // credited multiples: bit i <-> the region's i-th multiple
+            {
+                uint32_t d = d0, gap = gap0;
+                for (uint32_t i = 1; __ballot(d < RSI); i <<= 1)
+                    if (d < RSI) {
+                        const uint32_t bit = pc_w30_bit(d);
+                        if (((rw[bit >> 5] >> (bit & 31)) & 1u) && (d >= tb || d == ip))
+                            cm |= i;
+                        d += (gap & 15u) * p;
+                        gap = __builtin_amdgcn_alignbit(gap, gap, 4);
+                    }
+            }
             if (es0 < es1) {
                 bool have = false;
                 uint32_t pe = 0, pc0 = 0, pq = 0; // lane prefix of the region's block counts;
                 // first block (or, one block a lane, its count and quarter prefixes)
                 const float rp = __builtin_amdgcn_rcpf((float)p);
+                // multiples of a column with prime pc, region remainder r and
+                // first multiplier j (a before it) up to n integers past the
+                // region's start: multipliers k <= (n + 30 r) / p
+                auto multiples_to = [&](uint32_t n, uint32_t pc, float rpc, uint32_t r,
+                                        uint32_t j) -> uint32_t {
+                    const uint32_t k = small_quot(n + 30u * r, pc, rpc);
+                    return pc_w30_le(k) - (j == 31u ? 8u : j * 17u >> 6);
+                };
                 for (uint32_t s = es0; s < es1; s += 64) {
                     const uint32_t e = s + lane < es1 ? gbuf[s + lane] : 0u;
                     const uint32_t q = (e >> 2) & 0xFFFFFu;
@@ -514,32 +588,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     if (!pend)
                         continue;
                     if (!have) {
-                        uint32_t sum;
-                        if (BPT > 1) {
-                            uint32_t cnt[BPT];
-                            sum = block_counts(cnt);
-                            pc0 = cnt[0];
-                        } else {
-                            sum = block_counts_q(&pq);
-                            pc0 = sum;
-                        }
-                        pe = pc_wave_incl_scan_u32(sum) - sum;
+                        pc0 = block_counts_q(&pq);
+                        pe = pc_wave_incl_scan_u32(pc0) - pc0;
                         have = true;
                     }
-                    const uint32_t bl = in ? (q >> BL) - (R0 >> BL) : 0u;
-                    const uint32_t src = bl / BPT;
-                    uint32_t c = (uint32_t)__shfl((int)pe, (int)src, 64);
-                    if (BPT > 1) {
-                        const uint32_t c0 = (uint32_t)__shfl((int)pc0, (int)src, 64);
-                        c += (bl % BPT) ? c0 : 0u;
-                        if (in)
-                            c += in_block(q);
-                    } else { // the block is its lane's: count from its quarter prefixes
-                        const uint32_t tb = (uint32_t)__shfl((int)pc0, (int)src, 64);
-                        const uint32_t pk = (uint32_t)__shfl((int)pq, (int)src, 64);
-                        if (in)
-                            c += quarter_count(q, pk, tb);
-                    }
+                    uint32_t c = region_count(in, q, pe, pc0, pq);
                     // less the earlier columns' credited multiples below q:
                     // leaf by leaf (all lanes count for one leaf) or column
                     // by column (all leaves count one column), the shorter
@@ -551,15 +604,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                             const uint32_t ql = (uint32_t)__builtin_amdgcn_readlane((int)q, l);
                             const uint32_t kl = (uint32_t)__builtin_amdgcn_readlane((int)e, l) >> 22;
                             uint32_t below = 0;
-                            if (lane < kl && cm != 0 && ql > f) {
-                                const uint32_t d = ql - f - 1; // multiples f + t p, t <= d / p
-                                uint32_t t = (uint32_t)((float)d * rp);
-                                const int32_t r = (int32_t)(d - t * p);
-                                if (r < 0)
-                                    t--;
-                                else if (r >= (int32_t)p)
-                                    t++;
-                                below = (uint32_t)__builtin_popcount(t >= 31 ? cm : cm & ((2u << t) - 1));
+                            if (ql > R0) {
+                                const uint32_t n = pc_w30_int(ql - R0 - 1); // the last integer counted
+                                if (lane < kl && cm != 0 && n >= d0) {
+                                    const uint32_t t = multiples_to(n, p, rp, v_r, v_j); // 1 .. 31
+                                    below = (uint32_t)__builtin_popcount(cm & ((1u << t) - 1u));
+                                }
                             }
                             const uint32_t tot = pc_wave_sum_u32(below);
                             if (lane == (uint32_t)l)
@@ -567,21 +617,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                         }
                     } else {
                         const uint32_t ke = e >> 22;
+                        const uint32_t n = in && q > R0 ? pc_w30_int(q - R0 - 1) : 0u;
                         while (cols) {
                             const int32_t k = (int32_t)__builtin_ctzll(cols);
                             cols &= cols - 1;
-                            const uint32_t fk = (uint32_t)__builtin_amdgcn_readlane((int)f, k);
+                            const uint32_t dk = (uint32_t)__builtin_amdgcn_readlane((int)d0, k);
                             const uint32_t pk = (uint32_t)__builtin_amdgcn_readlane((int)p, k);
                             const uint32_t ck = (uint32_t)__builtin_amdgcn_readlane((int)cm, k);
-                            if (in && ke > (uint32_t)k && q > fk) {
-                                const uint32_t d = q - fk - 1;
-                                uint32_t t = (uint32_t)((float)d * __builtin_amdgcn_rcpf((float)pk));
-                                const int32_t r = (int32_t)(d - t * pk);
-                                if (r < 0)
-                                    t--;
-                                else if (r >= (int32_t)pk)
-                                    t++;
-                                c -= (uint32_t)__builtin_popcount(t >= 31 ? ck : ck & ((2u << t) - 1));
+                            const uint32_t rk = (uint32_t)__builtin_amdgcn_readlane((int)v_r, k);
+                            const uint32_t jk = (uint32_t)__builtin_amdgcn_readlane((int)v_j, k);
+                            if (in && q > R0 && ke > (uint32_t)k && n >= dk) {
+                                const uint32_t t =
+                                    multiples_to(n, pk, __builtin_amdgcn_rcpf((float)pk), rk, jk);
+                                c -= (uint32_t)__builtin_popcount(ck & ((1u << t) - 1u));
                             }
                         }
                     }
@@ -589,14 +637,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                         acc_local += (e & 2) ? -(int64_t)c : (int64_t)c;
                 }
             }
-            for (uint32_t i = 0; __ballot(i < nm); i++)
-                if (i < nm) {
-                    const uint32_t bit = f + i * p;
-                    __hip_atomic_fetch_and(&BW(bit >> 5), ~(1u << (bit & 31)), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
+            {
+                uint32_t d = d0, gap = gap0;
+                while (__ballot(d < RSI))
+                    if (d < RSI) {
+                        const uint32_t bit = pc_w30_bit(d);
+                        __hip_atomic_fetch_and(bm + wv * (RS / 32) + (bit >> 5), ~(1u << (bit & 31)),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        d += (gap & 15u) * p;
+                        gap = __builtin_amdgcn_alignbit(gap, gap, 4);
+                    }
+            }
             const uint32_t cr = (uint32_t)__builtin_popcount(cm);
-            if (nm)
+            if (d0 < RSI)
                 v_rem = cr;
             rc -= pc_wave_sum_u32(cr);
         };
@@ -616,11 +669,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 ensure_group(j);
                 const uint32_t ge = min(je, cg0 + 64);
                 const uint32_t xb = xbatch_from(j, ge);
-                uint64_t msk = __ballot(v_nm != 0 && cg0 + lane >= j && cg0 + lane < xb);
+                uint64_t msk = __ballot(v_d < RSI && cg0 + lane >= j && cg0 + lane < xb);
                 while (msk) {
                     const int32_t k = (int32_t)__builtin_ctzll(msk);
                     msk &= msk - 1;
-                    cross_k(k, (uint32_t)__builtin_amdgcn_readlane((int)v_nm, k));
+                    cross_k(k);
                 }
                 if (xb < ge)
                     xbatch(xb, ge, 0, 0);
@@ -763,34 +816,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 const bool in = (e & 1) && (q >> RSL) == wv;
                 if (__ballot(in)) {
                     if (!have) {
-                        uint32_t sum;
-                        if (BPT > 1) {
-                            uint32_t cnt[BPT];
-                            sum = block_counts(cnt);
-                            pc0 = cnt[0];
-                        } else {
-                            sum = block_counts_q(&pq);
-                            pc0 = sum;
-                        }
-                        pe = pc_wave_incl_scan_u32(sum) - sum;
+                        pc0 = block_counts_q(&pq);
+                        pe = pc_wave_incl_scan_u32(pc0) - pc0;
                         have = true;
                     }
-                    const uint32_t bl = in ? (q >> BL) - (R0 >> BL) : 0u;
-                    const uint32_t src = bl / BPT;
-                    uint32_t c = (uint32_t)__shfl((int)pe, (int)src, 64);
-                    if (BPT > 1) {
-                        const uint32_t c0 = (uint32_t)__shfl((int)pc0, (int)src, 64);
-                        c += (bl % BPT) ? c0 : 0u;
-                    }
-                    const uint32_t tb = (uint32_t)__shfl((int)pc0, (int)src, 64);
-                    const uint32_t pk = (uint32_t)__shfl((int)pq, (int)src, 64);
-                    if (in) {
-                        if (BPT > 1)
-                            c += in_block(q);
-                        else // the block is its lane's: count from its quarter prefixes
-                            c += quarter_count(q, pk, tb);
+                    const uint32_t c = region_count(in, q, pe, pc0, pq);
+                    if (in)
                         acc_local += (e & 2) ? -(int64_t)c : (int64_t)c;
-                    }
                 }
             }
         };
@@ -907,7 +939,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const uint32_t rm = gath ? g_rm[g_par * KMAX + lane] : 0u;
             const bool mine = gath && ((rm >> wv) & 1u);
             const uint64_t own = __ballot(mine && sm);
-            const uint64_t crs = __ballot(inw && sm && v_nm != 0);
+            const uint64_t crs = __ballot(inw && sm && v_d < RSI);
             uint64_t todo = own | crs;
             while (todo) {
                 const int32_t k = (int32_t)__builtin_ctzll(todo);
@@ -915,7 +947,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 if ((own >> k) & 1)
                     answer((uint32_t)__builtin_amdgcn_readlane((int)g, k));
                 if ((crs >> k) & 1)
-                    cross_k(k, (uint32_t)__builtin_amdgcn_readlane((int)v_nm, k));
+                    cross_k(k);
             }
             if (xb < we) {
                 // the large columns' slots run from the first one gathered to
@@ -1008,19 +1040,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             // order, one thread per column.  Its stored counts are 0.
             for (uint32_t col = cb + jend + tid; col < ncross; col += T) {
                 const uint32_t b = qc + 1 + col;
-                const uint64_t p = TB.primes[b];
-                uint64_t first = p;
-                if (lo > p) {
-                    first = pc_div(lo, p, TB.recip[b]) * p;
-                    if (first < lo)
-                        first += p;
-                    if ((first & 1) == 0)
-                        first += p;
+                const uint32_t p = TB.primes[b];
+                const uint32_t r30 = 30u * (uint32_t)(lob - pc_div(lob, p, TB.recip[b]) * p);
+                const uint32_t q = small_quot(r30, p, __builtin_amdgcn_rcpf((float)p));
+                const uint32_t j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
+                uint32_t gap =
+                    __builtin_amdgcn_alignbit(PC_W30_GAPS, PC_W30_GAPS, 4u * ((j * 17u >> 6) & 7u));
+                for (uint32_t d = j * p - r30; d < SPAN;) {
+                    const uint32_t bit = pc_w30_bit(d);
+                    __hip_atomic_fetch_and(bm + (bit >> 5), ~(1u << (bit & 31)), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    d += (gap & 15u) * p;
+                    gap = __builtin_amdgcn_alignbit(gap, gap, 4);
                 }
-                if (first < hi)
-                    for (uint32_t bit = (uint32_t)((first - lo - 1) >> 1); bit < S; bit += (uint32_t)p)
-                        __hip_atomic_fetch_and(&BW(bit >> 5), ~(1u << (bit & 31)), __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (MODE != PC_MODE_LEAVES && col >= cb + jall && col < r_len && col >= col_lo &&
                     col < col_hi) {
                     Q.cnt[r_off + col] = 0;
@@ -1061,14 +1093,14 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             for (uint32_t k = k1 + tid; k <= k2; k += T) {
                 uint32_t off; // x/p_k - lo
                 const bool in = k < TB.k32
-                                    ? pc_quot_in(x, xd, TB.primes[k], lo, 2u << LOG2_S, &off)
-                                    : pc_quot_in64(x, xd, TB.primes_hi[k - TB.k32], lo,
-                                                   2u << LOG2_S, &off);
+                                    ? pc_quot_in(x, xd, TB.primes[k], lo, SPAN, &off)
+                                    : pc_quot_in64(x, xd, TB.primes_hi[k - TB.k32], lo, SPAN,
+                                                   &off);
                 if (!in) {
                     atomicOr(A.err, 4);
                     continue;
                 }
-                acc_p2 += count_pre((off + 1) >> 1);
+                acc_p2 += count_pre(pc_w30_le(off));
             }
         }
         if (tid == 0) {
@@ -1081,7 +1113,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 extra_p2 = (pc_s128)np * (pc_s128)Q.carryP[row];
         }
     }
-#undef BW
     if (MODE != PC_MODE_COUNT) {
         const pc_s128 h = pc_block_sum128<T>((pc_s128)acc_local + acc_carry, scr128);
         const pc_s128 q = pc_block_sum128<T>((pc_s128)acc_p2 + extra_p2, scr128);
@@ -1125,6 +1156,52 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
 }
 #undef PC_PH
 #undef PC_EV
+
+// ---------------------------------------------------------------------------
+// Queries with c < 3 (y < 5, so x < 125 and z < 32): the same sums from the
+// definitions by one thread, the integers 1 .. z as the bits of one word.
+// ---------------------------------------------------------------------------
+__global__ void k_sieve_tiny(pc_tables T, pc_query Q)
+{
+    if (threadIdx.x != 0 || blockIdx.x != 0)
+        return;
+    uint64_t left = 0;
+    for (uint32_t n = 1; n <= (uint32_t)Q.z; n++) {
+        bool ok = true;
+        for (uint32_t i = 1; i <= Q.c; i++)
+            ok = ok && n % T.primes[i] != 0;
+        left |= (uint64_t)ok << n;
+    }
+    auto phi = [&](uint64_t u) { return (int64_t)__builtin_popcountll(left & ((2ull << u) - 1)); };
+    int64_t hard = 0, p2 = 0;
+    unsigned long long nhard = 0;
+    for (uint32_t b = Q.c + 1; b <= Q.c + Q.nb; b++) {
+        const uint64_t p = T.primes[b], h1 = Q.x / (p * p * p), h2 = Q.x / (p * Q.y1);
+        for (uint64_t m = max(Q.y / p, p) + 1; m <= min(Q.y, max(h1, h2)); m++) {
+            const int32_t v = T.mulpf[m];
+            if ((uint64_t)(v < 0 ? -v : v) <= p) // mu(m) = 0 or lpf(m) <= p_b
+                continue;
+            const int64_t f = phi(Q.x / (p * m));
+            hard += v > 0 ? -f : f;
+            nhard++;
+        }
+        for (uint32_t n = (uint32_t)p; n <= (uint32_t)Q.z; n += (uint32_t)p)
+            left &= ~(1ull << n);
+    }
+    for (uint32_t k = Q.a + 1; k <= Q.kx; k++)
+        p2 += phi(Q.x / T.primes[k]);
+    Q.sums->hard_local += hard;
+    Q.sums->p2_local += p2;
+    Q.sums->n_hard += nhard;
+}
+
+hipError_t pc_launch_sieve_tiny(const pc_tables &T, const pc_query &Q, hipStream_t s)
+{
+    if (Q.z > 62)
+        return hipErrorInvalidValue;
+    k_sieve_tiny<<<1, 64, 0, s>>>(T, Q);
+    return hipGetLastError();
+}
 
 // ---------------------------------------------------------------------------
 // Look-back scan over the segments of a window, independently per column:

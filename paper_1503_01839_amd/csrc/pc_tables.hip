@@ -6,8 +6,8 @@
 //   * 64-bit reciprocals of the primes, for exact division by invariant
 //     divisors;
 //   * mu(n)*lpf(n) for n <= y (Section 2.2: "p_min(y) mu(y)");
-//   * the wheel of size c (Section 4): the odd-only pre-sieve pattern of
-//     p_2..p_c and phi(r, c) for r below the primorial Q_c.
+//   * the wheel of size c (Section 4): the pre-sieve pattern of p_4..p_c over
+//     the integers prime to 30 and phi(r, c) for r below the primorial Q_c.
 #include "pc_block.h"
 #include "pc_internal.h"
 
@@ -451,8 +451,8 @@ hipError_t pc_launch_mulpf(const uint32_t *primes, uint32_t nsmall, uint64_t yma
 }
 
 // ---------------------------------------------------------------------------
-// Wheel of size c: pattern bit j <-> 2j+1 coprime to p_2..p_c, j < period+64;
-// phitab[r] = phi(r, c) for 0 <= r < Q_c.
+// Wheel of size c: pattern bit j <-> the j-th integer prime to 30 is coprime
+// to p_4..p_c, j < period + 64; phitab[r] = phi(r, c) for 0 <= r < Q_c.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_wheel(uint32_t c, const uint32_t *primes,
                                               uint32_t *pattern, uint32_t pattern_words,
@@ -469,9 +469,9 @@ __global__ __launch_bounds__(1024) void k_wheel(uint32_t c, const uint32_t *prim
     for (uint32_t w = t; w < pattern_words; w += 1024) {
         uint32_t word = 0;
         for (uint32_t j = 0; j < 32; j++) {
-            uint32_t n = 2 * (32 * w + j) + 1;
+            uint32_t n = pc_w30_int(32 * w + j);
             bool ok = true;
-            for (uint32_t i = 1; i < c; i++)
+            for (uint32_t i = 3; i < c; i++)
                 ok = ok && (n % P[i] != 0);
             word |= (ok ? 1u : 0u) << j;
         }
