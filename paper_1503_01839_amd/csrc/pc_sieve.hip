@@ -50,19 +50,15 @@ typedef uint32_t pc_quad __attribute__((ext_vector_type(4), may_alias));
 // CU (160 KiB of LDS, at most 8 waves per SIMD); the kernel asks the compiler
 // to fit its registers to that many, so a code change cannot silently cost a
 // resident workgroup.
-template <int LOG2_S, int T, int CH> constexpr uint32_t pc_sieve_gcap()
-{
-    return (1u << (LOG2_S - 9)) > 256u ? (1u << (LOG2_S - 9)) : 256u;
-}
+template <int T> constexpr uint32_t pc_sieve_gcap() { return 2 * T > 256 ? 2 * T : 256; }
 template <int LOG2_S, int T, int CH> constexpr int pc_sieve_waves_per_simd()
 {
     constexpr long S = 1l << LOG2_S, NW = S / 32, NBLK = S >> 9;
     constexpr long NWV = T / 64;
-    constexpr long KMAX = 64; // gathered columns per round (g_rc, g_rm)
-    constexpr long lds = 4 * (NW + 16) + 4 * (NBLK + 1) + 4 * pc_sieve_gcap<LOG2_S, T, CH>() +
-                         2 * KMAX * NWV + 8 * KMAX + 24 * CH + 16 * (CH / 64) + 8 + 8 * NWV +
-                         16 * NWV;
-    constexpr long wg = 163840 / lds;
+    constexpr long lds = 4 * (NW + 16) + 4 * (NBLK + 1) + 4 * pc_sieve_gcap<T>() + 4 * 2 * 64 +
+                         2 * (CH + 2) + 24 * CH + 16 * (CH / 64) + 8 + 8 * NWV + 16 * NWV;
+    // (the CU hands LDS out in pieces of 1280 bytes)
+    constexpr long wg = 163840 / ((lds + 1279) / 1280 * 1280);
     constexpr long waves = wg * NWV < 32 ? wg * NWV : 32;
     return waves / 4 < 1 ? 1 : (int)(waves / 4);
 }
@@ -85,13 +81,18 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     constexpr uint32_t RSB = RS / 8, RSI = RSB * 30; // its bytes, the integers it covers
     constexpr uint32_t RSL = LOG2_S - (NWV == 1 ? 0 : NWV == 2 ? 1 : NWV == 4 ? 2 : NWV == 8 ? 3 : 4);
     static_assert((1u << RSL) == RS && RS == 64 * BPT * 512, "a region is 64 threads' blocks");
-    constexpr uint32_t GCAP = pc_sieve_gcap<LOG2_S, T, CH>(); // gathered leaf items
-    constexpr uint32_t LIGHT = GCAP / 4; // more leaf items: the column is answered workgroup-wide
+    constexpr uint32_t GCAP = pc_sieve_gcap<T>(); // leaf items of a gather window
+    constexpr uint32_t SPT = GCAP / T;            // of which each thread takes SPT
+    // more leaf items: the column is answered workgroup-wide
+    constexpr uint32_t LIGHT = 127;
+    constexpr uint32_t MG = 64 / NWV < CH / 64 ? 64 / NWV : CH / 64; // groups of 64 columns of a window
+    static_assert(64 * MG * LIGHT < 65536 && LIGHT <= GCAP, "c_off counts modulo 2^16");
     // p >= XB_P: at most 112 consecutive multipliers k reach a wave's region, so
     // at most 31 of its multiples there are prime to 30
     constexpr uint32_t XB_P = RSI / 112 + 1;
-    constexpr uint32_t KMAX = 64;         // columns per gather round (as in pc_sieve_waves_per_simd)
-    static_assert(GCAP < 2048 && LIGHT < 2048, "gathered-column fields");
+    // columns that are only cleared (clear_columns): up to CLR_TINY by all
+    // threads together, from CLR_SEQ on by one lane each, between by eight
+    constexpr uint32_t CLR_TINY = 64, CLR_SEQ = SPAN / 60;
     static_assert(GCAP >= 64 * NWV, "64 slots of gbuf per wave in a heavy column");
 
     // Word w of the segment is bm[w]; no padding, so a crossing's address is
@@ -100,10 +101,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // its block (rot), which keeps a wavefront's reads on distinct banks.
     __shared__ __attribute__((aligned(16))) uint32_t bm[NW + 16]; // 16 spare words: a query at
                                                                   // q = S reads past the end
-    __shared__ uint32_t pre[NBLK + 1]; // prefix of the block counts; or a gather round's table
+    __shared__ uint32_t pre[NBLK + 1]; // prefix of the block counts
     __shared__ uint32_t gbuf[GCAP];    // gathered leaves: k << 22 | q << 2 | (mu(m) > 0) << 1 | 1
-    __shared__ uint16_t g_rc[KMAX * NWV]; // each wave's region count at gathered column k
-    __shared__ uint32_t g_rm[2 * KMAX];   // regions that hold a leaf of gathered column k (2 rounds)
+    __shared__ uint32_t g_bin[2 * 64]; // leaves per (group of columns, region) of a window (two windows)
+    __shared__ uint16_t c_off[CH + 2]; // exclusive prefix of the light columns' leaf items, mod 2^16
     __shared__ uint32_t c_p[CH];       // p_b
     __shared__ uint32_t c_rem[CH];     // (lo / 30) mod p_b
     __shared__ uint32_t c_ls[CH];      // first leaf item (m, or index of the prime m)
@@ -191,8 +192,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 off -= P;
         }
     }
-    if (tid < 2 * KMAX)
-        g_rm[tid] = 0;
+    for (uint32_t i = tid; i < 128; i += T)
+        g_bin[i] = 0;
     __syncthreads();
 
     // Thread tid's 16 BPT words, in quads of four; the step-th quad it reads is
@@ -310,14 +311,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return up ? through - (all - lt) : below + lt;
     };
 
-    uint32_t total = build_pre();
-    PC_PH(0);
-    // Wavefront wv owns bits [R0, R1).  rc = its unsieved integers, kept exact
-    // through every crossing: a leaf whose u lies in a higher region counts
-    // all of them, one in this region counts a prefix of it.
-    const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const uint32_t R0 = wv * RS, R1 = R0 + RS;
-    uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[R1 >> BL] - pre[R0 >> BL]));
     // floor(e / p), e < 2^27, quotient < 2^17: the fp32 reciprocal rp of p puts
     // the estimate within one of it, one step corrects it
     auto small_quot = [](uint32_t e, uint32_t p, float rp) -> uint32_t {
@@ -329,8 +322,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             q++;
         return q;
     };
-    // The lane's part of a crossing (cross_k): res(i), i = lane mod 8, and for
-    // each residue g the byte floor(res(g) res(i) / 30) << 3 | its bit
+    // The multiples of a prime p by residue class: the multipliers 30 k + res(i)
+    // fall on byte p k + floor(p res(i) / 30) of the integers, always at one bit
+    // of it.  With p = 30 a + res(g) the byte's part that depends on i is
+    // a res(i) + floor(res(g) res(i) / 30); the second term and the bit come
+    // from byte g of two words that a lane keeps for its i = lane mod 8.
     const uint32_t l_res = pc_w30_res(lane & 7u);
     uint32_t l_tab0 = 0, l_tab1 = 0;
 #pragma unroll
@@ -342,23 +338,106 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         else
             l_tab1 |= byte << (8 * (g - 4));
     }
+    // the lane's class of p: *bit, and the byte of 30 k + res(i) past p k
+    auto class_of = [&](uint32_t p, uint32_t *bit) -> uint32_t {
+        const uint32_t a = p / 30u, g = ((p - 30u * a) * 17u) >> 6; // g: the residue's number
+        const uint32_t eb = __builtin_amdgcn_perm(l_tab1, l_tab0, 0x0c0c0c00u | g);
+        *bit = eb & 7u;
+        return l_res * a + (eb >> 3);
+    };
+
+    // Clear the multiples of the columns [k0, k1) (their primes lie in order),
+    // in any order, with no counts: columns whose state no leaf of this tile
+    // reads.  Ends with a barrier.  Every thread must call it.
+    auto clear_columns = [&](uint32_t k0, uint32_t k1) {
+        char *const sb = reinterpret_cast<char *>(bm);
+        for (uint32_t kb = k0; kb < k1; kb += CH) {
+            const uint32_t n = min((uint32_t)CH, k1 - kb);
+            bool seq = false, tiny = false;
+            if (tid < n) {
+                const uint32_t b = qc + 1 + kb + tid, p = TB.primes[b];
+                const uint32_t rem = (uint32_t)(lob - pc_div(lob, p, TB.recip[b]) * p);
+                c_p[tid] = p;
+                c_rem[tid] = rem;
+                tiny = p < CLR_TINY;
+                seq = p >= CLR_SEQ;
+                if (seq) { // few multiples: one lane takes them in order
+                    const uint32_t r30 = 30u * rem;
+                    const uint32_t q = small_quot(r30, p, __builtin_amdgcn_rcpf((float)p));
+                    const uint32_t j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
+                    uint32_t gap = __builtin_amdgcn_alignbit(PC_W30_GAPS, PC_W30_GAPS,
+                                                             4u * ((j * 17u >> 6) & 7u));
+                    for (uint32_t d = j * p - r30; d < SPAN;) {
+                        const uint32_t bit = pc_w30_bit(d);
+                        __hip_atomic_fetch_and(bm + (bit >> 5), ~(1u << (bit & 31)),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        d += (gap & 15u) * p;
+                        gap = __builtin_amdgcn_alignbit(gap, gap, 4);
+                    }
+                }
+            }
+            const uint32_t ntiny = (uint32_t)__syncthreads_count(tiny);
+            const uint32_t nseq = (uint32_t)__syncthreads_count(seq);
+            // the smallest: a column's multiples in turn by all threads, T / 8
+            // rounds of its eight classes side by side
+            for (uint32_t k = 0; k < ntiny; k++) {
+                const uint32_t p = pc_uniform(c_p[k]), rem = pc_uniform(c_rem[k]);
+                uint32_t bit;
+                const uint32_t e = class_of(p, &bit);
+                int32_t at = (int32_t)((tid >> 3) * p + e) - (int32_t)rem;
+                const uint32_t keep = ~(1u << ((((uint32_t)at << 3) | bit) & 31u));
+                if (at < 0) // T / 8 p bytes on: the same bit of the word
+                    at += (int32_t)(T / 8 * p);
+                for (; at < (int32_t)(SPAN / 30); at += (int32_t)(T / 8 * p))
+                    __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(sb + (at & ~3)), keep,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            // the others: one lane per class of a column
+            for (uint32_t k = ntiny + (tid >> 3); k < n - nseq; k += T / 8) {
+                const uint32_t p = c_p[k];
+                uint32_t bit;
+                int32_t at = (int32_t)class_of(p, &bit) - (int32_t)c_rem[k];
+                if (at < 0)
+                    at += (int32_t)p;
+                for (; at < (int32_t)(SPAN / 30); at += (int32_t)p)
+                    __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(sb + (at & ~3)),
+                                           ~(1u << ((((uint32_t)at << 3) | bit) & 31u)),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            __syncthreads();
+        }
+    };
+
+    // a tile that owns the columns from col_lo on needs the earlier ones only cleared
+    const uint32_t col_lo = tile.col_lo, col_hi = tile.col_hi;
+    if (col_lo)
+        clear_columns(0, col_lo);
+    uint32_t total = build_pre();
+    PC_PH(0);
+    // Wavefront wv owns bits [R0, R1).  rc = its unsieved integers, kept exact
+    // through every crossing: a leaf whose u lies in a higher region counts
+    // all of them, one in this region counts a prefix of it.
+    const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t R0 = wv * RS, R1 = R0 + RS;
+    uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[R1 >> BL] - pre[R0 >> BL]));
     // unsieved integers of this wave's region below bit q of the segment (in:
-    // q lies in the region), from the lanes' counts c0, their exclusive
+    // q lies in the region or at the segment's end), from the lanes' counts c0, their exclusive
     // prefix pe and quarter prefixes pq
     auto region_count = [&](bool in, uint32_t q, uint32_t pe, uint32_t c0, uint32_t pq) -> uint32_t {
-        const int32_t src = in ? (int32_t)((q - R0) / (512 * BPT)) : 0;
+        const uint32_t d = in ? q - R0 : 0u;
+        const int32_t src = (int32_t)min(d / (512 * BPT), 63u);
         uint32_t c = (uint32_t)__shfl((int)pe, src, 64);
         const uint32_t tb = (uint32_t)__shfl((int)c0, src, 64);
         const uint32_t pk = (uint32_t)__shfl((int)pq, src, 64);
-        if (in)
-            c += quarter_count(q, pk, tb);
+        if (in) // (q = S, past the last region's last bit, counts all of it)
+            c += d < RS ? quarter_count(q, pk, tb) : tb;
         return c;
     };
     unsigned long long nleaf = 0;      // hard leaves answered by this thread
     int64_t acc_local = 0;             // sum of -mu(m) * in-segment count (hard leaves)
     int64_t acc_p2 = 0;                // sum of in-segment counts (P2 terms)
     pc_s128 acc_carry = 0;             // PC_MODE_LEAVES: carry * w
-    uint32_t g_par = 0;                // g_rm half of the current gather round
+    uint32_t g_par = 0;                // g_bin half of the current window
 
     // Leaf item it of column j: *m and *w = -mu(m), false if the candidate m
     // is not squarefree with lpf(m) > p_b.
@@ -387,10 +466,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return *ok ? pc_w30_le((uint32_t)(u - lo)) : 0u;
     };
 
-    const uint32_t col_lo = tile.col_lo, col_hi = tile.col_hi;
     const uint32_t ncross = min(col_hi, Q.nb);
     bool recounted = false; // the carried count was checked against the bitmap (uniform)
-    for (uint32_t cb = 0; cb < ncross; cb += CH) {
+    for (uint32_t cb = col_lo; cb < ncross; cb += CH) {
         const uint32_t jall = min((uint32_t)CH, ncross - cb);
         if (tid == 0) {
             s_first_large = jall;
@@ -399,6 +477,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
         // --- one lane per column: first multiple, leaf range ---
         bool leafy = false, heavy = false, large = false, skip = false;
+        uint32_t light = 0; // leaf items to gather
         if (tid < jall) {
             const uint32_t j = tid, col = cb + j, b = qc + 1 + col;
             const uint64_t p = TB.primes[b];
@@ -410,7 +489,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             // every hard leaf of b and of the later primes lies below ub.y
             const ulonglong2 ub = Q.Ub[b];
             skip = ub.y < lo;
-            if (MODE != PC_MODE_COUNT && col >= col_lo && col < col_hi && ub.x < hi && !skip)
+            if (MODE != PC_MODE_COUNT && ub.x < hi && !skip)
                 pc_leaf_range(TB, Q, b, p, rp, lo, hi, rhi, rlo, &ls, &lc);
             c_ls[j] = ls;
             c_lc[j] = lc;
@@ -418,6 +497,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             c_w[j] = 0;
             leafy = lc != 0;
             heavy = (lc & ~PC_CAND) > LIGHT;
+            light = heavy ? 0u : lc & ~PC_CAND;
+            n_leafy += leafy ? 1u : 0u;
+            n_leafy_small += leafy && !large ? 1u : 0u;
+        }
+        {
+            uint32_t tot;
+            const uint32_t ex = pc_block_excl_scan<T>(light, scr32, &tot);
+            c_off[tid] = (uint16_t)ex;
+            if (tid == T - 1)
+                c_off[T] = (uint16_t)tot;
         }
         {
             const uint64_t bl = __ballot(leafy), bh = __ballot(heavy), bg = __ballot(large);
@@ -452,9 +541,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 atomicAdd(&c_new[cg0 + lane], v_rem);
             v_rem = 0;
         };
-        // the group of 64 columns that holds column j
-        auto ensure_group = [&](uint32_t j) {
-            if (j - cg0 >= 64) {
+        auto load_group = [&](uint32_t j) { // the columns from j on
+            {
                 flush_removed();
                 cg0 = j;
                 v_p = 1;
@@ -475,23 +563,25 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 }
             }
         };
+        // a group that holds column j
+        auto ensure_group = [&](uint32_t j) {
+            if (j - cg0 >= 64)
+                load_group(j);
+        };
         // Cross column cg0 + k, which has a multiple in this wave's region.
         // Lane (i, t) = (lane mod 8, lane / 8) takes the multipliers
         // 30 (k0 + t + 8 s) + res(i), s = 0, 1, ...: byte
-        // (t + 8 s) p + floor(p res(i) / 30) - v_r of the region, always the
-        // same bit of it, so its multiples lie 8 p bytes (2 p words) apart at
-        // one bit of their words.  With p = 30 a + res(g), floor(p res(i) / 30)
-        // = a res(i) + floor(res(g) res(i) / 30), which comes with the bit from
-        // byte g of the lane's table.
+        // (t + 8 s) p + floor(p res(i) / 30) - v_r of the region, so its
+        // multiples lie 8 p bytes (2 p words) apart at one bit of their words.
         auto cross_k = [&](int32_t k) {
             PC_EV(0);
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)v_p, k);
             const int32_t r = __builtin_amdgcn_readlane((int)v_r, k);
-            const uint32_t a = p / 30u, g = ((p - 30u * a) * 17u) >> 6; // g: the residue's number
-            const uint32_t eb = __builtin_amdgcn_perm(l_tab1, l_tab0, 0x0c0c0c00u | g);
+            uint32_t cb;
+            const uint32_t e = class_of(p, &cb);
             // byte offset from the region's start (negative or past its end: none)
-            int32_t at = (int32_t)((lane >> 3) * p + l_res * a + (eb >> 3)) - r;
-            const uint32_t sh = ((uint32_t)at << 3 | (eb & 7u)) & 31u, keep = ~(1u << sh);
+            int32_t at = (int32_t)((lane >> 3) * p + e) - r;
+            const uint32_t sh = ((uint32_t)at << 3 | cb) & 31u, keep = ~(1u << sh);
             const int32_t step = (int32_t)(8u * p);
             char *const rb = reinterpret_cast<char *>(bm) + wv * RSB;
             auto clear = [&](int32_t o) -> uint32_t {
@@ -540,10 +630,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         // is first removed by p exactly when k = 1 or k >= p (p^3 >= hi leaves
         // n at most two prime factors, none below the first column's prime),
         // so each lane first reads its multiples and credits those, then
-        // clears them; the order of the columns no longer matters.  Gathered
-        // leaves in slots [es0, es1) that lie in this region are answered in
-        // between: their count at the start, less the credited multiples
-        // below them of the earlier columns.
+        // clears them; the order of the columns no longer matters.  The gathered
+        // leaves [es0, es1) (all of this region) of these columns are answered in
+        // between: their count at the start, less the credited multiples below
+        // them of the earlier columns.
         auto xbatch = [&](uint32_t ja, uint32_t jb, uint32_t es0, uint32_t es1) {
             const uint32_t col = cg0 + lane;
             const uint32_t p = v_p, d0 = col >= ja && col < jb ? v_d : RSI;
@@ -583,7 +673,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 for (uint32_t s = es0; s < es1; s += 64) {
                     const uint32_t e = s + lane < es1 ? gbuf[s + lane] : 0u;
                     const uint32_t q = (e >> 2) & 0xFFFFFu;
-                    const bool in = (e & 1) && (q >> RSL) == wv;
+                    const bool in = (e & 1) && (e >> 22) >= ja - cg0;
                     uint64_t pend = __ballot(in);
                     if (!pend)
                         continue;
@@ -681,106 +771,90 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             }
         };
 
-        // Gather rounds.  The leaves of the light leafy columns of a window
-        // (whole columns of one cached group of 64, in order, stopping at the
-        // next heavy column or when GCAP slots are full) go to gbuf, one
-        // candidate per slot; column cg0 + k is the round's column k.  Each
-        // wave answers only the leaves whose u lies in its own region, and
-        // records its region count per column in g_rc; when the round is over
-        // (every wave past its columns), settle() adds, for every leaf, the
-        // counts of the regions below its own.  Every wave computes the
-        // round's slot offsets itself, and thread t only ever reads and writes
-        // slots t, t + T, ..., so a round needs two barriers.
-        uint32_t g_used = 0; // slots of the open round (uniform); 0 = none open
-        auto settle = [&]() { // after a barrier that every wave reached past the round
-            for (uint32_t s = tid; s < g_used; s += T) {
-                const uint32_t e = gbuf[s];
-                if (!(e & 1))
-                    continue;
-                const uint32_t k = e >> 22, r = min(((e >> 2) & 0xFFFFFu) >> RSL, NWV);
-                uint32_t below = 0;
-                for (uint32_t w = 0; w < r; w++)
-                    below += g_rc[k * NWV + w];
-                acc_local += (e & 2) ? -(int64_t)below : (int64_t)below;
-            }
-            g_used = 0;
+        // Gather windows.  The leaves of the light columns of a window (columns
+        // in order from a leafy one on, up to the next heavy one, MG groups of
+        // 64 columns or GCAP leaf items) are found by the whole workgroup, one
+        // item per slot, and put into gbuf in bins by (group of 64 columns,
+        // region of u), so that a wave finds the leaves of its own region, and
+        // those of the regions above it, side by side: all lanes of an answer
+        // hold leaves (in slot order one in NWV did; one pi(10^18): 39.7 -> 34.6 ms
+        // per launch), and a window needs no barrier past its gather.
+        uint32_t v_bin = 0, w_used = 0; // lane i: the first leaf of bin i in gbuf; the leaves held
+        auto bin_at = [&](uint32_t i) -> uint32_t {
+            return i < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)v_bin, (int)i) : w_used;
         };
-        // j0 lies in the cached group and we <= cg0 + 64; returns the end of
-        // the round's window: every light leafy column of [j0, that end) is
-        // gathered, and pre[k] = slot offset << 11 | items of column cg0 + k
-        // (0 for columns outside the round or without leaves).
-        auto gather = [&](uint32_t j0, uint32_t we) -> uint32_t {
+        // the window from the leafy light column j0 on; returns its end
+        auto gather = [&](uint32_t j0) -> uint32_t {
             PC_PH(4);
-            __syncthreads(); // every wave is past the open round's columns
-            settle();
+            __syncthreads(); // every wave is past the last window's leaves
             PC_EV(2);
             g_par ^= 1;
-            // the next heavy column at or after j0 ends the round
-            uint32_t hvn = jend;
+            // the next heavy column at or after j0 ends the window
+            uint32_t lim = jend;
             {
                 uint32_t wd = j0 >> 6;
                 uint64_t msk = c_heavy[wd] & (~0ull << (j0 & 63));
                 while (!msk && ++wd < (jend + 63) / 64)
                     msk = c_heavy[wd];
                 if (msk)
-                    hvn = min(jend, wd * 64 + (uint32_t)__builtin_ctzll(msk));
+                    lim = min(jend, wd * 64 + (uint32_t)__builtin_ctzll(msk));
             }
-            hvn = min(hvn, we);
-            const uint32_t col = cg0 + lane;
-            uint32_t v = 0;
-            if (col >= j0 && col < hvn)
-                v = c_lc[col] & ~PC_CAND; // light: heavy columns lie at or past hvn
-            const uint32_t inc = pc_wave_incl_scan_u32(v), off = inc - v;
-            const uint64_t over = __ballot(v != 0 && inc > GCAP);
-            const uint32_t kend = over ? (uint32_t)__builtin_ctzll(over) : 64u;
-            const uint32_t used = kend ? (uint32_t)__builtin_amdgcn_readlane((int)off, (int)(kend - 1)) +
-                                             (uint32_t)__builtin_amdgcn_readlane((int)v, (int)(kend - 1))
-                                       : 0u;
-            uint32_t *const rm = g_rm + g_par * KMAX;
-            if (tid < KMAX)
-                g_rm[(g_par ^ 1) * KMAX + tid] = 0; // the next round's masks
-            for (uint32_t s0 = 0; s0 < used; s0 += T) {
-                // the column of slot s: the last lane whose offset is <= s
-                const uint32_t s = s0 + tid;
-                uint32_t a = 0, oa = 0;
+            lim = min(lim, j0 + 64 * MG);
+            const uint32_t o0 = c_off[j0];
+            uint32_t we = j0;
+            for (uint32_t base = j0; base < lim; base += 64) {
+                const uint32_t col = base + lane;
+                bool ok = false;
+                if (col < lim)
+                    ok = ((c_off[col + 1] - o0) & 0xFFFFu) <= GCAP;
+                const uint64_t m = __ballot(ok);
+                we = base + (uint32_t)__builtin_popcountll(m);
+                if (~m)
+                    break;
+            }
+            const uint32_t used = pc_uniform((c_off[we] - o0) & 0xFFFFu);
+            const uint32_t h0 = we - j0 > 1 ? 1u << (31 - __builtin_clz(we - j0 - 1)) : 0u;
+            uint32_t *const bins = g_bin + g_par * 64;
+            if (tid < 64)
+                g_bin[(g_par ^ 1) * 64 + tid] = 0; // the next window's
+            uint32_t ee[SPT], bn[SPT], rk[SPT];
 #pragma unroll
-                for (uint32_t h = 32; h; h >>= 1) {
-                    const uint32_t o = (uint32_t)__shfl((int)off, (int)(a + h), 64);
+            for (uint32_t i = 0; i < SPT; i++) {
+                ee[i] = 0;
+                bn[i] = 0;
+                rk[i] = 0;
+                const uint32_t s = i * T + tid;
+                if (i * T + wv * 64 >= used) // (uniform in the wave)
+                    continue;
+                // the column of slot s: the last one whose offset is <= s
+                uint32_t a = j0, oa = 0;
+                for (uint32_t h = h0; h; h >>= 1) {
+                    const uint32_t c = a + h;
+                    const uint32_t o = c < we ? (c_off[c] - o0) & 0xFFFFu : 0xFFFFu;
                     if (o <= s) {
-                        a += h;
+                        a = c;
                         oa = o;
                     }
                 }
-                int32_t wl = 0;   // -mu(m) of this slot's leaf, 0 if none
-                uint32_t rl = 0xFFu; // its region (0xFF: none, or above every region)
+                int32_t wl = 0; // -mu(m) of this slot's leaf, 0 if none
                 if (s < used) {
-                    const uint32_t aj = cg0 + a;
                     uint64_t m;
                     int32_t w;
-                    uint32_t e = 0;
-                    if (leaf_filter(aj, s - oa, &m, &w)) {
+                    if (leaf_filter(a, s - oa, &m, &w)) {
                         bool ok;
-                        const uint32_t q =
-                            leaf_q(Xb1[cb + aj], wide ? Xd1[cb + aj] : 0.0, m, &ok);
+                        const uint32_t q = leaf_q(Xb1[cb + a], wide ? Xd1[cb + a] : 0.0, m, &ok);
                         if (ok) {
-                            const uint32_t r = q >> RSL;
-                            e = (a << 22) | (q << 2) | (w < 0 ? 2u : 0u) | 1u;
+                            ee[i] = ((a - j0) & 63u) << 22 | (q << 2) | (w < 0 ? 2u : 0u) | 1u;
+                            bn[i] = ((a - j0) >> 6) * NWV + min(q >> RSL, NWV - 1);
+                            rk[i] = atomicAdd(&bins[bn[i]], 1u);
                             wl = w;
-                            rl = r < NWV ? r : 0xFFu;
                             nleaf++;
                         }
                     }
-                    gbuf[s] = e;
                 }
                 // The wave's slots are consecutive, so its lanes hold runs of one
-                // column (and within a column, of one region: u falls with m).
-                // Column weights: one add per run, from a wave scan of the
-                // weights; region masks: one OR per run of (column, region).
-                const uint32_t key = s < used ? a : 0xFFu;
-                const uint32_t kr = key << 8 | rl;
-                const uint32_t kr_prev = (uint32_t)__shfl_up((int)kr, 1, 64);
-                if (rl != 0xFFu && (lane == 0 || kr_prev != kr))
-                    atomicOr(&rm[a], 1u << rl);
+                // column: its weight takes one add per run, from a wave scan.
+                const uint32_t key = s < used ? a : 0xFFFFu;
                 const uint32_t inc = pc_wave_incl_scan_u32((uint32_t)wl);
                 const uint32_t key_next = (uint32_t)__shfl_down((int)key, 1, 64);
                 const bool tail = lane == 63 || key_next != key;
@@ -788,32 +862,33 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 const int32_t pt = below ? 63 - __builtin_clzll(below) : 0;
                 const uint32_t base = (uint32_t)__shfl((int)inc, pt, 64);
                 const int32_t run = (int32_t)(inc - (below ? base : 0u));
-                if (tail && key != 0xFFu && run != 0)
-                    atomicAdd(&c_w[cg0 + key], run);
+                if (tail && key != 0xFFFFu && run != 0)
+                    atomicAdd(&c_w[key], run);
             }
-            if (wv == 0) { // the round's table
-                const bool g = lane < kend && v != 0;
-                pre[lane] = g ? (off << 11) | v : 0u;
-                n_leafy += g ? 1u : 0u;
-                n_leafy_small += g && col < first_large ? 1u : 0u;
+            __syncthreads();
+            const uint32_t n = bins[lane], inc = pc_wave_incl_scan_u32(n);
+            v_bin = inc - n;
+            w_used = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+#pragma unroll
+            for (uint32_t i = 0; i < SPT; i++) {
+                const uint32_t at = (uint32_t)__shfl((int)v_bin, (int)bn[i], 64) + rk[i];
+                if (ee[i])
+                    gbuf[at] = ee[i];
             }
-            g_used = used;
             __syncthreads();
             PC_PH(2);
-            return over ? min(hvn, cg0 + kend) : hvn;
+            return we;
         };
-        // this wave's part of the leaves of gathered column j that lie in its
-        // region: a prefix of the region for each
-        auto answer = [&](uint32_t g) {
+        // The leaves of column cg0 + k among this wave's [s0, s1) (e0: the
+        // first 64 of them, one a lane): a prefix of the region for each.
+        auto answer = [&](uint32_t k, uint32_t s0, uint32_t s1, uint32_t e0) {
             PC_EV(1);
-            const uint32_t s0 = g >> 11, s1 = s0 + (g & 0x7FFu);
             bool have = false;
-            uint32_t pe = 0, pc0 = 0, pq = 0; // lane prefix of the region's block counts;
-                // first block (or, one block a lane, its count and quarter prefixes)
+            uint32_t pe = 0, pc0 = 0, pq = 0; // the lanes' counts, as in xbatch
             for (uint32_t s = s0; s < s1; s += 64) {
-                const uint32_t e = s + lane < s1 ? gbuf[s + lane] : 0u;
+                const uint32_t e = s == s0 ? e0 : s + lane < s1 ? gbuf[s + lane] : 0u;
                 const uint32_t q = (e >> 2) & 0xFFFFFu;
-                const bool in = (e & 1) && (q >> RSL) == wv;
+                const bool in = (e & 1) && (e >> 22) == k;
                 if (__ballot(in)) {
                     if (!have) {
                         pc0 = block_counts_q(&pq);
@@ -835,8 +910,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             constexpr uint32_t HU = 2;
             PC_PH(4);
             __syncthreads(); // every wave has crossed the columns before j
-            settle();
-            build_pre();     // (its barriers also end settle's reads of gbuf)
+            build_pre();
             const uint32_t lc = c_lc[j], n = lc & ~PC_CAND, ls = c_ls[j];
             const uint64_t X = pc_uniform64(Xb1[cb + j]);
             const double Xd = wide ? Xd1[cb + j] : 0.0;
@@ -915,53 +989,51 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const uint32_t ws = pc_wave_sum_u32((uint32_t)wsum);
             if (lane == 0 && ws != 0)
                 atomicAdd(&c_w[j], (int32_t)ws);
-            if (tid == 0) {
-                n_leafy++;
-                if (j < first_large)
-                    n_leafy_small++;
-            }
             __syncthreads(); // every read of the column's state precedes its crossing
             PC_PH(3);
         };
-        // Columns [j, we) of one cached group, their light leaves gathered:
-        // each wave visits, in order, the columns that have a leaf in its
-        // region (answered before the crossing) or a multiple in it, then
-        // records its region count before each gathered column (its count at
-        // j minus the removals of the window's earlier columns).
-        auto window = [&](uint32_t j, uint32_t we) {
-            const uint32_t rc0 = rc;
-            const uint32_t col = cg0 + lane;
-            const bool inw = col >= j && col < we;
-            const uint32_t xb = xbatch_from(j, we); // columns from xb on: one xbatch step
-            const bool sm = col < xb;
-            const uint32_t g = inw ? pre[lane] : 0u; // the round's table
-            const bool gath = g != 0;
-            const uint32_t rm = gath ? g_rm[g_par * KMAX + lane] : 0u;
-            const bool mine = gath && ((rm >> wv) & 1u);
-            const uint64_t own = __ballot(mine && sm);
-            const uint64_t crs = __ballot(inw && sm && v_d < RSI);
-            uint64_t todo = own | crs;
-            while (todo) {
-                const int32_t k = (int32_t)__builtin_ctzll(todo);
-                todo &= todo - 1;
-                if ((own >> k) & 1)
-                    answer((uint32_t)__builtin_amdgcn_readlane((int)g, k));
-                if ((crs >> k) & 1)
-                    cross_k(k);
+        // Columns [j0, we), their light leaves gathered: each wave visits, in
+        // order, the columns that have leaves (those in its region are answered
+        // before the crossing) or a multiple in its region; after a group of 64
+        // columns it adds its region's count at their columns (the count at the
+        // group's start minus the removals of its earlier columns) to the
+        // leaves of the regions above.
+        auto window = [&](uint32_t j0, uint32_t we) {
+            for (uint32_t j = j0, b = 0; j < we; j += 64, b += NWV) {
+                load_group(j);
+                const uint32_t ge = min(we, j + 64);
+                const uint32_t s0 = bin_at(b + wv), s1 = bin_at(b + wv + 1), s2 = bin_at(b + NWV);
+                const uint32_t e0 = s0 + lane < s1 ? gbuf[s0 + lane] : 0u;
+                const uint32_t rc0 = rc;
+                const uint32_t col = cg0 + lane;
+                const bool inw = col < ge;
+                const uint32_t xb = xbatch_from(j, ge); // columns from xb on: one xbatch step
+                const bool sm = col < xb;
+                const uint64_t own = s0 < s1 ? __ballot(sm && c_lc[sm ? col : cg0] != 0) : 0;
+                const uint64_t crs = __ballot(sm && v_d < RSI);
+                uint64_t todo = own | crs;
+                while (todo) {
+                    const int32_t k = (int32_t)__builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    if ((own >> k) & 1)
+                        answer((uint32_t)k, s0, s1, e0);
+                    if ((crs >> k) & 1)
+                        cross_k(k);
+                }
+                if (xb < ge)
+                    xbatch(xb, ge, s0, s1);
+                if (s1 < s2) {
+                    const uint32_t rem = inw ? v_rem : 0u;
+                    const uint32_t at = rc0 - (pc_wave_incl_scan_u32(rem) - rem);
+                    int32_t t = 0;
+                    for (uint32_t s = s1; s < s2; s += 64) {
+                        const uint32_t e = s + lane < s2 ? gbuf[s + lane] : 0u;
+                        const int32_t c = __shfl((int)at, (int)(e >> 22), 64);
+                        t += e & 1 ? (e & 2 ? -c : c) : 0;
+                    }
+                    acc_local += t;
+                }
             }
-            if (xb < we) {
-                // the large columns' slots run from the first one gathered to
-                // the end of the round
-                const uint64_t gl = __ballot(mine && !sm);
-                const uint32_t es0 =
-                    gl ? (uint32_t)__builtin_amdgcn_readlane((int)g, (int)__builtin_ctzll(gl)) >> 11
-                       : g_used;
-                xbatch(xb, we, es0, g_used);
-            }
-            const uint32_t rem = inw ? v_rem : 0u;
-            const uint32_t before = pc_wave_incl_scan_u32(rem) - rem;
-            if (gath)
-                g_rc[lane * NWV + wv] = (uint16_t)(rc0 - before);
         };
         // Columns in order.  Each wave crosses its own region, so between the
         // workgroup-wide steps (gather, heavy column) the waves move through
@@ -980,9 +1052,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     heavy_col(j);
                     cross_region(j);
                     j++;
-                } else { // a window within j's group of 64 columns
-                    ensure_group(j);
-                    const uint32_t we = gather(j, min(jend, cg0 + 64));
+                } else {
+                    const uint32_t we = gather(j);
                     window(j, we);
                     j = we;
                 }
@@ -1002,8 +1073,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         }
         flush_removed();
         PC_PH(4);
-        __syncthreads(); // c_new complete; every wave is past the open round
-        settle();
+        __syncthreads(); // c_new complete; every wave is past the last window
         // --- chunk results: cnt before each crossing, and w ---
         {
             const uint32_t v = tid < jend ? c_new[tid] : 0;
@@ -1011,7 +1081,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const uint32_t ex = pc_block_excl_scan<T>(v, scr32, &tot);
             const uint32_t col = cb + tid;
             // columns at or past the cut hold no leaf here or below: 0 (if stored)
-            if (tid < jall && col < r_len && col >= col_lo && col < col_hi) {
+            if (tid < jall && col < r_len) {
                 const bool cut = tid >= jend;
                 const uint64_t idx = r_off + col;
                 if (MODE != PC_MODE_LEAVES)
@@ -1022,7 +1092,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     acc_carry += (pc_s128)c_w[tid] * (pc_s128)Q.carry[idx];
             }
             // every column before the cut must be stored: the row's bound holds
-            if (tid < jend && col >= r_len && col >= col_lo && col < col_hi)
+            if (tid < jend && col >= r_len)
                 atomicOr(A.err, 8);
             total -= tot;
         }
@@ -1036,30 +1106,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             recounted = true;
             // Every column from cb + jend on is past its last hard leaf: its
             // count is read by no leaf and it removes nothing a later leaf of
-            // this segment counts, so its multiples are only cleared, in any
-            // order, one thread per column.  Its stored counts are 0.
-            for (uint32_t col = cb + jend + tid; col < ncross; col += T) {
-                const uint32_t b = qc + 1 + col;
-                const uint32_t p = TB.primes[b];
-                const uint32_t r30 = 30u * (uint32_t)(lob - pc_div(lob, p, TB.recip[b]) * p);
-                const uint32_t q = small_quot(r30, p, __builtin_amdgcn_rcpf((float)p));
-                const uint32_t j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
-                uint32_t gap =
-                    __builtin_amdgcn_alignbit(PC_W30_GAPS, PC_W30_GAPS, 4u * ((j * 17u >> 6) & 7u));
-                for (uint32_t d = j * p - r30; d < SPAN;) {
-                    const uint32_t bit = pc_w30_bit(d);
-                    __hip_atomic_fetch_and(bm + (bit >> 5), ~(1u << (bit & 31)), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    d += (gap & 15u) * p;
-                    gap = __builtin_amdgcn_alignbit(gap, gap, 4);
-                }
-                if (MODE != PC_MODE_LEAVES && col >= cb + jall && col < r_len && col >= col_lo &&
-                    col < col_hi) {
+            // this segment counts, so its multiples are only cleared.  Its
+            // stored counts are 0.
+            if (MODE != PC_MODE_LEAVES)
+                for (uint32_t col = cb + jall + tid; col < min(ncross, r_len); col += T) {
                     Q.cnt[r_off + col] = 0;
                     if (MODE == PC_MODE_TALLY)
                         Q.wgt[r_off + col] = 0;
                 }
-            }
+            if (col_hi == ncol) // (else nothing reads the segment any more)
+                clear_columns(cb + jend, ncross);
             PC_PH(5);
             break;
         }
