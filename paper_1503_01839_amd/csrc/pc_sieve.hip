@@ -93,7 +93,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // columns that are only cleared (clear_columns): up to CLR_TINY by all
     // threads together, from CLR_SEQ on by one lane each, between by eight
     constexpr uint32_t CLR_TINY = 64, CLR_SEQ = SPAN / 60;
-    static_assert(GCAP >= 64 * NWV, "64 slots of gbuf per wave in a heavy column");
+    static_assert(GCAP >= 2 * T, "a heavy column: 64 slots of gbuf per wave, then its quarter table");
 
     // Word w of the segment is bm[w]; no padding, so a crossing's address is
     // its byte offset with two bits masked.  Threads that count their own
@@ -167,9 +167,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         Q.row_off ? pc_uniform((uint32_t)(Q.row_off[row + 1] - Q.row_off[row])) : Q.nb;
     const uint32_t qc = pc_uniform(Q.c);
     const uint64_t *const Xb1 = pc_uniform_ptr(Q.Xb) + qc + 1; // X_b of column j of chunk cb: Xb1[cb + j]
-    // above 2^64 the leaf quotients take X_b's value in fp64 beside its low word
-    const bool wide = Q.x_hi != 0;
-    const double *const Xd1 = Q.Xd + qc + 1;
+    const double *const Xd1 = pc_uniform_ptr(Q.Xd) + qc + 1; // and its value in fp64
     const pc_tables &TB = A.T;
     const uint64_t rhi = pc_recip(hi);
     const uint64_t rlo = lo ? pc_recip(lo) : 0;
@@ -311,6 +309,26 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return up ? through - (all - lt) : below + lt;
     };
 
+    // pre[] with the quarter prefixes of every thread's words beside it, in the
+    // half of gbuf that a heavy column leaves free
+    uint32_t *const preq = gbuf + GCAP - T;
+    auto build_preq = [&]() {
+        uint32_t pq;
+        const uint32_t s = block_counts_q(&pq);
+        uint32_t tot;
+        const uint32_t ex = pc_block_excl_scan<T>(s, scr32, &tot);
+        pre[tid] = ex;
+        preq[tid] = pq;
+        if (tid == T - 1)
+            pre[T] = tot;
+        __syncthreads();
+    };
+    // unsieved integers among bits [0, q), q <= S, against build_preq
+    auto count_preq = [&](uint32_t q) -> uint32_t {
+        const uint32_t i = q / (512 * BPT);
+        const uint32_t ex = pre[i];
+        return q < S ? ex + quarter_count(q, preq[i], pre[i + 1] - ex) : ex;
+    };
     // floor(e / p), e < 2^27, quotient < 2^17: the fp32 reciprocal rp of p puts
     // the estimate within one of it, one step corrects it
     auto small_quot = [](uint32_t e, uint32_t p, float rp) -> uint32_t {
@@ -441,7 +459,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
 
     // Leaf item it of column j: *m and *w = -mu(m), false if the candidate m
     // is not squarefree with lpf(m) > p_b.
-    auto leaf_filter = [&](uint32_t j, uint32_t it, uint64_t *m, int32_t *w) -> bool {
+    auto leaf_filter = [&](uint32_t j, uint32_t it, uint32_t *m, int32_t *w) -> bool {
         const uint32_t lc = c_lc[j], ls = c_ls[j];
         if (lc & PC_CAND) {
             const uint32_t mc = pc_wheel_m(TB, ls + it);
@@ -456,14 +474,23 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         *w = 1;
         return true;
     };
-    // q = bits of the segment below u = floor(X_b / m), u in [lo, hi); X is
-    // X_b modulo 2^64 and Xd its value in fp64 (read only above 2^64)
-    auto leaf_q = [&](uint64_t X, double Xd, uint64_t m, bool *ok) -> uint32_t {
-        const uint64_t u = wide ? pc_div_small_qd(X, Xd, (uint32_t)m) : pc_div_small_q(X, m);
-        *ok = u >= lo && u < hi;
+    // q = bits of the segment up to u = floor(X_b / m), u in [lo, hi); X is X_b
+    // modulo 2^32 and Xd its value in fp64.  1/m is the hardware's fp64
+    // estimate refined to a few units of 2^-53, so Xd / m is off by less than
+    // u 2^-50 <= 1/4 (u < 2^48); raised by 1/4 its floor is u or u + 1, and the
+    // remainder X_b - q m, in [-m, m), m < 2^31, is its low 32 bits: their sign
+    // decides (an IEEE division with a 64-bit remainder takes five times the
+    // instructions).
+    const double qbase = 0.25 - (double)lo;
+    auto leaf_q = [&](uint32_t X, double Xd, uint32_t m, bool *ok) -> uint32_t {
+        const double t = __builtin_fma(Xd, pc_rcp_f64(m), qbase); // u - lo, raised
+        uint32_t off = (uint32_t)(int32_t)t;
+        if ((int32_t)(X - ((uint32_t)lo + off) * m) < 0)
+            off--;
+        *ok = t > -1.0 && off < SPAN;
         if (!*ok) // cannot happen if the m range is right
             atomicOr(A.err, 2);
-        return *ok ? pc_w30_le((uint32_t)(u - lo)) : 0u;
+        return *ok ? pc_w30_le(off) : 0u;
     };
 
     const uint32_t ncross = min(col_hi, Q.nb);
@@ -662,13 +689,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 uint32_t pe = 0, pc0 = 0, pq = 0; // lane prefix of the region's block counts;
                 // first block (or, one block a lane, its count and quarter prefixes)
                 const float rp = __builtin_amdgcn_rcpf((float)p);
-                // multiples of a column with prime pc, region remainder r and
-                // first multiplier j (a before it) up to n integers past the
-                // region's start: multipliers k <= (n + 30 r) / p
-                auto multiples_to = [&](uint32_t n, uint32_t pc, float rpc, uint32_t r,
-                                        uint32_t j) -> uint32_t {
-                    const uint32_t k = small_quot(n + 30u * r, pc, rpc);
-                    return pc_w30_le(k) - (j == 31u ? 8u : j * 17u >> 6);
+                // the region's multiples of the lane's column up to n integers past
+                // its start: multipliers k <= (n + 30 v_r) / p, less those before v_j
+                const uint32_t k0 = v_j == 31u ? 8u : v_j * 17u >> 6;
+                auto multiples_to = [&](uint32_t n) -> uint32_t {
+                    return pc_w30_le(small_quot(n + 30u * v_r, p, rp)) - k0;
                 };
                 for (uint32_t s = es0; s < es1; s += 64) {
                     const uint32_t e = s + lane < es1 ? gbuf[s + lane] : 0u;
@@ -687,7 +712,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     // leaf by leaf (all lanes count for one leaf) or column
                     // by column (all leaves count one column), the shorter
                     uint64_t cols = __ballot(cm != 0);
-                    if (__builtin_popcountll(pend) <= __builtin_popcountll(cols)) {
+                    if (4 * __builtin_popcountll(pend) <= __builtin_popcountll(cols)) {
                         while (pend) {
                             const int32_t l = (int32_t)__builtin_ctzll(pend);
                             pend &= pend - 1;
@@ -697,7 +722,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                             if (ql > R0) {
                                 const uint32_t n = pc_w30_int(ql - R0 - 1); // the last integer counted
                                 if (lane < kl && cm != 0 && n >= d0) {
-                                    const uint32_t t = multiples_to(n, p, rp, v_r, v_j); // 1 .. 31
+                                    const uint32_t t = multiples_to(n); // 1 .. 31
                                     below = (uint32_t)__builtin_popcount(cm & ((1u << t) - 1u));
                                 }
                             }
@@ -706,20 +731,24 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                                 c -= tot;
                         }
                     } else {
-                        const uint32_t ke = e >> 22;
-                        const uint32_t n = in && q > R0 ? pc_w30_int(q - R0 - 1) : 0u;
+                        // n: the last integer that the leaf counts; a credited
+                        // multiple d of column k lies below it if d <= n
+                        const int32_t ke = (int32_t)(e >> 22);
+                        const int32_t n = in && q > R0 ? (int32_t)pc_w30_int(q - R0 - 1) : -1;
                         while (cols) {
                             const int32_t k = (int32_t)__builtin_ctzll(cols);
                             cols &= cols - 1;
                             const uint32_t dk = (uint32_t)__builtin_amdgcn_readlane((int)d0, k);
                             const uint32_t pk = (uint32_t)__builtin_amdgcn_readlane((int)p, k);
-                            const uint32_t ck = (uint32_t)__builtin_amdgcn_readlane((int)cm, k);
-                            const uint32_t rk = (uint32_t)__builtin_amdgcn_readlane((int)v_r, k);
-                            const uint32_t jk = (uint32_t)__builtin_amdgcn_readlane((int)v_j, k);
-                            if (in && q > R0 && ke > (uint32_t)k && n >= dk) {
-                                const uint32_t t =
-                                    multiples_to(n, pk, __builtin_amdgcn_rcpf((float)pk), rk, jk);
-                                c -= (uint32_t)__builtin_popcount(ck & ((1u << t) - 1u));
+                            const uint32_t gk = (uint32_t)__builtin_amdgcn_readlane((int)gi, k);
+                            uint32_t ck = (uint32_t)__builtin_amdgcn_readlane((int)cm, k);
+                            const int32_t nk = ke > k ? n : -1;
+                            const uint32_t r0 = pc_w30_res(gk);
+                            while (ck) { // (positions in scalar arithmetic)
+                                const uint32_t i = gk + (uint32_t)__builtin_ctz(ck);
+                                ck &= ck - 1;
+                                const uint32_t d = dk + (pc_w30_int(i) - r0) * pk;
+                                c -= (int32_t)d <= nk ? 1u : 0u;
                             }
                         }
                     }
@@ -838,11 +867,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 }
                 int32_t wl = 0; // -mu(m) of this slot's leaf, 0 if none
                 if (s < used) {
-                    uint64_t m;
+                    uint32_t m;
                     int32_t w;
                     if (leaf_filter(a, s - oa, &m, &w)) {
                         bool ok;
-                        const uint32_t q = leaf_q(Xb1[cb + a], wide ? Xd1[cb + a] : 0.0, m, &ok);
+                        const uint32_t q = leaf_q((uint32_t)Xb1[cb + a], Xd1[cb + a], m, &ok);
                         if (ok) {
                             ee[i] = ((a - j0) & 63u) << 22 | (q << 2) | (w < 0 ? 2u : 0u) | 1u;
                             bn[i] = ((a - j0) >> 6) * NWV + min(q >> RSL, NWV - 1);
@@ -910,17 +939,18 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             constexpr uint32_t HU = 2;
             PC_PH(4);
             __syncthreads(); // every wave has crossed the columns before j
-            build_pre();
+            build_preq();
             const uint32_t lc = c_lc[j], n = lc & ~PC_CAND, ls = c_ls[j];
-            const uint64_t X = pc_uniform64(Xb1[cb + j]);
-            const double Xd = wide ? Xd1[cb + j] : 0.0;
+            const uint32_t X = pc_uniform((uint32_t)Xb1[cb + j]);
+            const double Xd = __longlong_as_double(
+                (long long)pc_uniform64((uint64_t)__double_as_longlong(Xd1[cb + j])));
             int32_t wsum = 0;
             int64_t lsum = 0;
-            auto one = [&](uint64_t m, int32_t w) {
+            auto one = [&](uint32_t m, int32_t w) {
                 bool ok;
                 const uint32_t q = leaf_q(X, Xd, m, &ok);
                 if (ok) {
-                    lsum += (int64_t)w * (int64_t)count_pre(q);
+                    lsum += (int64_t)w * (int64_t)count_preq(q);
                     wsum += w;
                     nleaf++;
                 }
