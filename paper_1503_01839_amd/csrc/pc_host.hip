@@ -228,7 +228,7 @@ uint32_t seed_rec_cols(uint64_t m, uint32_t c, uint32_t nb)
 struct QueryBufs {
     DevBuf Ub, Xb, Xd, Xbh, e_start, e_count, e_off, e_scount, e_bk, e_boff, e_tmp, e_total, e_clu,
         part, part3, sums, fin, qdev;
-    DevBuf work, hot, bounds, tiles_a, trace;
+    DevBuf work, tiles_a, trace;
     DevBuf tiles, cnt, wgt, carry_rows, carry_a, carry_b, status, ticket, part_tile_h,
         part_tile_p, part_scan_h, part_scan_p, err;
     DevBuf row_off, blkoff, cntP, wP, carryP, seed_term;
@@ -537,7 +537,7 @@ void drop_tables(bool release)
 void drop_query_bufs()
 {
     QueryBufs &B = g_Q;
-    DevBuf *all[] = {&B.Ub, &B.work, &B.hot, &B.bounds, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_start, &B.e_count, &B.e_off, &B.e_scount, &B.e_bk, &B.e_boff, &B.e_tmp, &B.e_total, &B.e_clu, &B.part, &B.part3,
+    DevBuf *all[] = {&B.Ub, &B.work, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_start, &B.e_count, &B.e_off, &B.e_scount, &B.e_bk, &B.e_boff, &B.e_tmp, &B.e_total, &B.e_clu, &B.part, &B.part3,
                      &B.sums, &B.fin, &B.tiles, &B.cnt, &B.wgt, &B.carry_rows,
                      &B.carry_a, &B.carry_b, &B.status, &B.ticket, &B.part_tile_h,
                      &B.part_tile_p, &B.part_scan_h, &B.part_scan_p, &B.err, &B.qdev,
@@ -609,6 +609,8 @@ uint64_t choose_y(pc_u128 x, double alpha)
     return y;
 }
 
+constexpr uint64_t kAutoTile = ~0ull; // tile work by the launch's work (pc_plan.hip)
+
 struct Knobs {
     uint32_t seg_log2 = 18;
     uint32_t wg = 512;
@@ -616,7 +618,7 @@ struct Knobs {
     bool batch = true;
     bool seeded = false;             // windows seeded on their own (Section 4), run last to first
     uint64_t carry_budget = 6ull << 30;
-    uint64_t tile_leaves = 1u << 22; // hard-leaf items per tile; 0 = no column splitting
+    uint64_t tile_leaves = kAutoTile; // hard-leaf items per tile; 0 = no column splitting
     uint32_t hot_log2 = 15;          // small one-wavefront segments below hot_span * y
     uint32_t hot_wg = 64;
     uint64_t hot_span = 0;           // 0 = no small segments (the measured best at every size)
@@ -731,74 +733,33 @@ double ms_since(clk::time_point t0)
     return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
 }
 
-// Tiles of the window [s0, s0 + rows): segments below plan_end whose estimated
-// hard-leaf work exceeds the target are cut into column ranges of about equal
-// work (these go first, heaviest first); every other segment is one tile.
-void plan_tiles(const pc_tables &T, const pc_query &Q, const Knobs &K, uint32_t log2s,
-                uint64_t lo_base, uint64_t seg_base, uint64_t s0, uint64_t rows, uint64_t plan_end,
-                std::vector<pc_tile> &tiles)
+// Segments of a query whose tiles the device planner weighs and may cut: the
+// leaf-dense low end, below 64 y or z / 32, and every segment of a small query
+// (of span integers each, starting at base).
+uint64_t planned_rows(uint64_t y, uint64_t z, uint64_t base, uint64_t span, uint64_t rows)
 {
-    QueryBufs &B = g_Q;
-    tiles.clear();
-    std::vector<uint8_t> split(rows, 0);
-    if (K.tile_leaves && plan_end > s0) {
-        const uint64_t np = plan_end - s0;
-        ensure(B.work, np * 8, "tile plan");
-        hipck(pc_launch_seg_work(T, Q, log2s, lo_base, seg_base, s0, (uint32_t)np,
-                                 ptr<uint64_t>(B.work), g_stream),
-              "tile plan");
-        std::vector<uint64_t> work(np);
-        d2h_sync(work.data(), B.work.p, np * 8, g_stream, "D2H");
-        // The target: K.tile_leaves, or less when the whole window holds little
-        // leaf work, so that no tile outlasts the rest of the launch (about
-        // 768 workgroups run at once; a tile should carry at most twice its
-        // share of the estimated work).
-        uint64_t total = 0;
-        for (uint64_t i = 0; i < np; i++)
-            total += work[i];
-        const uint64_t target =
-            std::clamp<uint64_t>(total / 384, std::min<uint64_t>(1u << 16, K.tile_leaves),
-                                 K.tile_leaves);
-        std::vector<uint4> hot;
-        uint32_t off = 0;
-        for (uint64_t i = 0; i < np; i++)
-            if (work[i] > target) {
-                uint64_t k = (work[i] + target - 1) / target;
-                k = std::min<uint64_t>(k, std::min<uint64_t>(4096, Q.nb));
-                if (k < 2)
-                    continue;
-                hot.push_back(uint4{(uint32_t)(s0 + i), (uint32_t)k, off, 0});
-                off += (uint32_t)k + 1;
-            }
-        if (!hot.empty()) {
-            std::sort(hot.begin(), hot.end(), [&](const uint4 &a, const uint4 &b) {
-                return work[a.x - s0] > work[b.x - s0];
-            });
-            off = 0;
-            for (uint4 &h : hot) {
-                h.z = off;
-                off += h.y + 1;
-            }
-            ensure(B.hot, hot.size() * sizeof(uint4), "tile plan");
-            ensure(B.bounds, (size_t)off * 4, "tile plan");
-            h2d(B.hot.p, hot.data(), hot.size() * sizeof(uint4), g_stream, "H2D");
-            hipck(pc_launch_seg_split(T, Q, log2s, lo_base, seg_base, ptr<uint4>(B.hot),
-                                      (uint32_t)hot.size(), ptr<uint32_t>(B.bounds), g_stream),
-                  "tile split");
-            std::vector<uint32_t> bd(off);
-            d2h_sync(bd.data(), B.bounds.p, (size_t)off * 4, g_stream, "D2H");
-            for (const uint4 &h : hot) {
-                const uint32_t *b = bd.data() + h.z;
-                for (uint32_t j = 0; j < h.y; j++)
-                    if (b[j] < b[j + 1])
-                        tiles.push_back(pc_tile{h.x, b[j], b[j + 1], 0});
-                split[h.x - s0] = 1;
-            }
-        }
-    }
-    for (uint64_t r = 0; r < rows; r++)
-        if (!split[r])
-            tiles.push_back(pc_tile{(uint32_t)(s0 + r), 0, Q.ncol, 0});
+    const uint64_t hot_end = std::max<uint64_t>(64 * y, z / 32);
+    const uint64_t n = hot_end <= base ? 0 : (hot_end - base) / span + 1;
+    return std::min(rows, std::max<uint64_t>(n, rows <= 4096 ? rows : 0));
+}
+
+// How many tiles cutting may add to a launch (pc_plan_args::extra): at least
+// twice the launch's work over the least work of a tile, 8192, by a rough
+// count of it (300 items per unit of y, 440 per stored cell), so that the
+// launch carries few empty tiles.
+uint32_t plan_extra(uint64_t ysum, uint64_t cells, uint64_t tile_work)
+{
+    if (tile_work == ~0ull)
+        return 1;
+    if (tile_work)
+        return 1u << 17;
+    return (uint32_t)std::clamp<uint64_t>((300 * ysum + 440 * cells) / 4096, 64, 4096);
+}
+
+// the caller's tile_leaves as pc_plan_args::tile_work
+uint64_t plan_tile_work(const Knobs &K)
+{
+    return K.tile_leaves == 0 ? ~0ull : K.tile_leaves == kAutoTile ? 0 : K.tile_leaves;
 }
 
 // Full decomposition for one (x, y); x >= 8, icbrt(x) <= y <= isqrt(x),
@@ -984,7 +945,10 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     {
         uint64_t cells = 0, rows = 0;
         for (uint64_t r = 0; r < nseg; r++) {
-            if (rows && (cells + rowlen[r]) * per_cell + (rows + 1) * per_row > K.carry_budget) {
+            // (the budget's unit is a row of 2 integers per bit: a query is cut
+            // into the same windows whatever a segment's bits stand for)
+            if (rows && ((cells + rowlen[r]) * per_cell + (rows + 1) * per_row) / 8 * 15 >
+                            K.carry_budget) {
                 win_start.push_back(r);
                 cells = rows = 0;
             }
@@ -1029,7 +993,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     ensure(B.ticket, 8, "ticket");
     ensure(B.part_scan_h, max_tickets * 16 + 16, "scan partials");
     ensure(B.part_scan_p, 16, "scan partials");
-    ensure(B.err, 8, "error flag");
+    ensure(B.err, 16, "error flag"); // the flag, tiles in all, tiles of the planned rows
     hipck(pc_launch_fill_u64(ptr<uint64_t>(B.carry_a), Q.ncol, 0, g_stream), "fill");
     // the query as the sieve reads it: one entry of a device array
     Q.row_off = ptr<uint64_t>(B.row_off);
@@ -1047,14 +1011,14 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     FILE *trace_file = nullptr;
     if (const char *tp = std::getenv("PICOUNT_TILE_TRACE"))
         trace_file = std::fopen(tp, "a");
-    std::vector<pc_tile> tiles_a, tiles_b;
-    uint64_t ntiles_total = 0;
+    std::vector<pc_tile> tiles_a;
+    uint64_t ntiles_a = 0, ntiles_total = 0;
     uint64_t *cin = ptr<uint64_t>(B.carry_a), *cout = ptr<uint64_t>(B.carry_b);
     const int bflag = K.batch ? 0 : 0x100;
     if (c < 3) { // y < 5: the bitmap needs 2, 3 and 5 in the wheel; z < 32 here
         ev_sieve.push_back(
             timed([&] { hipck(pc_launch_sieve_tiny(T, Q, g_stream), "sieve"); }));
-        ntiles_total = 1;
+        ntiles_a = 1;
     }
     for (uint64_t wi = 0; wi < (c < 3 ? 0 : nwin); wi++) {
         // seeded windows need nothing from each other: they run last to first
@@ -1085,29 +1049,44 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         tiles_a.clear();
         for (uint64_t r = r0; r < std::min(r1, nA); r++)
             tiles_a.push_back(pc_tile{(uint32_t)r, 0, Q.ncol, 0});
-        tiles_b.clear();
+        size_t tiles_b = 0;
         if (r1 > nA) {
-            const uint64_t b0 = std::max(r0, nA);
-            const uint64_t hot_end = std::max<uint64_t>(64 * y, z / 32);
-            const uint64_t plan_end =
-                hot_end <= baseB ? b0 : std::min(r1, nA + (hot_end - baseB) / spanB + 1);
-            plan_tiles(T, Q, K, K.seg_log2, baseB, nA, b0, r1 - b0, std::max(b0, plan_end),
-                       tiles_b);
+            const uint64_t b0 = std::max(r0, nA), lo0 = baseB + (b0 - nA) * spanB;
+            pc_plan_args P{};
+            P.T = T;
+            P.Qs = ptr<pc_query>(B.qdev);
+            P.seg_first = b0;
+            P.lo_base = baseB;
+            P.seg_base = nA;
+            P.tile_work = plan_tile_work(K);
+            P.nq = 1;
+            P.np = (uint32_t)planned_rows(y, z, lo0, spanB, r1 - b0);
+            P.nrest = (uint32_t)(r1 - b0 - P.np);
+            P.extra = plan_extra(y, max_cells, P.tile_work);
+            P.ntiles = P.np + P.nrest + P.extra;
+            P.seg_log2 = K.seg_log2;
+            tiles_b = P.ntiles;
+            ensure(B.work, (size_t)P.np * 16, "tile plan");
+            ensure(B.tiles, tiles_b * sizeof(pc_tile), "tiles");
+            P.work = ptr<uint64_t>(B.work);
+            P.cut = reinterpret_cast<uint2 *>(P.work + P.np);
+            P.tile_count = ptr<uint32_t>(B.err) + 1;
+            P.nplanned = ptr<uint32_t>(B.err) + 2;
+            P.tiles = ptr<pc_tile>(B.tiles);
+            hipck(pc_launch_plan(P, g_stream), "tile plan");
         }
-        ntiles_total += tiles_a.size() + tiles_b.size();
+        ntiles_a += tiles_a.size();
         ensure(B.tiles_a, tiles_a.size() * sizeof(pc_tile), "tiles");
-        ensure(B.tiles, tiles_b.size() * sizeof(pc_tile), "tiles");
-        const size_t npart = std::max(tiles_a.size(), tiles_b.size());
+        const size_t npart = std::max(tiles_a.size(), tiles_b);
         ensure(B.part_tile_h, npart * 16, "tile partials");
         ensure(B.part_tile_p, npart * 16, "tile partials");
         h2d(B.tiles_a.p, tiles_a.data(), tiles_a.size() * sizeof(pc_tile), g_stream, "tiles");
-        h2d(B.tiles.p, tiles_b.data(), tiles_b.size() * sizeof(pc_tile), g_stream, "tiles");
         auto sieve_args = [&](bool small) {
             pc_sieve_args A{};
             A.T = T;
             A.Qs = ptr<pc_query>(B.qdev);
             A.tiles = ptr<pc_tile>(small ? B.tiles_a : B.tiles);
-            A.ntiles = (uint32_t)(small ? tiles_a.size() : tiles_b.size());
+            A.ntiles = (uint32_t)(small ? tiles_a.size() : tiles_b);
             A.seg0 = r0;
             A.lo_base = small ? 0 : baseB;
             A.seg_base = small ? 0 : nA;
@@ -1139,8 +1118,13 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
                                      hipMemcpyDeviceToHost, g_stream),
                       "D2H");
                 hipck(hipStreamSynchronize(g_stream), "sync");
-                const std::vector<pc_tile> &tl = small ? tiles_a : tiles_b;
+                std::vector<pc_tile> tl(A.ntiles);
+                hipck(hipMemcpy(tl.data(), A.tiles, tl.size() * sizeof(pc_tile),
+                                hipMemcpyDeviceToHost),
+                      "D2H");
                 for (uint32_t i = 0; i < A.ntiles; i++) {
+                    if (tl[i].col_lo >= tl[i].col_hi)
+                        continue;
                     std::fprintf(trace_file, "%u %u %u %u %d", (unsigned)w, tl[i].seg,
                                  tl[i].col_lo, tl[i].col_hi, small ? 1 : 0);
                     for (uint32_t k = 0; k < PC_TRACE_W; k++)
@@ -1210,14 +1194,16 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     hipck(pc_launch_combine(sums, Q, kx, ptr<pc_final>(B.fin), g_stream), "combine");
     pc_final fin{};
     pc_sums hs{};
-    int32_t err = 0;
+    int32_t err2[2] = {0, 0}; // the error flag, the tiles
     uint64_t e_items = 0;
     hipck(hipMemcpyAsync(&e_items, B.e_total.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipMemcpyAsync(&hs, B.sums.p, sizeof hs, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipMemcpyAsync(&fin, B.fin.p, sizeof fin, hipMemcpyDeviceToHost, g_stream), "D2H");
-    hipck(hipMemcpyAsync(&err, B.err.p, 4, hipMemcpyDeviceToHost, g_stream), "D2H");
+    hipck(hipMemcpyAsync(err2, B.err.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipStreamSynchronize(g_stream), "sync");
     const double ms_sieve = ms_since(t2);
+    const int32_t err = err2[0];
+    ntiles_total = ntiles_a + (uint32_t)err2[1];
     if (err & 1)
         fail(PC_EINTERNAL, "look-back scan did not complete");
     if (err & 8)
@@ -1388,10 +1374,13 @@ struct RoundPlan {
     std::vector<uint64_t> roff;   // every query's row offsets (nseg + 1 each), uploaded
     std::vector<size_t> o_roff;   // where each query's offsets start in roff
     std::vector<uint64_t> cells;  // stored cells of each query's staircase
-    std::vector<pc_tile> tiles;
     std::vector<uint32_t> blk;
     size_t t_xb = 0, t_s1 = 0, t_ez = 0, t_sc = 0;
     uint32_t nb_xb = 0, nb_s1 = 0, nb_ez = 0, nb_sc = 0;
+    // the sieve's tiles, built on the device (pc_plan_args): the query order
+    // and its two prefix arrays in blk, the plan's arrays and the tiles in the arena
+    size_t t_ord = 0, t_plan = 0, t_rest = 0, o_work = 0, o_cut = 0, o_tiles = 0;
+    uint32_t np = 0, nrest = 0, extra = 0, ntiles = 0;
 };
 
 // Everything one batch round keeps while it is on the device: its stream
@@ -1399,7 +1388,7 @@ struct RoundPlan {
 // its copies read from.
 struct BatchSlot {
     hipStream_t st = nullptr;
-    DevBuf arena, qs, tiles, blk, roff, err;
+    DevBuf arena, qs, blk, roff, err;
     pc_final *h_fin = nullptr; // pinned
     size_t h_fin_cap = 0;
     int32_t *h_err = nullptr;  // pinned
@@ -1441,7 +1430,7 @@ void slot_release(BatchSlot &sl)
 {
     if (sl.st)
         (void)hipStreamSynchronize(sl.st);
-    for (DevBuf *b : {&sl.arena, &sl.qs, &sl.tiles, &sl.blk, &sl.roff, &sl.err})
+    for (DevBuf *b : {&sl.arena, &sl.qs, &sl.blk, &sl.roff, &sl.err})
         if (b->p) {
             (void)hipFree(b->p);
             g_dev_bytes -= b->cap;
@@ -1459,8 +1448,8 @@ void slot_release(BatchSlot &sl)
     sl = BatchSlot{};
 }
 
-// The round's arena layout, block tables and tiles.
-void plan_round(const std::vector<BatchQuery> &R, RoundPlan &P)
+// The round's arena layout, block tables and tile counts.
+void plan_round(const std::vector<BatchQuery> &R, const Knobs &K, RoundPlan &P)
 {
     const uint32_t nq = (uint32_t)R.size();
     P.arena = 0;
@@ -1519,16 +1508,36 @@ void plan_round(const std::vector<BatchQuery> &R, RoundPlan &P)
         &P.nb_ez);
     P.t_sc = table([](const BatchQuery &b) { return (b.ncol + 255) / 256; }, &P.nb_sc);
 
-    // sieve tiles, largest queries first, each query's low (leaf-dense) segments first
+    // the sieve's tiles: largest queries first, each query's low (leaf-dense) segments first
     std::vector<uint32_t> order(nq);
     for (uint32_t i = 0; i < nq; i++)
         order[i] = i;
     std::stable_sort(order.begin(), order.end(),
                      [&](uint32_t u, uint32_t v) { return R[u].bytes() > R[v].bytes(); });
-    P.tiles.clear();
-    for (uint32_t i : order)
-        for (uint64_t sg = 0; sg < R[i].nseg; sg++)
-            P.tiles.push_back(pc_tile{(uint32_t)sg, 0, R[i].ncol, i});
+    P.np = P.nrest = 0;
+    uint64_t ysum = 0, cells = 0;
+    std::vector<uint32_t> pp{0}, pr{0};
+    for (uint32_t i : order) {
+        const BatchQuery &b = R[i];
+        const uint64_t n = planned_rows(b.y, b.z, 0, pc_seg_span(kBatchLog2S), b.nseg);
+        P.np += (uint32_t)n;
+        P.nrest += (uint32_t)(b.nseg - n);
+        pp.push_back(P.np);
+        pr.push_back(P.nrest);
+        ysum += b.y;
+        cells += P.cells[i];
+    }
+    P.t_ord = P.blk.size();
+    P.blk.insert(P.blk.end(), order.begin(), order.end());
+    P.t_plan = P.blk.size();
+    P.blk.insert(P.blk.end(), pp.begin(), pp.end());
+    P.t_rest = P.blk.size();
+    P.blk.insert(P.blk.end(), pr.begin(), pr.end());
+    P.extra = plan_extra(ysum, cells, plan_tile_work(K));
+    P.ntiles = P.np + P.nrest + P.extra;
+    P.o_work = take((size_t)P.np * 8);
+    P.o_cut = take((size_t)P.np * 8);
+    P.o_tiles = take((size_t)P.ntiles * sizeof(pc_tile));
 }
 
 // The round's per-query scalars, with their arrays carved out of the arena at
@@ -1596,15 +1605,15 @@ void round_queries(const std::vector<BatchQuery> &R, const RoundPlan &P, char *b
 }
 
 // The round's kernels on st: clears, set-up, easy leaves, sieve, carries and
-// combination into the pc_final array of the arena.  qs, tiles and bk hold
-// the uploaded Qv, P.tiles and P.blk.
+// combination into the pc_final array of the arena.  qs and bk hold the
+// uploaded Qv and P.blk; err: the error flag and two words for the tile plan.
 void round_launches(const RoundPlan &P, uint32_t nq, char *base, const pc_tables &T,
-                    const pc_query *qs, const pc_tile *tiles, const uint32_t *bk, int32_t *err,
+                    const pc_query *qs, const uint32_t *bk, int32_t *err,
                     const Knobs &K, hipStream_t st)
 {
     pc_sums *sums = reinterpret_cast<pc_sums *>(base + P.o_sums);
     pc_final *fin = reinterpret_cast<pc_final *>(base + P.o_fin);
-    hipck(pc_launch_fill_u64(reinterpret_cast<uint64_t *>(err), 1, 0, st), "fill");
+    hipck(pc_launch_fill_u64(reinterpret_cast<uint64_t *>(err), 2, 0, st), "fill");
     hipck(pc_launch_fill_u64(reinterpret_cast<uint64_t *>(sums), nq * sizeof(pc_sums) / 8, 0, st),
           "fill");
     // results cleared (ok = 0): a read-back that overtook the combination
@@ -1617,11 +1626,30 @@ void round_launches(const RoundPlan &P, uint32_t nq, char *base, const pc_tables
           "batch set-up");
     hipck(pc_launch_batch_easy(T, qs, bk + P.t_ez, bk + P.t_ez + P.nb_ez, P.nb_ez, st),
           "batch easy");
+    pc_plan_args L{};
+    L.T = T;
+    L.Qs = qs;
+    L.order = bk + P.t_ord;
+    L.pfx_plan = bk + P.t_plan;
+    L.pfx_rest = bk + P.t_rest;
+    L.tile_work = plan_tile_work(K);
+    L.work = reinterpret_cast<uint64_t *>(base + P.o_work);
+    L.cut = reinterpret_cast<uint2 *>(base + P.o_cut);
+    L.tile_count = reinterpret_cast<uint32_t *>(err) + 1;
+    L.nplanned = reinterpret_cast<uint32_t *>(err) + 2;
+    L.tiles = reinterpret_cast<pc_tile *>(base + P.o_tiles);
+    L.nq = nq;
+    L.np = P.np;
+    L.nrest = P.nrest;
+    L.extra = P.extra;
+    L.ntiles = P.ntiles;
+    L.seg_log2 = kBatchLog2S;
+    hipck(pc_launch_plan(L, st), "tile plan");
     pc_sieve_args A{};
     A.T = T;
     A.Qs = qs;
-    A.tiles = tiles;
-    A.ntiles = (uint32_t)P.tiles.size();
+    A.tiles = L.tiles;
+    A.ntiles = P.ntiles;
     A.err = err;
     hipck(pc_launch_sieve(A, kBatchLog2S, kBatchWG, PC_MODE_TALLY | (K.batch ? 0 : 0x100), st),
           "batch sieve");
@@ -1639,16 +1667,15 @@ void submit_round(BatchSlot &sl, const Knobs &K, bool use_graph)
     hipStream_t st = sl.st ? sl.st : g_stream;
     const pc_tables T = tables_view(kWheelC);
     RoundPlan &P = sl.plan;
-    plan_round(R, P);
+    plan_round(R, K, P);
     slot_ensure(sl, sl.arena, P.arena, "batch arena");
     slot_ensure(sl, sl.roff, P.roff.size() * 8, "batch row offsets");
     char *base = static_cast<char *>(sl.arena.p);
     round_queries(R, P, base, ptr<uint64_t>(sl.roff), T, sl.Qv);
 
     slot_ensure(sl, sl.qs, nq * sizeof(pc_query), "batch queries");
-    slot_ensure(sl, sl.tiles, P.tiles.size() * sizeof(pc_tile), "batch tiles");
     slot_ensure(sl, sl.blk, P.blk.size() * 4, "batch blocks");
-    slot_ensure(sl, sl.err, 8, "error flag");
+    slot_ensure(sl, sl.err, 16, "error flag");
     if (sl.h_fin_cap < nq) {
         if (sl.h_fin)
             (void)hipHostFree(sl.h_fin);
@@ -1663,16 +1690,13 @@ void submit_round(BatchSlot &sl, const Knobs &K, bool use_graph)
         hipck(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming), "hipEventCreate");
     hipck(hipMemcpyAsync(sl.qs.p, sl.Qv.data(), nq * sizeof(pc_query), hipMemcpyHostToDevice, st),
           "H2D");
-    hipck(hipMemcpyAsync(sl.tiles.p, P.tiles.data(), P.tiles.size() * sizeof(pc_tile),
-                         hipMemcpyHostToDevice, st),
-          "H2D");
     hipck(hipMemcpyAsync(sl.blk.p, P.blk.data(), P.blk.size() * 4, hipMemcpyHostToDevice, st),
           "H2D");
     hipck(hipMemcpyAsync(sl.roff.p, P.roff.data(), P.roff.size() * 8, hipMemcpyHostToDevice, st),
           "H2D");
     auto launches = [&]() {
-        round_launches(P, nq, base, T, ptr<pc_query>(sl.qs), ptr<pc_tile>(sl.tiles),
-                       ptr<uint32_t>(sl.blk), ptr<int32_t>(sl.err), K, st);
+        round_launches(P, nq, base, T, ptr<pc_query>(sl.qs), ptr<uint32_t>(sl.blk),
+                       ptr<int32_t>(sl.err), K, st);
     };
     if (use_graph) {
         hipck(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
@@ -1849,7 +1873,7 @@ void run_batch(const uint64_t *xs, size_t n, const Knobs &K, double alpha, bool 
 struct AsyncRound {
     std::vector<BatchQuery> R;
     RoundPlan P;
-    size_t o_qs = 0, o_tiles = 0, o_blk = 0, o_pos = 0, o_roff = 0;
+    size_t o_qs = 0, o_blk = 0, o_pos = 0, o_roff = 0;
 };
 
 struct AsyncPlan {
@@ -1907,16 +1931,15 @@ void async_layout(const uint64_t *xs, size_t n, const std::vector<BatchQuery> &b
         return o;
     };
     for (AsyncRound &r : A.rounds) {
-        plan_round(r.R, r.P);
+        plan_round(r.R, K, r.P);
         r.o_qs = take(r.R.size() * sizeof(pc_query));
-        r.o_tiles = take(r.P.tiles.size() * sizeof(pc_tile));
         r.o_blk = take(r.P.blk.size() * 4);
         r.o_pos = take(r.R.size() * 8);
         r.o_roff = take(r.P.roff.size() * 8);
         arena = std::max(arena, r.P.arena);
     }
     A.o_kv = take(A.nkv * 16);
-    A.o_err = take(8);
+    A.o_err = take(16);
     A.o_arena = take(arena);
     A.total = A.rounds.empty() ? A.o_err : tot; // no round: no flag, no arena
 }
@@ -2001,7 +2024,6 @@ void async_queue(const AsyncPlan &A, const std::vector<ulonglong2> &kv, char *im
         round_queries(r.R, r.P, arena, reinterpret_cast<const uint64_t *>(ws + r.o_roff), T, Qv);
         memcpy(img + r.o_roff, r.P.roff.data(), r.P.roff.size() * 8);
         memcpy(img + r.o_qs, Qv.data(), Qv.size() * sizeof(pc_query));
-        memcpy(img + r.o_tiles, r.P.tiles.data(), r.P.tiles.size() * sizeof(pc_tile));
         memcpy(img + r.o_blk, r.P.blk.data(), r.P.blk.size() * 4);
         uint64_t *pos = reinterpret_cast<uint64_t *>(img + r.o_pos);
         for (size_t i = 0; i < r.R.size(); i++)
@@ -2018,7 +2040,6 @@ void async_queue(const AsyncPlan &A, const std::vector<ulonglong2> &kv, char *im
     for (const AsyncRound &r : A.rounds) {
         const uint32_t nq = (uint32_t)r.R.size();
         round_launches(r.P, nq, arena, T, reinterpret_cast<const pc_query *>(ws + r.o_qs),
-                       reinterpret_cast<const pc_tile *>(ws + r.o_tiles),
                        reinterpret_cast<const uint32_t *>(ws + r.o_blk), err, K, st);
         hipck(pc_launch_batch_out(reinterpret_cast<const pc_final *>(arena + r.P.o_fin),
                                   reinterpret_cast<const uint64_t *>(ws + r.o_pos), nq, err, d_out,

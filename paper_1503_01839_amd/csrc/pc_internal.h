@@ -192,13 +192,29 @@ hipError_t pc_launch_easy_band(const pc_tables &T, const pc_query &Q, pc_s128 *p
 hipError_t pc_launch_sum128(const pc_s128 *part, uint32_t n, pc_s128 *acc, hipStream_t s);
 hipError_t pc_launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
-// Tile planning: hard-leaf items per segment, and column cuts for hot segments.
-hipError_t pc_launch_seg_work(const pc_tables &T, const pc_query &Q, uint32_t seg_log2,
-                              uint64_t lo_base, uint64_t seg_base, uint64_t seg0, uint32_t nseg,
-                              uint64_t *work, hipStream_t s);
-hipError_t pc_launch_seg_split(const pc_tables &T, const pc_query &Q, uint32_t seg_log2,
-                               uint64_t lo_base, uint64_t seg_base, const uint4 *hot,
-                               uint32_t nhot, uint32_t *bounds, hipStream_t s);
+// The tile list of a sieve launch (pc_plan.hip), written to tiles[ntiles]:
+// the planned rows of every query (its first ones, the leaf-dense low end),
+// each whole or cut into column ranges, the rest rows whole, and empty tiles.
+// One query (nq = 1): segments from seg_first on, np planned and nrest more;
+// several: query order[k] has the planned rows pfx_plan[k] .. pfx_plan[k+1] - 1
+// and the rest rows pfx_rest[k] .. pfx_rest[k+1] - 1, its segments from 0 on.
+struct pc_plan_args {
+    pc_tables T;
+    const pc_query *Qs;
+    const uint32_t *order, *pfx_plan, *pfx_rest;
+    uint64_t seg_first, lo_base, seg_base; // as pc_sieve_args
+    uint64_t tile_work; // work of a tile; 0: by the launch's work, ~0: no cuts
+    uint64_t *work;     // np: estimated work
+    uint2 *cut;         // np: tiles, the first one's index
+    uint32_t *nplanned; // tiles of the planned rows
+    uint32_t *tile_count; // += the tiles that are not empty
+    pc_tile *tiles;
+    uint32_t nq, np, nrest;
+    uint32_t extra;     // the cuts add at most this many tiles
+    uint32_t ntiles;    // >= np + nrest + extra
+    uint32_t seg_log2;
+};
+hipError_t pc_launch_plan(const pc_plan_args &A, hipStream_t s);
 
 // Sieve and carry scan.
 hipError_t pc_launch_sieve(const pc_sieve_args &A, uint32_t seg_log2, uint32_t wg, int mode,
