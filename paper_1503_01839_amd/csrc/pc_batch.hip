@@ -6,7 +6,6 @@
 #include "pc_leafwork.h"
 
 #define BT 256
-#define BEZ_PER 32
 
 // block -> (query, block of the query, blocks of the query)
 struct pc_blk {
@@ -21,15 +20,6 @@ __device__ __forceinline__ void pc_blk_of(const pc_blk &B, uint32_t *q, uint32_t
     const uint32_t f = B.first[*q];
     *lb = blockIdx.x - f;
     *nlb = B.first[*q + 1] - f;
-}
-
-__global__ __launch_bounds__(BT) void k_xb_b(pc_tables T, const pc_query *Qs, pc_blk B)
-{
-    uint32_t q, lb, nlb;
-    pc_blk_of(B, &q, &lb, &nlb);
-    const pc_query &Q = Qs[q];
-    for (uint32_t b = lb * BT + threadIdx.x; b <= Q.a; b += nlb * BT)
-        pc_xb_item(T, Q, b);
 }
 
 __global__ __launch_bounds__(BT) void k_s1_b(pc_tables T, const pc_query *Qs, pc_blk B)
@@ -54,61 +44,26 @@ __global__ __launch_bounds__(BT) void k_s1_b(pc_tables T, const pc_query *Qs, pc
 
 __global__ __launch_bounds__(BT) void k_leaf_setup_b(pc_tables T, const pc_query *Qs, pc_blk B)
 {
-    __shared__ uint64_t scr[BT / 64];
+    __shared__ pc_s128 scr[BT / 64];
     uint32_t q, lb, nlb;
     pc_blk_of(B, &q, &lb, &nlb);
     const pc_query &Q = Qs[q];
-    uint64_t triv = 0, cross = 0;
-    for (uint32_t b = lb * BT + threadIdx.x; b <= max(Q.a, Q.c + Q.nb); b += nlb * BT) {
-        uint64_t t, c;
-        pc_leaf_setup_item(T, Q, b, &t, &c);
-        triv += t;
-        cross += c;
-    }
-    const uint64_t s = pc_block_sum<BT>(triv, scr);
-    const uint64_t cs = pc_block_sum<BT>(cross, scr);
-    if (threadIdx.x == 0) {
-        pc_atomic_add128(&Q.sums->s2t, (pc_s128)s);
-        atomicAdd(&Q.sums->n_trivial, (unsigned long long)s);
-        atomicAdd(&Q.sums->crossings, (unsigned long long)cs);
-    }
+    pc_setup_sums S;
+    const uint32_t n = max(Q.a, Q.c + Q.nb) + 1;
+    for (uint32_t b0 = lb * BT; b0 < n; b0 += nlb * BT)
+        pc_leaf_setup_band(T, Q, b0 + threadIdx.x, &S);
+    pc_setup_flush<BT>(Q, S, scr);
 }
 
-// Exclusive prefix of the counts cnt[0..n) (mode bit stripped) into off
-// (which may be cnt itself), the total into *total; the calling workgroup does
-// one query in chunks of BT.
-__device__ __forceinline__ void pc_escan(const pc_query &Q, const uint64_t *cnt, uint64_t *off,
-                                         uint32_t n, uint64_t *total, uint64_t *scr)
+// The bands' unit offsets and the suffix maxima of the hard-leaf u ranges
+// (pc_ub_suffix), one workgroup per query.
+__global__ __launch_bounds__(BT) void k_band_scan_b(const pc_query *Qs)
 {
-    uint64_t run = 0;
-    for (uint32_t i0 = 0; i0 < n; i0 += BT) {
-        const uint32_t i = i0 + threadIdx.x;
-        const uint64_t v = i < n ? cnt[i] & ~PC_MODEBIT : 0;
-        uint64_t tot;
-        const uint64_t ex = pc_block_excl_scan<BT>(v, scr, &tot);
-        if (i < n)
-            off[i] = run + ex;
-        run += tot;
-    }
-    if (threadIdx.x == 0)
-        *total = run;
-}
-
-// The easy leaves' offsets (candidates: e_off, e_total[0]) and bands
-// (singles and groups: e_bk, e_boff, e_total[1], e_total[2]), one workgroup
-// per query; then the suffix maxima of the hard-leaf u ranges (pc_ub_suffix).
-__global__ __launch_bounds__(BT) void k_escan_b(pc_tables T, const pc_query *Qs)
-{
-    __shared__ uint64_t scr[BT / 64];
     __shared__ uint64_t sh[BT];
     const pc_query &Q = Qs[blockIdx.x];
-    pc_escan(Q, Q.e_count, Q.e_off, Q.a + 1, Q.e_total, scr);
     const uint32_t nband = Q.a / PC_EZ_BAND + 1;
-    for (uint32_t g = threadIdx.x; g < nband; g += BT)
-        pc_easy_band_item(T, Q, g);
-    __syncthreads();
-    pc_escan(Q, Q.e_boff, Q.e_boff, nband, Q.e_total + 1, scr);
-    pc_escan(Q, Q.e_boff + nband, Q.e_boff + nband, nband, Q.e_total + 2, scr);
+    pc_band_scan<BT>(Q.e_boff, nband, Q.e_total, sh);
+    pc_band_scan<BT>(Q.e_boff + nband, nband, Q.e_total + 1, sh);
     pc_ub_suffix<BT>(Q, sh);
 }
 
@@ -116,15 +71,14 @@ __global__ __launch_bounds__(BT) void k_easy_b(pc_tables T, const pc_query *Qs, 
 {
     __shared__ pc_s128 scr[BT / 64];
     __shared__ unsigned long long scr64[BT / 64];
-    __shared__ uint32_t s_b0, s_g[2];
+    __shared__ pc_cand_lds<BT> L;
     uint32_t q, lb, nlb;
     pc_blk_of(B, &q, &lb, &nlb);
     const pc_query &Q = Qs[q];
     unsigned long long nleaf = 0;
     int64_t acc = 0;
-    pc_easy_tiles<BT, BEZ_PER>(T, Q, lb, nlb, &s_b0, &acc, &nleaf);
-    pc_easy_bands<BT, false>(T, Q, lb, nlb, &s_g[0], &acc);
-    pc_easy_bands<BT, true>(T, Q, lb, nlb, &s_g[1], &acc);
+    pc_easy_cands<BT>(T, Q, lb, nlb, L, &acc, &nleaf);
+    pc_easy_primes<BT>(T, Q, lb, nlb, &acc);
     const pc_s128 s = pc_block_sum128<BT>((pc_s128)acc, scr);
     nleaf = pc_block_sum<BT>(nleaf, scr64);
     if (threadIdx.x == 0) {
@@ -204,10 +158,9 @@ hipError_t pc_launch_batch_setup(const pc_tables &T, const pc_query *Qs, const u
                                  const uint32_t *bf_s1, uint32_t nb_s1, uint32_t nq,
                                  hipStream_t s)
 {
-    k_xb_b<<<nb_xb, BT, 0, s>>>(T, Qs, pc_blk{bq_xb, bf_xb});
     k_s1_b<<<nb_s1, BT, 0, s>>>(T, Qs, pc_blk{bq_s1, bf_s1});
     k_leaf_setup_b<<<nb_xb, BT, 0, s>>>(T, Qs, pc_blk{bq_xb, bf_xb});
-    k_escan_b<<<nq, BT, 0, s>>>(T, Qs);
+    k_band_scan_b<<<nq, BT, 0, s>>>(Qs);
     return hipGetLastError();
 }
 

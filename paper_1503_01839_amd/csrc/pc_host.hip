@@ -226,8 +226,7 @@ uint32_t seed_rec_cols(uint64_t m, uint32_t c, uint32_t nb)
 }
 
 struct QueryBufs {
-    DevBuf Ub, Xb, Xd, Xbh, e_start, e_count, e_off, e_scount, e_bk, e_boff, e_tmp, e_total, e_clu,
-        part, part3, sums, fin, qdev;
+    DevBuf Ub, Xb, Xd, Xbh, e_rng, e_bk, e_boff, e_lim, e_total, sums, fin, qdev;
     DevBuf work, tiles_a, trace;
     DevBuf tiles, cnt, wgt, carry_rows, carry_a, carry_b, status, ticket, part_tile_h,
         part_tile_p, part_scan_h, part_scan_p, err;
@@ -537,7 +536,7 @@ void drop_tables(bool release)
 void drop_query_bufs()
 {
     QueryBufs &B = g_Q;
-    DevBuf *all[] = {&B.Ub, &B.work, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_start, &B.e_count, &B.e_off, &B.e_scount, &B.e_bk, &B.e_boff, &B.e_tmp, &B.e_total, &B.e_clu, &B.part, &B.part3,
+    DevBuf *all[] = {&B.Ub, &B.work, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_rng, &B.e_bk, &B.e_boff, &B.e_lim, &B.e_total,
                      &B.sums, &B.fin, &B.tiles, &B.cnt, &B.wgt, &B.carry_rows,
                      &B.carry_a, &B.carry_b, &B.status, &B.ticket, &B.part_tile_h,
                      &B.part_tile_p, &B.part_scan_h, &B.part_scan_p, &B.err, &B.qdev,
@@ -843,8 +842,6 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         ensure(B.Xbh, (a + 2) * 4, "X_b");
         Q.Xbh = ptr<uint32_t>(B.Xbh);
     }
-    hipck(pc_launch_xb(T, Q, g_stream), "X_b");
-
     ensure(B.sums, sizeof(pc_sums), "sums");
     ensure(B.fin, sizeof(pc_final), "final");
     ensure(B.e_total, 32, "easy total");
@@ -852,49 +849,22 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     pc_sums *sums = ptr<pc_sums>(B.sums);
     Q.sums = sums;
 
-    const uint32_t s1_blocks = (uint32_t)std::min<uint64_t>(2048, y / 256 + 1);
-    const uint32_t ls_blocks = (uint32_t)(a / 256 + 1);
-    const uint32_t ez_blocks = 4096;
-    ensure(B.part, (size_t)std::max<uint32_t>({s1_blocks, ls_blocks, ez_blocks}) * 16, "partials");
-    ensure(B.part3, (size_t)ez_blocks * 16, "partials");
-    auto t1 = clk::now();
-    const size_t ev_s1 = timed(
-        [&] { hipck(pc_launch_s1(T, Q, ptr<pc_s128>(B.part), s1_blocks, g_stream), "S1"); });
-    hipck(pc_launch_sum128(ptr<pc_s128>(B.part), s1_blocks, &sums->s1, g_stream), "S1 sum");
-
-    ensure(B.e_start, (a + 2) * 8, "easy ranges");
-    ensure(B.e_count, (a + 2) * 8, "easy ranges");
-    ensure(B.e_off, (a + 2) * 8, "easy offsets");
-    ensure(B.e_scount, (a + 2) * 8, "easy ranges");
     const uint64_t nband = a / PC_EZ_BAND + 1;
+    ensure(B.e_rng, (a + 2) * 8, "easy ranges");
     ensure(B.e_bk, 2 * nband * 4, "easy bands");
     ensure(B.e_boff, 2 * nband * 8, "easy bands");
-
-    ensure(B.e_clu, (a + 2) * 16, "easy clusters");
-    ensure(B.e_tmp, ((a + 2) / 4096 + 2) * 8, "scan");
+    ensure(B.e_lim, nband * 8, "easy bands");
     ensure(B.Ub, (a + 2) * 16, "hard-leaf u ranges");
     Q.Ub = Q.Ub_w = ptr<ulonglong2>(B.Ub);
-    Q.e_start = ptr<uint64_t>(B.e_start);
-    Q.e_count = ptr<uint64_t>(B.e_count);
-    Q.e_off = ptr<uint64_t>(B.e_off);
-    Q.e_scount = ptr<uint64_t>(B.e_scount);
+    Q.e_rng = ptr<uint2>(B.e_rng);
     Q.e_bk = ptr<uint32_t>(B.e_bk);
     Q.e_boff = ptr<uint64_t>(B.e_boff);
+    Q.e_lim = ptr<uint2>(B.e_lim);
     Q.e_total = ptr<uint64_t>(B.e_total);
-    Q.e_clu = ptr<uint4>(B.e_clu);
-    hipck(pc_launch_leaf_setup(T, Q, ptr<pc_s128>(B.part), ls_blocks, g_stream), "leaf setup");
-    hipck(pc_launch_sum128(ptr<pc_s128>(B.part), ls_blocks, &sums->s2t, g_stream), "S2t sum");
-    hipck(pc_launch_strip(ptr<uint64_t>(B.e_count), ptr<uint64_t>(B.e_off), a + 1, g_stream),
-          "strip");
-    hipck(pc_launch_scan_u64(ptr<uint64_t>(B.e_off), a + 1, ptr<uint64_t>(B.e_tmp),
-                             ptr<uint64_t>(B.e_total), g_stream),
-          "easy scan");
-    hipck(pc_launch_easy_bands(T, Q, g_stream), "easy bands");
-    for (int kind = 0; kind < 2; kind++)
-        hipck(pc_launch_scan_u64(ptr<uint64_t>(B.e_boff) + kind * nband, nband,
-                                 ptr<uint64_t>(B.e_tmp), ptr<uint64_t>(B.e_total) + 1 + kind,
-                                 g_stream),
-              "easy scan");
+    const size_t ev_s1 = timed([&] {
+        hipck(pc_launch_s1(T, Q, (uint32_t)std::min<uint64_t>(2048, y / 256 + 1), g_stream), "S1");
+    });
+    hipck(pc_launch_leaf_setup(T, Q, g_stream), "leaf setup");
     // The easy leaves touch nothing the sieve writes: they run on the second
     // stream once the last sieve window is queued, and rejoin before the
     // combination.  Both kernels keep every CU busy, so running them side by
@@ -908,25 +878,20 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         forked = true;
         hipck(hipEventRecord(g_fork, g_stream), "hipEventRecord");
         hipck(hipStreamWaitEvent(g_stream2, g_fork, 0), "hipStreamWaitEvent");
-        // the bands (integer issue) and the candidates (table reads) side by
-        // side on two streams, each with its own partials
+        // the primes and the candidates side by side on two streams; as many
+        // workgroups as 4096, fewer for a small y
+        const uint32_t nblk = (uint32_t)std::clamp<uint64_t>(y / 256, 256, 4096);
         ev_easy = timed(
             [&] {
                 hipck(hipStreamWaitEvent(g_stream3, g_fork, 0), "hipStreamWaitEvent");
-                hipck(pc_launch_easy(T, Q, ptr<pc_s128>(B.part3), ez_blocks, g_stream3), "easy");
+                hipck(pc_launch_easy_cands(T, Q, nblk, g_stream3), "easy");
                 hipck(hipEventRecord(g_join3, g_stream3), "hipEventRecord");
-                hipck(pc_launch_easy_band(T, Q, ptr<pc_s128>(B.part), ez_blocks, g_stream2),
-                      "easy");
+                hipck(pc_launch_easy_primes(T, Q, nblk, g_stream2), "easy");
                 hipck(hipStreamWaitEvent(g_stream2, g_join3, 0), "hipStreamWaitEvent");
             },
             g_stream2);
-        hipck(pc_launch_sum128(ptr<pc_s128>(B.part), ez_blocks, &sums->s2e, g_stream2),
-              "S2e sum");
-        hipck(pc_launch_sum128(ptr<pc_s128>(B.part3), ez_blocks, &sums->s2e, g_stream2),
-              "S2e sum");
         hipck(hipEventRecord(g_join, g_stream2), "hipEventRecord");
     };
-    (void)t1;
 
     // --- the sieve of [1, z] in windows of segments ---
     auto t2 = clk::now();
@@ -1195,8 +1160,6 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     pc_final fin{};
     pc_sums hs{};
     int32_t err2[2] = {0, 0}; // the error flag, the tiles
-    uint64_t e_items = 0;
-    hipck(hipMemcpyAsync(&e_items, B.e_total.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipMemcpyAsync(&hs, B.sums.p, sizeof hs, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipMemcpyAsync(&fin, B.fin.p, sizeof fin, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipMemcpyAsync(err2, B.err.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
@@ -1239,7 +1202,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         res->n_s1 = hs.n_s1;
         res->n_easy = hs.n_easy;
         res->n_hard = hs.n_hard;
-        res->n_easy_items = e_items + hs.n_easy_terms;
+        res->n_easy_items = hs.n_easy_terms;
         res->crossings = hs.crossings;
         res->segments = nseg;
         res->tiles = ntiles_total;
@@ -1353,7 +1316,7 @@ constexpr uint32_t kBatchWG = 512;
 
 size_t r256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// A query's chunk of a round arena: X_b, Ub, four easy arrays, e_clu, Xd, bands,
+// A query's chunk of a round arena: X_b, Ub, e_rng, Xd, bands,
 // counts and weights (cells of the count staircase), the P2 column's counts
 // and weights, each rounded up to 256 bytes exactly as round_queries takes
 // them.
@@ -1361,8 +1324,8 @@ size_t query_chunk(const BatchQuery &b, uint64_t cells)
 {
     const size_t na = b.a + 2;
     const size_t nband = b.a / PC_EZ_BAND + 1;
-    return 6 * r256(na * 8) + 2 * r256(na * 16) + r256(2 * nband * 4) + r256(2 * nband * 8) +
-           2 * r256(cells * 4) + 2 * r256(b.nseg * 4);
+    return 3 * r256(na * 8) + r256(na * 16) + r256(2 * nband * 4) + r256(2 * nband * 8) +
+           r256(nband * 8) + 2 * r256(cells * 4) + 2 * r256(b.nseg * 4);
 }
 
 // What the host builds for one round: the arena layout (sums, easy totals,
@@ -1580,16 +1543,13 @@ void round_queries(const std::vector<BatchQuery> &R, const RoundPlan &P, char *b
         Q.kx = (uint32_t)b.kx;
         Q.Xb = Q.Xb_w = reinterpret_cast<uint64_t *>(carve(na * 8));
         Q.Ub = Q.Ub_w = reinterpret_cast<ulonglong2 *>(carve(na * 16));
-        Q.e_start = reinterpret_cast<uint64_t *>(carve(na * 8));
-        Q.e_count = reinterpret_cast<uint64_t *>(carve(na * 8));
-        Q.e_off = reinterpret_cast<uint64_t *>(carve(na * 8));
-        Q.e_scount = reinterpret_cast<uint64_t *>(carve(na * 8));
-        Q.e_clu = reinterpret_cast<uint4 *>(carve(na * 16));
+        Q.e_rng = reinterpret_cast<uint2 *>(carve(na * 8));
         Q.Xd = reinterpret_cast<double *>(carve(na * 8));
         Q.Xbh = nullptr; // batch queries lie below 2^64
         const size_t nband = b.a / PC_EZ_BAND + 1;
         Q.e_bk = reinterpret_cast<uint32_t *>(carve(2 * nband * 4));
         Q.e_boff = reinterpret_cast<uint64_t *>(carve(2 * nband * 8));
+        Q.e_lim = reinterpret_cast<uint2 *>(carve(nband * 8));
         Q.row_off = roff + P.o_roff[i];
         Q.cnt = reinterpret_cast<uint32_t *>(carve(P.cells[i] * 4));
         Q.wgt = reinterpret_cast<int32_t *>(carve(P.cells[i] * 4));

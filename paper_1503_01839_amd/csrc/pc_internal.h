@@ -69,27 +69,23 @@ struct pc_query {
     uint32_t *cntP;         // per row: the count after the last crossing (P2 column)
     int32_t *wP;            // per row: the P2 terms landing in the row
     const uint64_t *carryP; // PC_MODE_LEAVES: exclusive carries of cntP
-    // Easy leaves per b (pc_leaf_setup_item), in three kinds:
-    //   candidates (p_b^2 <= y): the integers m prime to p_1..p_c, by their
-    //     wheel numbers k = e_start[b] .. + e_count[b] - 1 (pc_wheel_m; bit 63
-    //     of e_count set), e_off the exclusive prefix of e_count over b and
-    //     e_total[0] its total;
-    //   singles (p_b^2 > y): primes p_k, k = e_start[b] .. + e_scount[b] - 1;
-    //   groups (p_b^2 > y): e_clu[b] = {nk, klo, z, w}, K = klo .. klo + nk
-    //     (none when nk = 0).
-    // Singles and groups are dealt out in bands of PC_EZ_BAND consecutive b:
-    // unit j of band g is the 256 prime indices from e_bk[g] + 256 j on, each
-    // taken against every b of the band.  e_bk[g] / e_boff[g] (g < nband):
-    // first k and exclusive prefix of the units of the singles; at nband + g
-    // the same for the groups; e_total[1] / e_total[2] the units.  Xd[b] =
-    // X_b rounded to double.
-    uint64_t *e_start;
-    uint64_t *e_count;
-    uint64_t *e_off;
-    uint64_t *e_scount;
-    uint4 *e_clu;
+    // Easy leaves per b (pc_leaf_setup_band), taken in bands of PC_EZ_BAND
+    // consecutive b, band g = the b from PC_EZ_BAND g on:
+    //   primes (p_b^2 > y): e_rng[b] = {lo, hi}, the prime indices k of
+    //     lo <= k < hi whose pi(X_b / p_k) counts twice (pc_easy_primes);
+    //   candidates (p_b^2 <= y): e_rng[b] = {PC_CAND | m1, m2}, the leaves'
+    //     m1 <= m <= m2 (pc_easy_cands);
+    //   {0, 0}: none.
+    // Unit j of a band is PC_EZ_UNIT prime indices from e_bk[g] + PC_EZ_UNIT j
+    // on, or PC_EZ_TILE wheel numbers (pc_wheel_m) from e_bk[nband + g] +
+    // PC_EZ_TILE j on, against every b of the band; e_boff[g] / e_boff[nband +
+    // g]: exclusive prefix of the units, e_total[0] / e_total[1] their sums.
+    // e_lim[g] = {the largest lo, the smallest hi} of the band's b (empty
+    // unless every b of it has primes).  Xd[b] = X_b rounded to double.
+    uint2 *e_rng;
     uint32_t *e_bk;
     uint64_t *e_boff;
+    uint2 *e_lim;
     double *Xd;
     uint64_t *e_total;
     ulonglong2 *Ub_w;       // writable view of Ub (set-up kernels)
@@ -133,10 +129,11 @@ __device__ __forceinline__ uint64_t pc_xv_small_q(pc_xv X, uint32_t m)
 
 enum { PC_MODE_TALLY = 0, PC_MODE_COUNT = 1, PC_MODE_LEAVES = 2 };
 
-// b per band of the singles and groups of the easy leaves; bands of a query:
-// a / PC_EZ_BAND + 1.
+// b per band of the easy leaves (one per lane of a wavefront; bands of a query:
+// a / PC_EZ_BAND + 1), prime indices and wheel numbers per unit.
 #define PC_EZ_BAND 64
 #define PC_EZ_UNIT 256
+#define PC_EZ_TILE 2048
 
 // per-tile trace record: 0 ticks (100 MHz), 1 hard leaves, 2 candidates read,
 // 3 leafy columns, 4 of them with p^3 < segment end, 5.. phase ticks
@@ -173,22 +170,16 @@ hipError_t pc_launch_wheel(uint32_t c, const uint32_t *primes, uint32_t *pattern
                            hipStream_t s);
 hipError_t pc_launch_lookup(const uint2 *pitab, const uint64_t *in, uint32_t n, uint64_t *out,
                             hipStream_t s);
-hipError_t pc_launch_xb(const pc_tables &T, const pc_query &Q, hipStream_t s);
 
-// Leaves outside the sieve: S1, trivial and easy special leaves.  The set-up
-// and easy kernels use the per-query arrays named in pc_query.
-hipError_t pc_launch_s1(const pc_tables &T, const pc_query &Q, pc_s128 *part, uint32_t nblocks,
-                        hipStream_t s);
-hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, pc_s128 *part_trivial,
-                                uint32_t nblocks, hipStream_t s);
-hipError_t pc_launch_strip(const uint64_t *e_count, uint64_t *e_off, uint64_t n, hipStream_t s);
-hipError_t pc_launch_scan_u64(uint64_t *data, uint64_t n, uint64_t *tmp, uint64_t *total,
-                              hipStream_t s);
-hipError_t pc_launch_easy(const pc_tables &T, const pc_query &Q, pc_s128 *part, uint32_t nblocks,
-                          hipStream_t s);
-hipError_t pc_launch_easy_bands(const pc_tables &T, const pc_query &Q, hipStream_t s);
-hipError_t pc_launch_easy_band(const pc_tables &T, const pc_query &Q, pc_s128 *part,
-                               uint32_t nblocks, hipStream_t s);
+// Leaves outside the sieve: S1, trivial and easy special leaves, into the
+// query's sums.  The set-up (X_b, Ub, the trivial leaves, the easy leaves'
+// ranges and bands) and the easy kernels use the arrays named in pc_query.
+hipError_t pc_launch_s1(const pc_tables &T, const pc_query &Q, uint32_t nblocks, hipStream_t s);
+hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, hipStream_t s);
+hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
+                                hipStream_t s);
+hipError_t pc_launch_easy_primes(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
+                                 hipStream_t s);
 hipError_t pc_launch_sum128(const pc_s128 *part, uint32_t n, pc_s128 *acc, hipStream_t s);
 hipError_t pc_launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
@@ -265,7 +256,7 @@ hipError_t pc_launch_seed(const pc_tables &T, uint32_t c, uint64_t m, uint32_t n
 struct pc_sums {
     pc_s128 s1, s2t, s2e, hard_local, hard_dot, p2_local, p2_dot;
     unsigned long long n_s1, n_easy, n_hard, crossings, n_trivial;
-    unsigned long long n_easy_terms; // singles and group terms of the easy leaves
+    unsigned long long n_easy_terms; // candidates, single primes and group values of the easy leaves
 };
 struct pc_final {
     pc_s128 s1, s2t, s2e, s2h, p2, phi;

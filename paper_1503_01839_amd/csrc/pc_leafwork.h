@@ -14,14 +14,10 @@
 #include "pc_internal.h"
 #include "pc_leafrange.h"
 
-#define PC_MODEBIT (1ull << 63)
-
-// X_b = floor(x / p_b) for 1 <= b <= a (X_0 = x): its low word, its high
+// X_b = floor(x / p_b) for 0 <= b <= a (X_0 = x): its low word, its high
 // word (above 2^64, when Xbh is not null) and its value in fp64.
-__device__ __forceinline__ void pc_xb_item(const pc_tables &T, const pc_query &Q, uint32_t b)
+__device__ __forceinline__ pc_xv pc_xb_item(const pc_tables &T, const pc_query &Q, uint32_t b)
 {
-    if (b > Q.a)
-        return;
     uint64_t lo, hi = 0;
     if (b == 0) {
         lo = Q.x;
@@ -31,10 +27,15 @@ __device__ __forceinline__ void pc_xb_item(const pc_tables &T, const pc_query &Q
     } else {
         lo = pc_div_u128_32(Q.x_hi, Q.x, T.primes[b], &hi, nullptr);
     }
+    pc_xv X;
+    X.lo = lo;
+    X.hi = (uint32_t)hi;
+    X.d = hi ? (double)(((pc_u128)hi << 64) | lo) : (double)lo;
     Q.Xb_w[b] = lo;
     if (Q.Xbh)
         Q.Xbh[b] = (uint32_t)hi;
-    Q.Xd[b] = hi ? (double)(((pc_u128)hi << 64) | lo) : (double)lo;
+    Q.Xd[b] = X.d;
+    return X;
 }
 
 // The S1 term of n (pcc = p_c): adds mu(n) phi(x/n, c) to *acc when n <= y is
@@ -62,29 +63,82 @@ __device__ __forceinline__ bool pc_s1_item(const pc_tables &T, const pc_query &Q
     return true;
 }
 
+// pi(floor(X / p)), X in fp64 and its low word, rp = 1 / p, quotient < 2^31.
+__device__ __forceinline__ uint32_t pc_pi_quot_exact(const pc_tables &T, uint64_t X, double Xd,
+                                                     uint32_t p, double rp)
+{
+    return pc_pi_lookup32(T.pitab, pc_quot31r(X, Xd, p, rp));
+}
+
+// The same less one, without a remainder: one fma forms the quotient less one
+// in fixed point with 20 fractional bits in the low bits of a double (2^-20 is
+// its last place, as 1.5 2^32 < the sum < 2^33), raised by 4 units.  X rp is
+// off by less than 3 units (quotient < 2^31, X and rp off by 2^-53, 1 / p from
+// pc_rcp_f64 by 2^-51), so the integer part is right unless the fraction came
+// out below 8 units: *amb collects the least fraction, and the caller repeats
+// the exact way where some lane's is below PC_AMB (one step in a few thousand).
+// The table's entry and the bits counted in it come from shifts of the same
+// double.  About 10 instructions, none of them a 32-bit multiply, where the
+// remainder test takes 19.  on: lanes that hold a term (the others read the
+// first entry).
+#define PC_AMB 8u
+__device__ __forceinline__ uint32_t pc_pi_quot_less1(const uint2 *pitab, double Xd, double rp,
+                                                     bool on, uint32_t *amb)
+{
+    constexpr double kMagic = 6442450944.0 - 1.0 + 4.0 / 1048576.0;
+    const uint64_t v = (uint64_t)__double_as_longlong(__builtin_fma(Xd, rp, kMagic));
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    const uint32_t off = __builtin_amdgcn_alignbit(hi, lo, 23) & (on ? 0x0FFFFFF8u : 0u);
+    const uint2 e = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(pitab) + off);
+    const uint32_t i = __builtin_amdgcn_alignbit(hi, lo, 21); // (quotient - 1) / 2, modulo 32
+    *amb = min(*amb, on ? lo & 0xFFFFFu : PC_AMB);
+    return e.y + (uint32_t)__builtin_popcount(e.x << (~i & 31u));
+}
+
 // Per-b set-up of the special leaves outside the sieve, c < b < a:
 //   trivial leaves: primes m with max(p_b, x/p_b^2) < m <= y  (counted);
-//   easy range:     max(y/p_b, H_b, p_b) < m <= min(y, x/p_b^2),
-//                   H_b = max(x/p_b^3, x/(p_b (y+1)));
-// for p_b^2 > y every m in the range is prime, so the range is stored as
-// prime indices; otherwise as candidate m (bit 63 of the count).  A prime
-// range is cut at s = isqrt(x/p_b): each prime m <= s is a "single"
-// (e_start, e_scount); above s, where u = x/(m p_b) < m and consecutive m
-// share pi(u), the primes m are taken by the value K = pi(u) instead: those
-// with x/(p_b p_{K+1}) < m <= x/(p_b p_K), all with phi(u, b-1) = K - b + 2
-// (e_clu; pc_easy_group_term).  For a sieving prime it also records the u
-// range of its hard leaves (Ub) and the odd multiples below the sieve end
-// (*cross).
-__device__ __forceinline__ void pc_leaf_setup_item(const pc_tables &T, const pc_query &Q,
-                                                   uint32_t b, uint64_t *triv, uint64_t *cross)
+//   easy range:     e1 = max(y/p_b, H_b, p_b) + 1 <= m <= e2 = min(y, x/p_b^2),
+//                   H_b = max(x/p_b^3, x/(p_b (y+1))).
+// For a sieving prime it also records the u range of its hard leaves (Ub) and
+// the odd multiples below the sieve end.
+//
+// p_b^2 <= y: the m of the range are tested one by one (pc_easy_cands).
+// p_b^2 > y: they are prime.  With s = isqrt(X_b), X = X_b:
+//   singles, primes m <= s: phi(u, b-1) = pi(u) - b + 2, u = X / m, so their
+//     part is the sum of pi(X / p_k) over k1 <= k < k1 + ns less ns (b - 2);
+//   groups, primes m > s, taken by K = pi(X / m), klo <= K < klo + nk: with
+//     C(v) = min(max(v, s), e2) and V_K = pi(C(X / p_K)), the primes with
+//     pi(u) = K number V_K - V_{K+1} (also when there are none), so their part
+//     sum_K (V_K - V_{K+1}) (K - b + 2) telescopes to
+//       sum_{klo <= K <= klo + nk} V_K + V_klo (klo - b + 1)
+//         - V_{klo + nk} (klo + nk + 2 - b).
+//     V_klo = pi(e2) and V_{klo + nk} = pi(s); the K between need no C.
+// So both parts sum pi(X / p_k), the singles over [k1, k1 + ns), the groups
+// over [klo + 1, klo + nk), and these ranges hardly differ: both end near
+// pi(s), and e1 - 1 = max(p_b, X / (y + 1)) and X / e2 = max(p_b, X / y) differ
+// by at most one, so each end differs by a prime or two.  The common range is
+// taken once and counted twice (pc_easy_primes); the ends are added here.
+//
+// The calling workgroup (NT threads; every thread calls) takes the b of block
+// index b0 / NT; its wavefronts are bands.  Added up over the calls: the
+// trivial leaves, the crossings, and the constant parts of S2e.
+struct pc_setup_sums {
+    uint64_t triv = 0, cross = 0, terms = 0;
+    int64_t leaves = 0;
+    pc_s128 cst = 0;
+};
+
+__device__ __forceinline__ void pc_leaf_setup_band(const pc_tables &T, const pc_query &Q,
+                                                   uint32_t b, pc_setup_sums *S)
 {
-    *triv = 0;
-    *cross = 0;
-    if (b > Q.c && b <= Q.c + Q.nb) { // a sieving prime
+    const bool known = b <= Q.a || b <= Q.c + Q.nb;
+    pc_xv X{};
+    if (b <= Q.a)
+        X = pc_xb_item(T, Q, b);
+    if (known && b > Q.c && b <= Q.c + Q.nb) { // a sieving prime (nb <= a - c: y >= isqrt z)
         const uint64_t p = T.primes[b], rp = T.recip[b];
-        const pc_xv X = pc_xb(Q, b);
         // odd multiples k p_b, k odd, below the sieve end
-        *cross = (pc_div(Q.sieve_end - 1, p, rp) + 1) / 2;
+        S->cross += (pc_div(Q.sieve_end - 1, p, rp) + 1) / 2;
         // u range of the hard leaves of b: y/p < m <= y, m > p, m <= max(x/p^3, x/(p(y+1)))
         uint64_t m1 = pc_div(Q.y, p, rp) + 1;
         if (m1 < p + 1)
@@ -103,55 +157,124 @@ __device__ __forceinline__ void pc_leaf_setup_item(const pc_tables &T, const pc_
         }
         Q.Ub_w[b] = ub;
     }
-    if (b <= Q.a) {
-        uint64_t st = 0, cn = 0, sn = 0;
-        uint4 clu = make_uint4(0, 0, 0, 0);
-        if (b > Q.c && b < Q.a) {
-            const uint64_t p = T.primes[b], rp = T.recip[b];
-            const pc_xv X = pc_xb(Q, b);
-            const uint64_t tp = pc_xv_div(X, (uint32_t)p, rp); // floor(x / p^2): u >= p <=> m <= tp
-            uint64_t m1 = pc_div(Q.y, p, rp) + 1;
-            if (m1 < p + 1)
-                m1 = p + 1;
-            const uint64_t h1 = pc_div(tp, p, rp);
-            const uint64_t h2 = pc_xv_div64(X, Q.y1, Q.recip_y1);
-            const uint64_t H = h1 > h2 ? h1 : h2;
-            uint64_t e1 = H + 1 > m1 ? H + 1 : m1;
-            uint64_t e2 = tp < Q.y ? tp : Q.y;
-            if (p > Q.sqrty) {
-                if (e1 <= e2) {
-                    const uint64_t sx = X.hi ? pc_isqrt_wide(X.hi, X.lo) : pc_isqrt(X.lo);
-                    uint64_t s = sx; // single-m items: m <= s
-                    if (s < e1 - 1)
-                        s = e1 - 1;
-                    if (s > e2)
-                        s = e2;
-                    const uint64_t k1 = pc_pi_lookup(T.pitab, e1 - 1) + 1;
-                    const uint64_t ns = pc_pi_lookup(T.pitab, s) + 1 - k1;
-                    uint64_t klo = 0, nk = 0;
-                    if (s < e2) { // K = pi(u) for u in [X / e2, X / (s + 1)]
-                        klo = pc_pi_lookup(T.pitab, pc_xv_small_q(X, (uint32_t)e2));
-                        nk = pc_pi_lookup(T.pitab, pc_xv_small_q(X, (uint32_t)(s + 1))) + 1 - klo;
-                    }
-                    st = k1;
-                    sn = ns;
-                    clu = make_uint4((uint32_t)nk, (uint32_t)klo, (uint32_t)s, (uint32_t)e2);
+    uint32_t lo = 0, hi = 0;                 // e_rng of a prime b
+    uint32_t w0 = UINT32_MAX, w1 = 0;        // wheel numbers of a candidate b
+    uint2 rng = make_uint2(0, 0);
+    const bool in = b > Q.c && b < Q.a;
+    if (in) {
+        const uint64_t p = T.primes[b], rp = T.recip[b];
+        const uint64_t tp = pc_xv_div(X, (uint32_t)p, rp); // floor(x / p^2): u >= p <=> m <= tp
+        uint64_t m1 = pc_div(Q.y, p, rp) + 1;
+        if (m1 < p + 1)
+            m1 = p + 1;
+        const uint64_t h1 = pc_div(tp, p, rp);
+        const uint64_t h2 = pc_xv_div64(X, Q.y1, Q.recip_y1);
+        const uint64_t H = h1 > h2 ? h1 : h2;
+        const uint64_t e1 = H + 1 > m1 ? H + 1 : m1;
+        const uint64_t e2 = tp < Q.y ? tp : Q.y;
+        if (p > Q.sqrty) {
+            if (e1 <= e2) {
+                uint64_t s = X.hi ? pc_isqrt_wide(X.hi, X.lo) : pc_isqrt(X.lo);
+                if (s < e1 - 1)
+                    s = e1 - 1;
+                if (s > e2)
+                    s = e2;
+                const uint32_t k1 = pc_pi_lookup(T.pitab, e1 - 1) + 1;
+                const uint32_t ps = pc_pi_lookup(T.pitab, s);
+                const uint32_t s1 = ps + 1; // singles [k1, s1)
+                uint32_t g0 = 0, g1 = 0;    // groups between the ends [g0, g1)
+                S->cst -= (pc_s128)(s1 - k1) * ((int64_t)b - 2);
+                S->leaves += s1 - k1;
+                S->terms += s1 - k1;
+                if (s < e2) { // K = pi(u) for u in [X / e2, X / (s + 1)]
+                    const uint32_t klo =
+                        pc_pi_lookup(T.pitab, pc_xv_small_q(X, (uint32_t)e2));
+                    const uint32_t kend =
+                        pc_pi_lookup(T.pitab, pc_xv_small_q(X, (uint32_t)(s + 1))) + 1;
+                    const int64_t v0 = pc_pi_lookup(T.pitab, e2), v1 = ps;
+                    S->cst += v0 + v1 + (pc_s128)v0 * ((int64_t)klo - b + 1) -
+                              (pc_s128)v1 * ((int64_t)kend + 2 - b);
+                    S->leaves += v0 - v1;
+                    S->terms += kend - klo + 1;
+                    g0 = klo + 1;
+                    g1 = kend;
                 }
-                // trivial: m prime, m > max(m1 - 1, tp), m <= y
-                uint64_t t0 = tp > m1 - 1 ? tp : m1 - 1;
-                if (t0 < Q.y)
-                    *triv = Q.a - pc_pi_lookup(T.pitab, t0);
-            } else if (e1 <= e2) {
-                // every m with lpf(m) > p_b > p_c is prime to p_1..p_c: only
-                // those are items, by their wheel numbers (pc_wheel_m)
-                st = pc_wheel_count(T, Q, e1 - 1);
-                cn = (pc_wheel_count(T, Q, e2) - st) | PC_MODEBIT;
+                lo = max(k1, g0);
+                hi = min(s1, g1);
+                if (lo >= hi)
+                    lo = hi = s1; // nothing in common
+                auto add = [&](uint32_t ka, uint32_t kb) {
+                    for (uint32_t k = ka; k < kb; k++)
+                        S->cst += pc_pi_quot_exact(T, X.lo, X.d, T.primes[k], T.rcpd[k]);
+                };
+                add(k1, min(lo, s1)); // the singles and the groups outside [lo, hi)
+                add(max(hi, k1), s1);
+                add(g0, min(lo, g1));
+                add(max(hi, g0), g1);
+                if (lo < hi)
+                    rng = make_uint2(lo, hi);
+                else
+                    lo = hi = 0;
             }
+            // trivial: m prime, m > max(m1 - 1, tp), m <= y
+            const uint64_t t0 = tp > m1 - 1 ? tp : m1 - 1;
+            if (t0 < Q.y)
+                S->triv += Q.a - pc_pi_lookup(T.pitab, t0);
+        } else if (e1 <= e2) {
+            // every m with lpf(m) > p_b > p_c is prime to p_1..p_c: only
+            // those are items, by their wheel numbers (pc_wheel_m)
+            w0 = (uint32_t)pc_wheel_count(T, Q, e1 - 1);
+            w1 = (uint32_t)pc_wheel_count(T, Q, e2);
+            S->terms += w1 - w0;
+            if (w0 < w1)
+                rng = make_uint2((uint32_t)e1 | PC_CAND, (uint32_t)e2);
+            else
+                w0 = UINT32_MAX;
         }
-        Q.e_start[b] = st;
-        Q.e_count[b] = cn;
-        Q.e_scount[b] = sn;
-        Q.e_clu[b] = clu;
+    }
+    if (b <= Q.a)
+        Q.e_rng[b] = rng;
+    // the band: this wavefront's b
+    const bool some = lo < hi;
+    uint32_t p_lo = some ? lo : UINT32_MAX, p_hi = some ? hi : 0;
+    uint32_t l_lo = !in ? 0 : some ? lo : UINT32_MAX, l_hi = !in ? UINT32_MAX : some ? hi : 0;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        p_lo = min(p_lo, (uint32_t)__shfl_xor((int)p_lo, d, 64));
+        p_hi = max(p_hi, (uint32_t)__shfl_xor((int)p_hi, d, 64));
+        l_lo = max(l_lo, (uint32_t)__shfl_xor((int)l_lo, d, 64));
+        l_hi = min(l_hi, (uint32_t)__shfl_xor((int)l_hi, d, 64));
+        w0 = min(w0, (uint32_t)__shfl_xor((int)w0, d, 64));
+        w1 = max(w1, (uint32_t)__shfl_xor((int)w1, d, 64));
+    }
+    const uint32_t nband = Q.a / PC_EZ_BAND + 1, g = b / PC_EZ_BAND;
+    if (pc_lane() == 0 && g < nband) {
+        Q.e_bk[g] = p_lo;
+        Q.e_boff[g] = p_hi > p_lo ? (p_hi - p_lo + PC_EZ_UNIT - 1) / PC_EZ_UNIT : 0;
+        Q.e_bk[nband + g] = w0;
+        Q.e_boff[nband + g] = w1 > w0 ? (w1 - w0 + PC_EZ_TILE - 1) / PC_EZ_TILE : 0;
+        Q.e_lim[g] = make_uint2(l_lo, l_hi);
+    }
+}
+
+// S, summed over the workgroup, into the query's sums.
+template <int NT>
+__device__ __forceinline__ void pc_setup_flush(const pc_query &Q, const pc_setup_sums &S,
+                                               pc_s128 *scr)
+{
+    uint64_t *const scr64 = reinterpret_cast<uint64_t *>(scr);
+    const uint64_t tr = pc_block_sum<NT>(S.triv, scr64);
+    const uint64_t cr = pc_block_sum<NT>(S.cross, scr64);
+    const uint64_t te = pc_block_sum<NT>(S.terms, scr64);
+    const uint64_t le = pc_block_sum<NT>((uint64_t)S.leaves, scr64);
+    const pc_s128 cst = pc_block_sum128<NT>(S.cst, scr);
+    if (threadIdx.x == 0) {
+        pc_atomic_add128(&Q.sums->s2t, (pc_s128)tr);
+        pc_atomic_add128(&Q.sums->s2e, cst);
+        atomicAdd(&Q.sums->n_trivial, (unsigned long long)tr);
+        atomicAdd(&Q.sums->crossings, (unsigned long long)cr);
+        atomicAdd(&Q.sums->n_easy, (unsigned long long)le);
+        atomicAdd(&Q.sums->n_easy_terms, (unsigned long long)te);
     }
 }
 
@@ -185,207 +308,193 @@ template <int NT> __device__ __forceinline__ void pc_ub_suffix(const pc_query &Q
     }
 }
 
-// The group terms of a prime-item b (cl = its e_clu entry: nk, klo, z = s,
-// w = e2; bm2 = b - 2).  With C(v) = min(max(v, z), w) and
-// V_K = pi(C(X_b / p_K)), the primes m in (max(X_b / p_{K+1}, z),
-// min(X_b / p_K, w)] number V_K - V_{K+1} (also when that range is empty, as
-// C is monotone), so the part of S2e over K = klo .. khi = klo + nk - 1 is
-//   sum_K (V_K - V_{K+1}) (K - bm2)
-//     = sum_{klo <= K <= khi + 1} V_K
-//       + V_klo (klo - bm2 - 1) - V_{khi+1} (khi + 1 - bm2),
-// and its leaves number V_klo - V_{khi+1}.  The sum of the V_K is taken in
-// bands (pc_easy_bands), the two end terms once per b (pc_easy_band_item).
-// Every quotient is at most y < 2^31 - 1, every p_K < 2^31.
-__device__ __forceinline__ int64_t pc_easy_group_v(const pc_tables &T, uint4 cl, uint64_t X,
-                                                   double Xd, uint32_t K)
+// Exclusive prefix of the n units of a kind over the bands, in place, and
+// their sum into *total, by the calling workgroup.
+template <int NT>
+__device__ __forceinline__ void pc_band_scan(uint64_t *off, uint32_t n, uint64_t *total,
+                                             uint64_t *scr)
 {
-    return pc_pi_lookup32(T.pitab,
-                          min(max(pc_quot31r(X, Xd, T.primes[K], T.rcpd[K]), cl.z), cl.w));
+    uint64_t run = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += NT) {
+        const uint32_t i = i0 + threadIdx.x;
+        const uint64_t v = i < n ? off[i] : 0;
+        uint64_t tot;
+        const uint64_t ex = pc_block_excl_scan<NT>(v, scr, &tot);
+        if (i < n)
+            off[i] = run + ex;
+        run += tot;
+    }
+    if (threadIdx.x == 0)
+        *total = run;
 }
 
-// b in [c+1, a-1] with off[b] <= i0 < off[b+1] (off = an exclusive prefix of
-// item counts; the last such b, so b has items).
-__device__ __forceinline__ uint32_t pc_item_owner(const pc_query &Q, const uint64_t *off,
-                                                  uint64_t i0)
+// the last band g with off[g] <= u (uniform)
+__device__ __forceinline__ uint32_t pc_band_of(const uint64_t *off, uint32_t nband, uint64_t u)
 {
-    uint32_t lo_b = Q.c + 1, hi_b = Q.a - 1;
-    while (lo_b < hi_b) {
-        const uint32_t mid = (lo_b + hi_b + 1) >> 1;
-        if (off[mid] <= i0)
-            lo_b = mid;
+    uint32_t lo = 0, hi = nband - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= u)
+            lo = mid;
         else
-            hi_b = mid - 1;
+            hi = mid - 1;
     }
-    return lo_b;
+    return lo;
 }
 
-// The candidate easy leaves (p_b^2 <= y), items (wheel numbers of the m prime
-// to p_1..p_c) laid end to end over b (e_off = exclusive prefix of the counts,
-// e_total[0] their sum).  The calling
-// workgroup (NT threads; every thread calls) takes tiles lb, lb + nlb, ... of
-// NT * PER consecutive items; one search finds the b of a tile's first item,
-// then thread t takes items i0 + t, i0 + t + NT, ... so neighbouring lanes
-// read neighbouring entries.  u = x/(m p_b) <= y < 2^31 - 1, so the
-// reciprocal estimate quotient is exact after its remainder check.
-template <int NT, int PER>
-__device__ __forceinline__ void pc_easy_tiles(const pc_tables &T, const pc_query &Q, uint64_t lb,
-                                              uint64_t nlb, uint32_t *s_b0, int64_t *acc,
-                                              unsigned long long *nleaf)
-{
-    constexpr uint64_t TILE = (uint64_t)NT * PER;
-    const uint64_t E = Q.e_total[0];
-    const uint64_t *e_off = Q.e_off, *e_count = Q.e_count, *e_start = Q.e_start;
-    for (uint64_t i0 = lb * TILE; i0 < E; i0 += nlb * TILE) {
-        if (threadIdx.x == 0)
-            *s_b0 = pc_item_owner(Q, e_off, i0);
-        __syncthreads();
-        uint32_t b = *s_b0;
-        const uint32_t n = (uint32_t)(i0 + TILE < E ? TILE : E - i0); // items of the tile
-        uint64_t off = e_off[b], cn = e_count[b] & ~PC_MODEBIT, st = e_start[b], X = Q.Xb[b];
-        double Xd = Q.Xd[b];
-        uint32_t p = T.primes[b];
-        const uint64_t iend = i0 + n;
-        for (uint64_t i = i0 + threadIdx.x; i < iend; i += NT) {
-            while (i >= off + cn) {
-                b++;
-                off = e_off[b];
-                cn = e_count[b] & ~PC_MODEBIT;
-                st = e_start[b];
-                X = Q.Xb[b];
-                Xd = Q.Xd[b];
-                p = T.primes[b];
-            }
-            const uint32_t m = pc_wheel_m(T, (uint32_t)(st + (i - off)));
-            const int32_t v = T.mulpf[m];
-            const uint32_t l = v < 0 ? (uint32_t)(-v) : (uint32_t)v;
-            if (l <= p) // mu(m) = 0 or lpf(m) <= p_b
-                continue;
-            const uint32_t u = pc_quot31(X, Xd, m); // u <= y < 2^31 - 1
-            const int64_t phi = (int64_t)pc_pi_lookup32(T.pitab, u) - (int64_t)b + 2;
-            *acc += v > 0 ? -phi : phi; // -mu(m) phi(u, b-1)
-            (*nleaf)++;
-        }
-        __syncthreads();
-    }
-}
-
-// The bands of the singles and groups (layout in pc_query): for band g, the
-// first and one past the last prime index of each kind over the band's b, and
-// its units; and the parts of S2e and of the
-// leaf count that the bands' sums leave out: -(b - 2) for each single
-// (pc_easy_bands adds pi(u) alone), the two end terms of each b's groups
-// (pc_easy_group_v), and every single and group leaf.
-__device__ __forceinline__ void pc_easy_band_item(const pc_tables &T, const pc_query &Q,
-                                                  uint32_t g)
-{
-    const uint32_t nband = Q.a / PC_EZ_BAND + 1;
-    if (g >= nband)
-        return;
-    const uint32_t b0 = g * PC_EZ_BAND, b1 = min(b0 + PC_EZ_BAND, Q.a + 1);
-    uint32_t s_lo = UINT32_MAX, s_hi = 0, g_lo = UINT32_MAX, g_hi = 0;
-    pc_s128 cst = 0;
-    int64_t leaves = 0;
-    unsigned long long terms = 0;
-    for (uint32_t b = b0; b < b1; b++) {
-        const uint64_t X = Q.Xb[b];
-        const double Xd = Q.Xd[b];
-        const uint32_t ns = (uint32_t)Q.e_scount[b];
-        if (ns) {
-            const uint32_t k1 = (uint32_t)Q.e_start[b];
-            s_lo = min(s_lo, k1);
-            s_hi = max(s_hi, k1 + ns);
-            cst -= (pc_s128)ns * (b - 2);
-            leaves += ns;
-            terms += ns;
-        }
-        const uint4 cl = Q.e_clu[b];
-        if (cl.x) {
-            const uint32_t klo = cl.y, khi1 = cl.y + cl.x; // K = klo .. khi1
-            g_lo = min(g_lo, klo);
-            g_hi = max(g_hi, khi1 + 1);
-            const int64_t v0 = pc_easy_group_v(T, cl, X, Xd, klo);
-            const int64_t v1 = pc_easy_group_v(T, cl, X, Xd, khi1);
-            cst += (pc_s128)v0 * (int64_t)(klo - b + 1) - (pc_s128)v1 * (int64_t)(khi1 + 2 - b);
-            leaves += v0 - v1;
-            terms += cl.x + 1;
-        }
-    }
-    if (cst != 0)
-        pc_atomic_add128(&Q.sums->s2e, cst);
-    if (leaves)
-        atomicAdd(&Q.sums->n_easy, (unsigned long long)leaves);
-    if (terms)
-        atomicAdd(&Q.sums->n_easy_terms, terms);
-    Q.e_bk[g] = s_lo;
-    Q.e_boff[g] = s_hi > s_lo ? (s_hi - s_lo + PC_EZ_UNIT - 1) / PC_EZ_UNIT : 0;
-    Q.e_bk[nband + g] = g_lo;
-    Q.e_boff[nband + g] = g_hi > g_lo ? (g_hi - g_lo + PC_EZ_UNIT - 1) / PC_EZ_UNIT : 0;
-}
-
-// Singles (GRP false) or groups (GRP true) of the easy leaves, in units of
-// PC_EZ_UNIT prime indices k (one per thread; NT = PC_EZ_UNIT) against the
-// PC_EZ_BAND b of a band (layout in pc_query).  The calling workgroup takes the
-// contiguous units [U lb / nlb, U (lb + 1) / nlb).  A thread loads p_k and 1/p_k
-// once per unit; for each b of the band that has k in its range it adds
-//   singles: pi(u), u = X_b / p_k;
-//   groups:  V_k = pi(C(X_b / p_k)) (pc_easy_group_v);
-// the rest of each term is added once per b (pc_easy_band_item).  Every
-// thread takes every b (a lane outside the b's range looks up pi(2) and drops
-// it), so the loop has no branches; band data are uniform over the workgroup.
-template <int NT, bool GRP>
-__device__ __forceinline__ void pc_easy_bands(const pc_tables &T, const pc_query &Q, uint64_t lb,
-                                              uint64_t nlb, uint32_t *s_g, int64_t *acc)
+// The prime easy leaves (p_b^2 > y): *acc += 2 pi(X_b / p_k) over the band's b
+// and lo_b <= k < hi_b, in units of PC_EZ_UNIT prime indices, one per thread
+// (NT = PC_EZ_UNIT), against the b of a band.  The calling workgroup takes the
+// contiguous units [U lb / nlb, U (lb + 1) / nlb).  A thread loads p_k and
+// 1/p_k once per unit; X_b and the ranges are uniform (scalar loads).  Where
+// the unit lies in every b's range (99% of them at x = 10^18) no lane tests
+// its own, and four table reads are in flight.
+//
+// Integer issue bounds it, and the table reads (L2-resident, u <= y) close
+// behind: one pi(10^18) takes 4.4 ms (12.2 ms with singles and groups summed
+// apart and a remainder test per quotient).
+template <int NT>
+__device__ __forceinline__ void pc_easy_primes(const pc_tables &T, const pc_query &Q, uint64_t lb,
+                                               uint64_t nlb, int64_t *acc)
 {
     static_assert(NT == PC_EZ_UNIT, "one thread per prime index of a unit");
     const uint32_t nband = Q.a / PC_EZ_BAND + 1;
-    const uint64_t *boff = Q.e_boff + (GRP ? nband : 0);
-    const uint32_t *bk = Q.e_bk + (GRP ? nband : 0);
-    const uint64_t U = Q.e_total[GRP ? 2 : 1];
+    const uint64_t *const boff = Q.e_boff;
+    const uint64_t U = Q.e_total[0];
     const uint64_t u0 = U * lb / nlb, u1 = U * (lb + 1) / nlb;
     if (u0 >= u1)
         return;
-    if (threadIdx.x == 0) { // the band of unit u0: last g with boff[g] <= u0
-        uint32_t lo = 0, hi = nband - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (boff[mid] <= u0)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        *s_g = lo;
-    }
-    __syncthreads();
-    uint32_t g = __builtin_amdgcn_readfirstlane(*s_g);
+    uint32_t g = pc_band_of(boff, nband, u0);
     uint64_t gend = g + 1 < nband ? boff[g + 1] : U;
-    int64_t a = 0;
+    uint64_t a = 0;
     const uint32_t kcap = Q.a + 1; // p_k and 1/p_k exist for k <= a + 1
     for (uint64_t u = u0; u < u1; u++) {
         while (u >= gend) {
             g++;
             gend = g + 1 < nband ? boff[g + 1] : U;
         }
-        const uint32_t k = bk[g] + (uint32_t)(u - boff[g]) * PC_EZ_UNIT + threadIdx.x;
-        const uint32_t kk = min(k, kcap);
+        const uint32_t k0 = Q.e_bk[g] + (uint32_t)(u - boff[g]) * PC_EZ_UNIT;
+        const uint32_t k = k0 + threadIdx.x, kk = min(k, kcap);
         const uint32_t m = T.primes[kk];
         const double rm = T.rcpd[kk];
-        const uint32_t b1 = min(g * PC_EZ_BAND + PC_EZ_BAND, Q.a + 1);
-#pragma unroll 4
-        for (uint32_t b = g * PC_EZ_BAND; b < b1; b++) {
-            bool in;
-            uint32_t q = pc_quot31r(Q.Xb[b], Q.Xd[b], m, rm);
-            if constexpr (!GRP) {
-                in = k - (uint32_t)Q.e_start[b] < (uint32_t)Q.e_scount[b];
-            } else {
-                const uint4 cl = Q.e_clu[b];
-                in = (k - cl.y <= cl.x) && cl.x != 0;
-                q = min(max(q, cl.z), cl.w);
+        const uint32_t b0 = max(g * PC_EZ_BAND, Q.c + 1), b1 = min(g * PC_EZ_BAND + PC_EZ_BAND, Q.a);
+        const uint2 lim = Q.e_lim[g];
+        // unsigned sums of 16 values of pi, each at most pi(2^31) < 2^27
+        uint32_t b = b0;
+        if (lim.x <= k0 && k0 + PC_EZ_UNIT <= lim.y) {
+            for (; b + 16 <= b1; b += 16) {
+                uint32_t s = 0;
+                for (uint32_t h = 0; h < 16; h += 4) {
+                    uint32_t v[4], amb = PC_AMB;
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; i++)
+                        v[i] = pc_pi_quot_less1(T.pitab, Q.Xd[b + h + i], rm, true, &amb);
+                    if (__ballot(amb < PC_AMB)) {
+                        for (uint32_t i = 0; i < 4; i++)
+                            s += pc_pi_quot_exact(T, Q.Xb[b + h + i], Q.Xd[b + h + i], m, rm) - 1u;
+                    } else {
+                        s += v[0] + v[1] + v[2] + v[3];
+                    }
+                }
+                a += s + 16u;
             }
-            const uint32_t v = pc_pi_lookup32(T.pitab, in ? q : 2u);
+        }
+        for (; b < b1; b++) {
+            const uint2 r = Q.e_rng[b];
+            if (r.x & PC_CAND)
+                continue;
+            const bool in = k >= r.x && k < r.y;
+            if (!__ballot(in))
+                continue;
+            uint32_t amb = PC_AMB;
+            uint32_t v = pc_pi_quot_less1(T.pitab, Q.Xd[b], rm, in, &amb) + 1u;
+            if (__ballot(amb < PC_AMB)) {
+                if (in)
+                    v = pc_pi_quot_exact(T, Q.Xb[b], Q.Xd[b], m, rm);
+            }
             a += in ? v : 0u;
         }
     }
-    *acc += a;
+    *acc += (int64_t)(2 * a);
+}
+
+// The candidate easy leaves (p_b^2 <= y): *acc -= mu(m) phi(u, b-1), u = X_b / m,
+// over the band's b and the squarefree m of b's range with lpf(m) > p_b.  The
+// calling workgroup (NT threads; every thread calls) takes tiles lb, lb + nlb,
+// ... of PC_EZ_TILE wheel numbers of a band: it keeps those m that can be a
+// leaf of the band's first b (lpf(m) > p_b; a third of them where p_b^2 is
+// near y), packed in LDS, and then each thread takes one m, with 1/m formed
+// once, against the b of the band.  (One item per (b, m), the table tested for
+// each, took 6.3 ms of one pi(10^18); this takes 3.4 ms beside the prime leaves.)
+template <int NT> struct pc_cand_lds {
+    uint32_t m[PC_EZ_TILE]; // m | (mu(m) > 0) << 31
+    uint32_t l[PC_EZ_TILE]; // lpf(m)
+    uint32_t n;
+};
+template <int NT>
+__device__ __forceinline__ void pc_easy_cands(const pc_tables &T, const pc_query &Q, uint64_t lb,
+                                              uint64_t nlb, pc_cand_lds<NT> &L, int64_t *acc,
+                                              unsigned long long *nleaf)
+{
+    const uint32_t nband = Q.a / PC_EZ_BAND + 1, lane = pc_lane();
+    const uint64_t *const boff = Q.e_boff + nband;
+    const uint64_t U = Q.e_total[1];
+    for (uint64_t u = lb; u < U; u += nlb) {
+        const uint32_t g = pc_uniform(pc_band_of(boff, nband, u));
+        const uint32_t b0 = max(g * PC_EZ_BAND, Q.c + 1), b1 = min(g * PC_EZ_BAND + PC_EZ_BAND, Q.a);
+        const uint32_t k0 = Q.e_bk[nband + g] + (uint32_t)(u - boff[g]) * PC_EZ_TILE;
+        const uint32_t p0 = T.primes[b0];
+        __syncthreads(); // the last tile's reads
+        if (threadIdx.x == 0)
+            L.n = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t i = 0; i < PC_EZ_TILE / NT; i++) {
+            const uint32_t m = pc_wheel_m(T, k0 + i * NT + threadIdx.x);
+            const int32_t v = m <= (uint32_t)Q.y ? T.mulpf[m] : 0;
+            const uint32_t l = v < 0 ? (uint32_t)(-v) : (uint32_t)v;
+            const bool keep = l > p0;
+            const uint64_t bal = __ballot(keep);
+            uint32_t at = 0;
+            if (lane == 0 && bal)
+                at = atomicAdd(&L.n, (uint32_t)__builtin_popcountll(bal));
+            at = pc_uniform(at) + (uint32_t)__builtin_popcountll(bal & ((1ull << lane) - 1));
+            if (keep) {
+                L.m[at] = m | (v > 0 ? 0x80000000u : 0u);
+                L.l[at] = l;
+            }
+        }
+        __syncthreads();
+        const uint32_t n = L.n;
+        for (uint32_t i = threadIdx.x; (i & ~63u) < n; i += NT) {
+            const bool have = i < n;
+            const uint32_t e = have ? L.m[i] : 1u, l = have ? L.l[i] : 0u;
+            const uint32_t m = e & 0x7FFFFFFFu;
+            const double rm = pc_rcp_f64(m);
+            int64_t s = 0;
+            uint32_t cnt = 0;
+            for (uint32_t b = b0; b < b1; b++) {
+                const uint2 r = Q.e_rng[b];
+                if (!(r.x & PC_CAND))
+                    continue;
+                const bool in = l > T.primes[b] && m >= (r.x & ~PC_CAND) && m <= r.y;
+                if (!__ballot(in))
+                    continue;
+                uint32_t amb = PC_AMB;
+                uint32_t v = pc_pi_quot_less1(T.pitab, Q.Xd[b], rm, in, &amb);
+                if (__ballot(amb < PC_AMB)) {
+                    if (in)
+                        v = pc_pi_lookup32(T.pitab, pc_quot31(Q.Xb[b], Q.Xd[b], m)) - 1u;
+                }
+                if (in) { // phi(u, b-1) = pi(u) - b + 2
+                    s += (int64_t)v + 3 - (int64_t)b;
+                    cnt++;
+                }
+            }
+            *acc += (e >> 31) ? -s : s;
+            *nleaf += cnt;
+        }
+    }
 }
 
 // pi(x) = S1 + S2t + S2e + S2h + a - 1 - P2, with

@@ -8,7 +8,7 @@
 // ---------------------------------------------------------------------------
 // S1: one lane per n <= y (grid-stride).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(LV_T) void k_s1(pc_tables T, pc_query Q, pc_s128 *part)
+__global__ __launch_bounds__(LV_T) void k_s1(pc_tables T, pc_query Q)
 {
     __shared__ pc_s128 scr[LV_T / 64];
     __shared__ unsigned long long scr64[LV_T / 64];
@@ -21,130 +21,93 @@ __global__ __launch_bounds__(LV_T) void k_s1(pc_tables T, pc_query Q, pc_s128 *p
     acc = pc_block_sum128<LV_T>(acc, scr);
     terms = pc_block_sum<LV_T>(terms, scr64);
     if (threadIdx.x == 0) {
-        part[blockIdx.x] = acc;
+        pc_atomic_add128(&Q.sums->s1, acc);
         atomicAdd(&Q.sums->n_s1, terms);
     }
 }
 
-hipError_t pc_launch_s1(const pc_tables &T, const pc_query &Q, pc_s128 *part, uint32_t nblocks,
-                        hipStream_t s)
+hipError_t pc_launch_s1(const pc_tables &T, const pc_query &Q, uint32_t nblocks, hipStream_t s)
 {
-    k_s1<<<nblocks, LV_T, 0, s>>>(T, Q, part);
+    k_s1<<<nblocks, LV_T, 0, s>>>(T, Q);
     return hipGetLastError();
 }
 
-// X_b for b <= a (pc_xb_item).
-__global__ __launch_bounds__(LV_T) void k_xb(pc_tables T, pc_query Q)
+// X_b and the per-b set-up of the special leaves (pc_leaf_setup_band); at most
+// 1024 workgroups, so that few of them meet at the sums.
+__global__ __launch_bounds__(LV_T) void k_leaf_setup(pc_tables T, pc_query Q)
 {
-    pc_xb_item(T, Q, blockIdx.x * LV_T + threadIdx.x);
+    __shared__ pc_s128 scr[LV_T / 64];
+    pc_setup_sums S;
+    const uint32_t n = max(Q.a, Q.c + Q.nb) + 1; // b < n
+    for (uint32_t b0 = blockIdx.x * LV_T; b0 < n; b0 += gridDim.x * LV_T)
+        pc_leaf_setup_band(T, Q, b0 + threadIdx.x, &S);
+    pc_setup_flush<LV_T>(Q, S, scr);
 }
 
-hipError_t pc_launch_xb(const pc_tables &T, const pc_query &Q, hipStream_t s)
+// The bands' unit offsets (workgroups 0 and 1, a kind each) and the suffix
+// maxima of the hard-leaf u ranges (workgroup 2).
+#define BS_T 1024
+__global__ __launch_bounds__(BS_T) void k_band_scan(pc_query Q)
 {
-    k_xb<<<Q.a / LV_T + 1, LV_T, 0, s>>>(T, Q);
+    __shared__ uint64_t sh[BS_T];
+    const uint32_t nband = Q.a / PC_EZ_BAND + 1, w = blockIdx.x;
+    if (w < 2)
+        pc_band_scan<BS_T>(Q.e_boff + w * nband, nband, Q.e_total + w, sh);
+    else
+        pc_ub_suffix<BS_T>(Q, sh);
+}
+
+hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, hipStream_t s)
+{
+    const uint32_t n = Q.a > Q.c + Q.nb ? Q.a + 1 : Q.c + Q.nb + 1;
+    const uint32_t blocks = (n + LV_T - 1) / LV_T;
+    k_leaf_setup<<<blocks < 1024 ? blocks : 1024, LV_T, 0, s>>>(T, Q);
+    k_band_scan<<<3, BS_T, 0, s>>>(Q);
     return hipGetLastError();
 }
 
-// Per-b set-up of the special leaves outside the sieve (pc_leaf_setup_item).
-__global__ __launch_bounds__(LV_T) void k_leaf_setup(pc_tables T, pc_query Q, pc_s128 *part_t)
-{
-    __shared__ uint64_t scr[LV_T / 64];
-    uint64_t triv, cross;
-    pc_leaf_setup_item(T, Q, blockIdx.x * LV_T + threadIdx.x, &triv, &cross);
-    const uint64_t s = pc_block_sum<LV_T>(triv, scr);
-    const uint64_t cs = pc_block_sum<LV_T>(cross, scr);
-    if (threadIdx.x == 0) {
-        part_t[blockIdx.x] = (pc_s128)s;
-        atomicAdd(&Q.sums->n_trivial, (unsigned long long)s);
-        atomicAdd(&Q.sums->crossings, (unsigned long long)cs);
-    }
-}
-
-__global__ __launch_bounds__(1024) void k_ub_suffix(pc_query Q)
-{
-    __shared__ uint64_t sh[1024];
-    pc_ub_suffix<1024>(Q, sh);
-}
-
-hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, pc_s128 *part_trivial,
-                                uint32_t nblocks, hipStream_t s)
-{
-    k_leaf_setup<<<nblocks, LV_T, 0, s>>>(T, Q, part_trivial);
-    k_ub_suffix<<<1, 1024, 0, s>>>(Q);
-    return hipGetLastError();
-}
-
-// e_off[b] = exclusive prefix of the item counts (mode bit stripped)
-__global__ void k_strip_counts(const uint64_t *e_count, uint64_t *e_off, uint64_t n)
-{
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n)
-        e_off[i] = e_count[i] & ~PC_MODEBIT;
-}
-
-// Candidate easy leaves of one query, tiles of EZ_T * EZ_PER items (pc_easy_tiles).
+// Candidate easy leaves of one query (pc_easy_cands).
 #define EZ_T 256
-#define EZ_PER 32
-
-__global__ __launch_bounds__(EZ_T) void k_easy(pc_tables T, pc_query Q, pc_s128 *part)
+__global__ __launch_bounds__(EZ_T) void k_easy_cands(pc_tables T, pc_query Q)
 {
     __shared__ pc_s128 scr[EZ_T / 64];
     __shared__ unsigned long long scr64[EZ_T / 64];
-    __shared__ uint32_t s_b0;
+    __shared__ pc_cand_lds<EZ_T> L;
+    if (blockIdx.x >= Q.e_total[1])
+        return;
     unsigned long long nleaf = 0;
     int64_t acc = 0;
-    pc_easy_tiles<EZ_T, EZ_PER>(T, Q, blockIdx.x, gridDim.x, &s_b0, &acc, &nleaf);
+    pc_easy_cands<EZ_T>(T, Q, blockIdx.x, gridDim.x, L, &acc, &nleaf);
     const pc_s128 s = pc_block_sum128<EZ_T>((pc_s128)acc, scr);
     nleaf = pc_block_sum<EZ_T>(nleaf, scr64);
-    if (threadIdx.x == 0) {
-        part[blockIdx.x] = s;
+    if (threadIdx.x == 0 && nleaf) {
+        pc_atomic_add128(&Q.sums->s2e, s);
         atomicAdd(&Q.sums->n_easy, nleaf);
     }
 }
 
-hipError_t pc_launch_easy(const pc_tables &T, const pc_query &Q, pc_s128 *part, uint32_t nblocks,
-                          hipStream_t s)
+hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
+                                hipStream_t s)
 {
-    k_easy<<<nblocks, EZ_T, 0, s>>>(T, Q, part);
+    k_easy_cands<<<nblocks, EZ_T, 0, s>>>(T, Q);
     return hipGetLastError();
 }
 
-// The bands of the singles and groups (pc_easy_band_item), one thread per band.
-__global__ __launch_bounds__(LV_T) void k_easy_bands(pc_tables T, pc_query Q)
-{
-    pc_easy_band_item(T, Q, blockIdx.x * LV_T + threadIdx.x);
-}
-
-hipError_t pc_launch_easy_bands(const pc_tables &T, const pc_query &Q, hipStream_t s)
-{
-    const uint32_t nband = Q.a / PC_EZ_BAND + 1;
-    k_easy_bands<<<(nband + LV_T - 1) / LV_T, LV_T, 0, s>>>(T, Q);
-    return hipGetLastError();
-}
-
-// The singles and the groups of the easy leaves of one query (pc_easy_bands).
-__global__ __launch_bounds__(PC_EZ_UNIT) void k_easy_band(pc_tables T, pc_query Q, pc_s128 *part)
+// The prime easy leaves of one query (pc_easy_primes).
+__global__ __launch_bounds__(PC_EZ_UNIT) void k_easy_primes(pc_tables T, pc_query Q)
 {
     __shared__ pc_s128 scr[PC_EZ_UNIT / 64];
-    __shared__ uint32_t s_g[2];
     int64_t acc = 0;
-    pc_easy_bands<PC_EZ_UNIT, false>(T, Q, blockIdx.x, gridDim.x, &s_g[0], &acc);
-    pc_easy_bands<PC_EZ_UNIT, true>(T, Q, blockIdx.x, gridDim.x, &s_g[1], &acc);
+    pc_easy_primes<PC_EZ_UNIT>(T, Q, blockIdx.x, gridDim.x, &acc);
     const pc_s128 s = pc_block_sum128<PC_EZ_UNIT>((pc_s128)acc, scr);
-    if (threadIdx.x == 0)
-        part[blockIdx.x] = s;
+    if (threadIdx.x == 0 && s != 0)
+        pc_atomic_add128(&Q.sums->s2e, s);
 }
 
-hipError_t pc_launch_easy_band(const pc_tables &T, const pc_query &Q, pc_s128 *part,
-                               uint32_t nblocks, hipStream_t s)
+hipError_t pc_launch_easy_primes(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
+                                 hipStream_t s)
 {
-    k_easy_band<<<nblocks, PC_EZ_UNIT, 0, s>>>(T, Q, part);
-    return hipGetLastError();
-}
-
-hipError_t pc_launch_strip(const uint64_t *e_count, uint64_t *e_off, uint64_t n, hipStream_t s)
-{
-    k_strip_counts<<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(e_count, e_off, n);
+    k_easy_primes<<<nblocks, PC_EZ_UNIT, 0, s>>>(T, Q);
     return hipGetLastError();
 }
 
