@@ -54,7 +54,6 @@ std::atomic<size_t> g_dev_bytes{0}, g_dev_peak{0}; // device bytes held, and the
 
 hipStream_t g_stream = nullptr;  // the library stream
 hipStream_t g_stream2 = nullptr; // easy leaves, concurrent with the sieve (same priority)
-hipStream_t g_stream3 = nullptr; // the candidate easy leaves, beside the bands (same priority)
 
 // Completion events of caller-memory batches queued on callers' streams
 // (they read the shared tables), and spare events to record the next ones.
@@ -75,8 +74,6 @@ void dfree(DevBuf &b)
         async_wait_all(); // kernels queued earlier may still read the buffer
         if (g_stream2)
             (void)hipStreamSynchronize(g_stream2);
-        if (g_stream3)
-            (void)hipStreamSynchronize(g_stream3);
         if (g_stream)
             (void)hipStreamSynchronize(g_stream);
         (void)hipFree(b.p);
@@ -226,15 +223,15 @@ uint32_t seed_rec_cols(uint64_t m, uint32_t c, uint32_t nb)
 }
 
 struct QueryBufs {
-    DevBuf Ub, Xb, Xd, Xbh, e_rng, e_bk, e_boff, e_lim, e_total, sums, fin, qdev;
+    DevBuf Ub, Xb, Xd, Xbh, e_rng, e_bk, e_boff, e_lim, sums, qdev;
     DevBuf work, tiles_a, trace;
-    DevBuf tiles, cnt, wgt, carry_rows, carry_a, carry_b, status, ticket, part_tile_h,
-        part_tile_p, part_scan_h, part_scan_p, err;
+    DevBuf tiles, cnt, wgt, carry_rows, carry_a, carry_b, status, err;
     DevBuf row_off, blkoff, cntP, wP, carryP, seed_term;
 };
 QueryBufs g_Q;
 
-hipEvent_t g_fork = nullptr, g_join = nullptr, g_join3 = nullptr;
+hipEvent_t g_fork = nullptr, g_join = nullptr;
+pc_back *g_back = nullptr; // pinned: what a query brings back
 
 void init_stream()
 {
@@ -242,10 +239,8 @@ void init_stream()
         hipck(hipStreamCreateWithFlags(&g_stream, hipStreamNonBlocking), "hipStreamCreate");
     if (!g_stream2)
         hipck(hipStreamCreateWithFlags(&g_stream2, hipStreamNonBlocking), "hipStreamCreate");
-    if (!g_stream3)
-        hipck(hipStreamCreateWithFlags(&g_stream3, hipStreamNonBlocking), "hipStreamCreate");
-    if (!g_join3)
-        hipck(hipEventCreateWithFlags(&g_join3, hipEventDisableTiming), "hipEventCreate");
+    if (!g_back)
+        hipck(hipHostMalloc((void **)&g_back, sizeof(pc_back), hipHostMallocDefault), "hipHostMalloc");
     if (!g_fork)
         hipck(hipEventCreateWithFlags(&g_fork, hipEventDisableTiming), "hipEventCreate");
     if (!g_join)
@@ -520,8 +515,6 @@ void drop_tables(bool release)
         async_wait_all();
         if (g_stream2)
             (void)hipStreamSynchronize(g_stream2);
-        if (g_stream3)
-            (void)hipStreamSynchronize(g_stream3);
         if (g_stream)
             (void)hipStreamSynchronize(g_stream);
     }
@@ -536,10 +529,9 @@ void drop_tables(bool release)
 void drop_query_bufs()
 {
     QueryBufs &B = g_Q;
-    DevBuf *all[] = {&B.Ub, &B.work, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_rng, &B.e_bk, &B.e_boff, &B.e_lim, &B.e_total,
-                     &B.sums, &B.fin, &B.tiles, &B.cnt, &B.wgt, &B.carry_rows,
-                     &B.carry_a, &B.carry_b, &B.status, &B.ticket, &B.part_tile_h,
-                     &B.part_tile_p, &B.part_scan_h, &B.part_scan_p, &B.err, &B.qdev,
+    DevBuf *all[] = {&B.Ub, &B.work, &B.tiles_a, &B.trace, &B.Xb, &B.Xd, &B.Xbh, &B.e_rng, &B.e_bk, &B.e_boff, &B.e_lim,
+                     &B.sums, &B.tiles, &B.cnt, &B.wgt, &B.carry_rows,
+                     &B.carry_a, &B.carry_b, &B.status, &B.err, &B.qdev,
                      &B.row_off, &B.blkoff, &B.cntP, &B.wP, &B.carryP, &B.seed_term};
     for (DevBuf *b : all)
         dfree(*b);
@@ -708,8 +700,15 @@ EvPair &ev_next()
 }
 
 // time the launches made by f on stream st; returns the event pair index
+// (g_ev_on false: nobody asks for the times; the launches only)
+bool g_ev_on = true;
+
 template <typename F> size_t timed(F &&f, hipStream_t st = nullptr)
 {
+    if (!g_ev_on) {
+        f();
+        return 0;
+    }
     if (!st)
         st = g_stream;
     EvPair &e = ev_next();
@@ -766,12 +765,14 @@ uint64_t plan_tile_work(const Knobs &K)
 // bits; the sieve's and the leaves' quotients all stay below 2^64).
 constexpr pc_u128 kWideMax = (pc_u128)1 << 72;
 
-void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
+// want_times: the caller reads the ms_k_* and ms_leaves fields.
+void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_times = false)
 {
     auto t0 = clk::now();
     init_stream();
-    // the plan copies of an earlier query (one that failed part way too) are done
+    // the work of an earlier query (one that failed part way too) is done
     hipck(hipStreamSynchronize(g_stream), "sync");
+    hipck(hipStreamSynchronize(g_stream2), "sync");
     g_pin.reset();
     QueryBufs &B = g_Q;
     const uint64_t x_hi = (uint64_t)(x >> 64);
@@ -831,6 +832,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     Q.sieve_end = baseB + nB * spanB;
     Q.nseg = nseg;
     g_ev_used = 0;
+    g_ev_on = want_times;
 
     // --- per-query tables and the leaves outside the sieve ---
     ensure(B.Xb, (a + 2) * 8, "X_b");
@@ -842,10 +844,16 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         ensure(B.Xbh, (a + 2) * 4, "X_b");
         Q.Xbh = ptr<uint32_t>(B.Xbh);
     }
-    ensure(B.sums, sizeof(pc_sums), "sums");
-    ensure(B.fin, sizeof(pc_final), "final");
-    ensure(B.e_total, 32, "easy total");
-    hipck(pc_launch_fill_u64(ptr<uint64_t>(B.sums), sizeof(pc_sums) / 8, 0, g_stream), "fill");
+    ensure(B.sums, sizeof(pc_sums) + 16, "sums"); // and the easy leaves' unit totals
+    ensure(B.err, 16, "error flag");              // the flag, tiles in all, of the planned rows
+    {
+        pc_prep_args P{};
+        P.zero[0] = ptr<uint64_t>(B.sums);
+        P.nz[0] = sizeof(pc_sums) / 8;
+        P.zero[1] = ptr<uint64_t>(B.err);
+        P.nz[1] = 2;
+        hipck(pc_launch_prep(P, g_stream), "clear");
+    }
     pc_sums *sums = ptr<pc_sums>(B.sums);
     Q.sums = sums;
 
@@ -860,38 +868,44 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     Q.e_bk = ptr<uint32_t>(B.e_bk);
     Q.e_boff = ptr<uint64_t>(B.e_boff);
     Q.e_lim = ptr<uint2>(B.e_lim);
-    Q.e_total = ptr<uint64_t>(B.e_total);
-    const size_t ev_s1 = timed([&] {
-        hipck(pc_launch_s1(T, Q, (uint32_t)std::min<uint64_t>(2048, y / 256 + 1), g_stream), "S1");
-    });
+    Q.e_total = reinterpret_cast<uint64_t *>(sums + 1);
     hipck(pc_launch_leaf_setup(T, Q, g_stream), "leaf setup");
-    // The easy leaves touch nothing the sieve writes: they run on the second
-    // stream once the last sieve window is queued, and rejoin before the
-    // combination.  Both kernels keep every CU busy, so running them side by
-    // side gains nothing (measured); after the windows, neither delays the
-    // other's launches.
-    size_t ev_easy = 0;
-    bool forked = false;
-    auto fork_easy = [&]() {
-        if (forked)
-            return;
-        forked = true;
+    // S1 and the easy leaves touch nothing the sieve writes.  Of a large query
+    // they and the sieve each keep every CU busy, so they start once the last
+    // sieve window is queued and delay none of its launches: S1, then the candidates
+    // (table reads) beside the prime leaves (integer issue) on the second stream.  Of a small one (the GPU mostly waits) all of them start at
+    // once, on the second stream.
+    const bool early = nseg <= 4096;
+    size_t ev_s1 = 0, ev_easy = 0;
+    auto leaves = [&]() {
+        const hipStream_t st = early ? g_stream2 : g_stream;
+        const uint32_t nblk = (uint32_t)std::clamp<uint64_t>(y / 256, 256, 4096);
+        auto s1 = [&]() {
+            ev_s1 = timed(
+                [&] {
+                    hipck(pc_launch_s1(T, Q, (uint32_t)std::min<uint64_t>(2048, y / 256 + 1), st),
+                          "S1");
+                },
+                st);
+        };
+        if (!early)
+            s1();
         hipck(hipEventRecord(g_fork, g_stream), "hipEventRecord");
         hipck(hipStreamWaitEvent(g_stream2, g_fork, 0), "hipStreamWaitEvent");
-        // the primes and the candidates side by side on two streams; as many
-        // workgroups as 4096, fewer for a small y
-        const uint32_t nblk = (uint32_t)std::clamp<uint64_t>(y / 256, 256, 4096);
+        if (early)
+            s1();
         ev_easy = timed(
             [&] {
-                hipck(hipStreamWaitEvent(g_stream3, g_fork, 0), "hipStreamWaitEvent");
-                hipck(pc_launch_easy_cands(T, Q, nblk, g_stream3), "easy");
-                hipck(hipEventRecord(g_join3, g_stream3), "hipEventRecord");
+                hipck(pc_launch_easy_cands(T, Q, nblk, st), "easy");
                 hipck(pc_launch_easy_primes(T, Q, nblk, g_stream2), "easy");
-                hipck(hipStreamWaitEvent(g_stream2, g_join3, 0), "hipStreamWaitEvent");
+                hipck(hipEventRecord(g_join, g_stream2), "hipEventRecord");
+                if (!early)
+                    hipck(hipStreamWaitEvent(g_stream, g_join, 0), "hipStreamWaitEvent");
             },
-            g_stream2);
-        hipck(hipEventRecord(g_join, g_stream2), "hipEventRecord");
+            st);
     };
+    if (early)
+        leaves();
 
     // --- the sieve of [1, z] in windows of segments ---
     auto t2 = clk::now();
@@ -934,7 +948,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         std::vector<uint32_t> &bo = blkoffs[w];
         bo.push_back(0);
         for (uint64_t r = win_start[w]; r < win_start[w + 1]; r += R)
-            bo.push_back(bo.back() + (rowlen[r] + 255) / 256);
+            bo.push_back(bo.back() + (rowlen[r] + 255) / 256 + 1); // the last one: P2
         max_tickets = std::max<uint64_t>(max_tickets, bo.back());
     }
 
@@ -949,17 +963,12 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     else
         ensure(B.carryP, max_rows * 8, "P2 carries");
     ensure(B.row_off, (max_rows + 1) * 8, "row offsets");
-    ensure(B.blkoff, (max_chunks + 1) * 4, "scan blocks");
+    ensure(B.blkoff, (max_chunks + 2) * 4, "scan blocks"); // (copied as 64-bit words)
     ensure(B.carry_a, (size_t)Q.ncol * 8, "carry");
     ensure(B.carry_b, (size_t)Q.ncol * 8, "carry");
     if (K.seeded)
         ensure(B.seed_term, (size_t)Q.ncol * 8, "seed terms");
-    ensure(B.status, max_tickets * 256 * 8 + 8, "look-back status");
-    ensure(B.ticket, 8, "ticket");
-    ensure(B.part_scan_h, max_tickets * 16 + 16, "scan partials");
-    ensure(B.part_scan_p, 16, "scan partials");
-    ensure(B.err, 16, "error flag"); // the flag, tiles in all, tiles of the planned rows
-    hipck(pc_launch_fill_u64(ptr<uint64_t>(B.carry_a), Q.ncol, 0, g_stream), "fill");
+    ensure(B.status, max_tickets * 256 * 8 + 8, "look-back status, ticket");
     // the query as the sieve reads it: one entry of a device array
     Q.row_off = ptr<uint64_t>(B.row_off);
     Q.cnt = ptr<uint32_t>(B.cnt);
@@ -969,17 +978,17 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
     Q.wP = ptr<int32_t>(B.wP);
     Q.carryP = ptr<uint64_t>(B.carryP);
     ensure(B.qdev, sizeof(pc_query), "query");
-    hipck(hipMemcpyAsync(B.qdev.p, &Q, sizeof Q, hipMemcpyHostToDevice, g_stream), "H2D");
-    hipck(pc_launch_fill_u64(ptr<uint64_t>(B.err), 1, 0, g_stream), "fill");
+    static_assert(sizeof(pc_query) % 8 == 0, "copied as 64-bit words");
 
     // PICOUNT_TILE_TRACE=<path>: append one line per sieve tile (profiling aid)
     FILE *trace_file = nullptr;
     if (const char *tp = std::getenv("PICOUNT_TILE_TRACE"))
         trace_file = std::fopen(tp, "a");
     std::vector<pc_tile> tiles_a;
-    uint64_t ntiles_a = 0, ntiles_total = 0;
+    uint64_t ntiles_a = 0;
     uint64_t *cin = ptr<uint64_t>(B.carry_a), *cout = ptr<uint64_t>(B.carry_b);
     const int bflag = K.batch ? 0 : 0x100;
+    bool first_window = true;
     if (c < 3) { // y < 5: the bitmap needs 2, 3 and 5 in the wheel; z < 32 here
         ev_sieve.push_back(
             timed([&] { hipck(pc_launch_sieve_tiny(T, Q, g_stream), "sieve"); }));
@@ -1000,15 +1009,37 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
                                      g_stream),
                       "seeds");
             }));
-        } else if (K.seeded) {
-            hipck(pc_launch_fill_u64(cin, Q.ncol, 0, g_stream), "fill");
         }
-        {
-            std::vector<uint64_t> off(rows + 1, 0);
+        const uint32_t nticket = blkoffs[w].back();
+        { // the window's plan, straight from pinned memory, and what starts at zero
+            pc_prep_args P{};
+            uint64_t *const off = static_cast<uint64_t *>(g_pin.take((rows + 1) * 8));
+            off[0] = 0;
             for (uint64_t r = 0; r < rows; r++)
                 off[r + 1] = off[r] + rowlen[r0 + r];
-            h2d(B.row_off.p, off.data(), off.size() * 8, g_stream, "row offsets");
-            h2d(B.blkoff.p, blkoffs[w].data(), blkoffs[w].size() * 4, g_stream, "scan blocks");
+            P.src[0] = off;
+            P.dst[0] = ptr<uint64_t>(B.row_off);
+            P.n[0] = rows + 1;
+            P.n[1] = (blkoffs[w].size() + 1) / 2;
+            uint64_t *const bo = static_cast<uint64_t *>(g_pin.take(P.n[1] * 8));
+            memcpy(bo, blkoffs[w].data(), blkoffs[w].size() * 4);
+            P.src[1] = bo;
+            P.dst[1] = ptr<uint64_t>(B.blkoff);
+            if (first_window) { // the query as the sieve reads it: one entry of a device array
+                void *const q = g_pin.take(sizeof Q);
+                memcpy(q, &Q, sizeof Q);
+                P.src[2] = static_cast<uint64_t *>(q);
+                P.dst[2] = ptr<uint64_t>(B.qdev);
+                P.n[2] = sizeof Q / 8;
+            }
+            P.zero[0] = ptr<uint64_t>(B.status); // the look-back words, then the ticket
+            P.nz[0] = (uint64_t)nticket * 256 + 1;
+            if (K.seeded ? w == 0 : first_window) {
+                P.zero[1] = cin;
+                P.nz[1] = Q.ncol;
+            }
+            first_window = false;
+            hipck(pc_launch_prep(P, g_stream), "plan");
         }
         // rows [r0, min(r1, nA)) are small segments, the rest workgroup segments
         tiles_a.clear();
@@ -1042,9 +1073,6 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         }
         ntiles_a += tiles_a.size();
         ensure(B.tiles_a, tiles_a.size() * sizeof(pc_tile), "tiles");
-        const size_t npart = std::max(tiles_a.size(), tiles_b);
-        ensure(B.part_tile_h, npart * 16, "tile partials");
-        ensure(B.part_tile_p, npart * 16, "tile partials");
         h2d(B.tiles_a.p, tiles_a.data(), tiles_a.size() * sizeof(pc_tile), g_stream, "tiles");
         auto sieve_args = [&](bool small) {
             pc_sieve_args A{};
@@ -1055,12 +1083,10 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
             A.seg0 = r0;
             A.lo_base = small ? 0 : baseB;
             A.seg_base = small ? 0 : nA;
-            A.part_hard = ptr<pc_s128>(B.part_tile_h);
-            A.part_p2 = ptr<pc_s128>(B.part_tile_p);
             A.err = ptr<int32_t>(B.err);
             return A;
         };
-        // one sieve launch per geometry; the tile partials are folded right after
+        // one sieve launch per geometry
         auto sieve = [&](bool small, int mode) {
             pc_sieve_args A = sieve_args(small);
             if (A.ntiles == 0)
@@ -1097,14 +1123,6 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
                     std::fputc('\n', trace_file);
                 }
             }
-            if (mode != PC_MODE_COUNT) {
-                hipck(pc_launch_sum128(ptr<pc_s128>(B.part_tile_h), A.ntiles, &sums->hard_local,
-                                       g_stream),
-                      "sum");
-                hipck(pc_launch_sum128(ptr<pc_s128>(B.part_tile_p), A.ntiles, &sums->p2_local,
-                                       g_stream),
-                      "sum");
-            }
         };
         const int first = K.two_pass ? PC_MODE_COUNT : PC_MODE_TALLY;
         sieve(true, first);
@@ -1122,19 +1140,14 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         SA.carry_in = cin;
         SA.carry_out = cout;
         SA.status = ptr<uint64_t>(B.status);
-        SA.ticket = ptr<uint32_t>(B.ticket);
-        SA.part_hard = ptr<pc_s128>(B.part_scan_h);
-        SA.part_p2 = ptr<pc_s128>(B.part_scan_p);
+        SA.ticket = reinterpret_cast<uint32_t *>(SA.status + (uint64_t)nticket * 256);
+        SA.sums = sums;
         SA.err = ptr<int32_t>(B.err);
         SA.nrows = rows;
         SA.nb = Q.nb;
         SA.rows_per_chunk = R;
         SA.nchunk = (uint32_t)((rows + R - 1) / R);
-        SA.nticket = blkoffs[w].back();
-        hipck(pc_launch_fill_u64(ptr<uint64_t>(B.status), (uint64_t)SA.nticket * 256, 0,
-                                 g_stream),
-              "fill");
-        hipck(pc_launch_fill_u64(ptr<uint64_t>(B.ticket), 1, 0, g_stream), "fill");
+        SA.nticket = nticket;
         ev_scan.push_back(timed([&] {
             hipck(pc_launch_scan(SA, K.two_pass ? PC_MODE_COUNT : PC_MODE_TALLY, g_stream),
                   "scan");
@@ -1142,31 +1155,24 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         if (K.two_pass) {
             sieve(true, PC_MODE_LEAVES);
             sieve(false, PC_MODE_LEAVES);
-        } else {
-            hipck(pc_launch_sum128(ptr<pc_s128>(B.part_scan_h), SA.nticket, &sums->hard_dot,
-                                   g_stream),
-                  "sum");
-            hipck(pc_launch_sum128(ptr<pc_s128>(B.part_scan_p), 1, &sums->p2_dot, g_stream),
-                  "sum");
         }
         if (!K.seeded)
             std::swap(cin, cout);
     }
     if (trace_file)
         std::fclose(trace_file);
-    fork_easy();
-    hipck(hipStreamWaitEvent(g_stream, g_join, 0), "hipStreamWaitEvent");
-    hipck(pc_launch_combine(sums, Q, kx, ptr<pc_final>(B.fin), g_stream), "combine");
-    pc_final fin{};
-    pc_sums hs{};
-    int32_t err2[2] = {0, 0}; // the error flag, the tiles
-    hipck(hipMemcpyAsync(&hs, B.sums.p, sizeof hs, hipMemcpyDeviceToHost, g_stream), "D2H");
-    hipck(hipMemcpyAsync(&fin, B.fin.p, sizeof fin, hipMemcpyDeviceToHost, g_stream), "D2H");
-    hipck(hipMemcpyAsync(err2, B.err.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
+    if (!early)
+        leaves();
+    else
+        hipck(hipStreamWaitEvent(g_stream, g_join, 0), "hipStreamWaitEvent");
+    memset(g_back, 0, sizeof *g_back); // ok = 0 until the combination writes it
+    hipck(pc_launch_combine(sums, Q, kx, ptr<int32_t>(B.err), g_back, g_stream), "combine");
     hipck(hipStreamSynchronize(g_stream), "sync");
+    const pc_final &fin = g_back->fin;
+    const pc_sums &hs = g_back->sums;
     const double ms_sieve = ms_since(t2);
-    const int32_t err = err2[0];
-    ntiles_total = ntiles_a + (uint32_t)err2[1];
+    const int32_t err = g_back->err[0];
+    const uint64_t ntiles_total = ntiles_a + (uint32_t)g_back->err[1];
     if (err & 1)
         fail(PC_EINTERNAL, "look-back scan did not complete");
     if (err & 8)
@@ -1209,13 +1215,17 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
         res->windows = nwin;
         res->segment_bits = S;
         res->small_segments = nA;
+        res->sieve_launches = (uint32_t)ev_sieve.size();
+        res->scan_launches = (uint32_t)ev_scan.size();
         res->device_bytes = g_dev_peak;
         res->ms_total = ms_since(t0);
         res->ms_tables = ms_tables;
+        res->ms_sieve = ms_sieve;
+        if (!want_times)
+            return;
         float ms_lv = 0; // S1 start to the end of the easy leaves (GPU clock)
         hipck(hipEventElapsedTime(&ms_lv, g_ev[ev_s1].a, g_ev[ev_easy].b), "hipEventElapsedTime");
         res->ms_leaves = ms_lv;
-        res->ms_sieve = ms_sieve;
         res->ms_k_s1 = ev_ms(ev_s1);
         res->ms_k_easy = ev_ms(ev_easy);
         for (size_t i : ev_sieve)
@@ -1224,8 +1234,6 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res)
             res->ms_k_scan += ev_ms(i);
         for (size_t i : ev_seed)
             res->ms_k_seed += ev_ms(i);
-        res->sieve_launches = (uint32_t)ev_sieve.size();
-        res->scan_launches = (uint32_t)ev_scan.size();
     }
 }
 
@@ -1287,7 +1295,7 @@ void pi_one(pc_u128 x, const Knobs &K, double alpha, pc_result *res, uint64_t *p
         Kx.wg = e.wg;
     }
     pc_result r;
-    run_query(x, y, Kx, &r);
+    run_query(x, y, Kx, &r, res != nullptr);
     *pi = r.pi;
     if (res)
         *res = r;
@@ -2342,7 +2350,7 @@ pc_status pc_decompose(uint64_t x, uint64_t y, const pc_config *cfg, pc_result *
         Knobs K = knobs_from(cfg);
         if (cfg && (cfg->flags & PC_FLAG_REBUILD_TABLES))
             drop_tables(false);
-        run_query(x, y, K, &r);
+        run_query(x, y, K, &r, true);
     });
     if (st == PC_OK && res)
         *res = r;
@@ -2627,17 +2635,19 @@ void pc_shutdown(void)
     g_async_host_cap = 0;
     drop_query_bufs();
     g_pin.release();
-    for (hipStream_t *st : {&g_stream2, &g_stream3})
-        if (*st) {
-            (void)hipStreamSynchronize(*st);
-            (void)hipStreamDestroy(*st);
-            *st = nullptr;
-        }
+    if (g_stream2) {
+        (void)hipStreamSynchronize(g_stream2);
+        (void)hipStreamDestroy(g_stream2);
+        g_stream2 = nullptr;
+    }
     if (g_stream) {
         (void)hipStreamDestroy(g_stream);
         g_stream = nullptr;
     }
-    for (hipEvent_t *e : {&g_fork, &g_join, &g_join3})
+    if (g_back)
+        (void)hipHostFree(g_back);
+    g_back = nullptr;
+    for (hipEvent_t *e : {&g_fork, &g_join})
         if (*e) {
             (void)hipEventDestroy(*e);
             *e = nullptr;

@@ -148,8 +148,6 @@ struct pc_sieve_args {
     uint64_t seg0;          // first segment of the window: row = seg - seg0
     uint64_t lo_base;       // segment seg starts at lo_base + (seg - seg_base) * pc_seg_span
     uint64_t seg_base;
-    pc_s128 *part_hard;     // per tile; null: added to the tile's query sums instead
-    pc_s128 *part_p2;       // per tile (null as part_hard)
     int32_t *err;
     uint32_t *trace;        // optional, PC_TRACE_W words per tile (profiling aid)
 };
@@ -180,8 +178,18 @@ hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t 
                                 hipStream_t s);
 hipError_t pc_launch_easy_primes(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
                                  hipStream_t s);
-hipError_t pc_launch_sum128(const pc_s128 *part, uint32_t n, pc_s128 *acc, hipStream_t s);
 hipError_t pc_launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
+
+// Up to three word ranges copied from host memory that the device reads (pinned)
+// and four cleared, in one launch.
+struct pc_prep_args {
+    const uint64_t *src[3];
+    uint64_t *dst[3];
+    uint64_t n[3];
+    uint64_t *zero[4];
+    uint64_t nz[4];
+};
+hipError_t pc_launch_prep(const pc_prep_args &A, hipStream_t s);
 
 // The tile list of a sieve launch (pc_plan.hip), written to tiles[ntiles]:
 // the planned rows of every query (its first ones, the leaf-dense low end),
@@ -215,9 +223,9 @@ hipError_t pc_launch_sieve(const pc_sieve_args &A, uint32_t seg_log2, uint32_t w
 hipError_t pc_launch_sieve_tiny(const pc_tables &T, const pc_query &Q, hipStream_t s);
 // The carries of one window: per sieving column an exclusive scan of the
 // staircase rows (decoupled look-back over chunks of rows), and the same for
-// the P2 column (cntP, one workgroup).  Workgroup tickets run chunk by chunk;
-// chunk k has blkoff[k+1] - blkoff[k] blocks of 256 columns (those below the
-// chunk's first row length).
+// the P2 column (cntP).  Workgroup tickets run chunk by chunk; chunk k has
+// blkoff[k+1] - blkoff[k] of them: a block of 256 columns each (those below the
+// chunk's first row length) and one for the P2 column.
 struct pc_scan_args {
     const uint32_t *cnt;
     const int32_t *wgt;
@@ -231,8 +239,7 @@ struct pc_scan_args {
     uint64_t *carry_out;      // per column, for the next window
     uint64_t *status;         // [blkoff[nchunk] * 256] look-back words, zeroed
     uint32_t *ticket;         // zeroed
-    pc_s128 *part_hard;       // per ticket
-    pc_s128 *part_p2;         // one
+    pc_sums *sums;            // hard_dot, p2_dot
     int32_t *err;
     uint64_t nrows;
     uint32_t nb;
@@ -282,5 +289,12 @@ hipError_t pc_launch_batch_out(const pc_final *fin, const uint64_t *pos, uint32_
                                const int32_t *err, uint64_t *out, hipStream_t s);
 hipError_t pc_launch_scatter_u64(const ulonglong2 *kv, uint64_t n, uint64_t *out, hipStream_t s);
 
+// What one query brings back to the host, written by the combination into
+// pinned memory (no copy).
+struct pc_back {
+    pc_final fin;
+    pc_sums sums;
+    int32_t err[4]; // the error flag, the sieve's tiles
+};
 hipError_t pc_launch_combine(const pc_sums *sums, const pc_query &Q, uint64_t kp2,
-                             pc_final *out, hipStream_t s);
+                             const int32_t *err, pc_back *out, hipStream_t s);

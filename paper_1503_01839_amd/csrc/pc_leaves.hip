@@ -67,7 +67,7 @@ hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, hipStream
 }
 
 // Candidate easy leaves of one query (pc_easy_cands).
-#define EZ_T 256
+#define EZ_T PC_EZ_UNIT
 __global__ __launch_bounds__(EZ_T) void k_easy_cands(pc_tables T, pc_query Q)
 {
     __shared__ pc_s128 scr[EZ_T / 64];
@@ -86,6 +86,17 @@ __global__ __launch_bounds__(EZ_T) void k_easy_cands(pc_tables T, pc_query Q)
     }
 }
 
+// The prime easy leaves of one query (pc_easy_primes).
+__global__ __launch_bounds__(EZ_T) void k_easy_primes(pc_tables T, pc_query Q)
+{
+    __shared__ pc_s128 scr[EZ_T / 64];
+    int64_t acc = 0;
+    pc_easy_primes<EZ_T>(T, Q, blockIdx.x, gridDim.x, &acc);
+    const pc_s128 s = pc_block_sum128<EZ_T>((pc_s128)acc, scr);
+    if (threadIdx.x == 0 && s != 0)
+        pc_atomic_add128(&Q.sums->s2e, s);
+}
+
 hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
                                 hipStream_t s)
 {
@@ -93,41 +104,37 @@ hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t 
     return hipGetLastError();
 }
 
-// The prime easy leaves of one query (pc_easy_primes).
-__global__ __launch_bounds__(PC_EZ_UNIT) void k_easy_primes(pc_tables T, pc_query Q)
-{
-    __shared__ pc_s128 scr[PC_EZ_UNIT / 64];
-    int64_t acc = 0;
-    pc_easy_primes<PC_EZ_UNIT>(T, Q, blockIdx.x, gridDim.x, &acc);
-    const pc_s128 s = pc_block_sum128<PC_EZ_UNIT>((pc_s128)acc, scr);
-    if (threadIdx.x == 0 && s != 0)
-        pc_atomic_add128(&Q.sums->s2e, s);
-}
-
 hipError_t pc_launch_easy_primes(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
                                  hipStream_t s)
 {
-    k_easy_primes<<<nblocks, PC_EZ_UNIT, 0, s>>>(T, Q);
+    k_easy_primes<<<nblocks, EZ_T, 0, s>>>(T, Q);
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// acc += sum of part[0..n)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(LV_T) void k_sum128(const pc_s128 *part, uint32_t n, pc_s128 *acc)
+__global__ __launch_bounds__(LV_T) void k_prep(pc_prep_args A)
 {
-    __shared__ pc_s128 scr[LV_T / 64];
-    pc_s128 s = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += LV_T)
-        s += part[i];
-    s = pc_block_sum128<LV_T>(s, scr);
-    if (threadIdx.x == 0)
-        *acc += s;
+    const uint64_t i0 = (uint64_t)blockIdx.x * LV_T + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * LV_T;
+#pragma unroll
+    for (int r = 0; r < 3; r++)
+        for (uint64_t i = i0; i < A.n[r]; i += stride)
+            A.dst[r][i] = A.src[r][i];
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        for (uint64_t i = i0; i < A.nz[r]; i += stride)
+            A.zero[r][i] = 0;
 }
 
-hipError_t pc_launch_sum128(const pc_s128 *part, uint32_t n, pc_s128 *acc, hipStream_t s)
+hipError_t pc_launch_prep(const pc_prep_args &A, hipStream_t s)
 {
-    k_sum128<<<1, LV_T, 0, s>>>(part, n, acc);
+    uint64_t n = 1;
+    for (int r = 0; r < 4; r++) {
+        n = n < A.nz[r] ? A.nz[r] : n;
+        if (r < 3)
+            n = n < A.n[r] ? A.n[r] : n;
+    }
+    const uint64_t nb = (n + LV_T - 1) / LV_T;
+    k_prep<<<(uint32_t)(nb < 1024 ? nb : 1024), LV_T, 0, s>>>(A);
     return hipGetLastError();
 }
 
@@ -149,16 +156,28 @@ hipError_t pc_launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s
     return hipGetLastError();
 }
 
-// pi(x) and its parts from the partial sums (pc_combine_one).
-__global__ void k_combine(const pc_sums *S, pc_query Q, uint64_t kp2, pc_final *out)
+// pi(x) and its parts from the partial sums (pc_combine_one), with the sums
+// and the flags, into the host's memory: one word a thread.
+__global__ __launch_bounds__(64) void k_combine(const pc_sums *S, pc_query Q, uint64_t kp2,
+                                               const int32_t *err, pc_back *out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        pc_combine_one(*S, Q, kp2, out);
+    __shared__ pc_back b;
+    static_assert(sizeof(pc_back) % 8 == 0, "copied as 64-bit words");
+    if (threadIdx.x == 0) {
+        b.sums = *S;
+        pc_combine_one(b.sums, Q, kp2, &b.fin);
+        for (int i = 0; i < 4; i++)
+            b.err[i] = err[i];
+    }
+    __syncthreads();
+    const uint64_t *const w = reinterpret_cast<const uint64_t *>(&b);
+    for (uint32_t i = threadIdx.x; i < sizeof(pc_back) / 8; i += 64)
+        reinterpret_cast<uint64_t *>(out)[i] = w[i];
 }
 
-hipError_t pc_launch_combine(const pc_sums *sums, const pc_query &Q, uint64_t kp2, pc_final *out,
-                             hipStream_t s)
+hipError_t pc_launch_combine(const pc_sums *sums, const pc_query &Q, uint64_t kp2,
+                             const int32_t *err, pc_back *out, hipStream_t s)
 {
-    k_combine<<<1, 64, 0, s>>>(sums, Q, kp2, out);
+    k_combine<<<1, 64, 0, s>>>(sums, Q, kp2, err, out);
     return hipGetLastError();
 }

@@ -147,13 +147,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     tile.q = pc_uniform(tile.q);
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63;
-    if (tile.col_lo >= tile.col_hi) { // a split that owns no column
-        if (MODE != PC_MODE_COUNT && tid == 0 && A.part_hard) {
-            A.part_hard[blockIdx.x] = 0;
-            A.part_p2[blockIdx.x] = 0;
-        }
+    if (tile.col_lo >= tile.col_hi) // an empty tile
         return;
-    }
     const uint64_t seg = tile.seg;
     const uint64_t lo = A.lo_base + (seg - A.seg_base) * SPAN;
     const uint64_t hi = lo + SPAN;
@@ -1230,13 +1225,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             }
         }
         if (tid == 0) {
-            if (A.part_hard) {
-                A.part_hard[blockIdx.x] = h;
-                A.part_p2[blockIdx.x] = q;
-            } else {
-                pc_atomic_add128(&Q.sums->hard_local, h);
-                pc_atomic_add128(&Q.sums->p2_local, q);
-            }
+            pc_atomic_add128(&Q.sums->hard_local, h);
+            pc_atomic_add128(&Q.sums->p2_local, q);
         }
     }
 }
@@ -1294,7 +1284,8 @@ hipError_t pc_launch_sieve_tiny(const pc_tables &T, const pc_query &Q, hipStream
 // carry[s][col] = carry_in[col] + sum_{s' < s} cnt[s'][col], over the rows
 // that store the column (a prefix of the window's rows: row lengths never
 // grow).  Workgroups take tickets in order; ticket t is block t - blkoff[k]
-// of chunk k (256 columns by rows_per_chunk rows).  A workgroup publishes
+// of chunk k: 256 columns by rows_per_chunk rows, or, the last block of a
+// chunk, the P2 column (cntP, wP) of its rows.  A workgroup publishes
 // its column sums and looks back through earlier chunks until one has
 // published an inclusive prefix (decoupled look-back); a column stored in a
 // chunk's first row is stored in every earlier chunk, so every look-back
@@ -1314,8 +1305,81 @@ hipError_t pc_launch_sieve_tiny(const pc_tables &T, const pc_query &Q, hipStream
 #define LB_P (2ull << 62)
 #define LB_V ((1ull << 62) - 1)
 
+// The ticket's share of the look-back: publish agg (the chunk's sum), return
+// the sum of the earlier chunks, whose words are at index word(jc).
+template <typename F>
+__device__ __forceinline__ uint64_t scan_look_back(const pc_scan_args &A, uint64_t *st,
+                                                   uint32_t rc, uint64_t agg, F word)
+{
+    if (rc == 0) {
+        __hip_atomic_store(st, LB_P | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return 0;
+    }
+    __hip_atomic_store(st, LB_A | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t pre = 0;
+    int64_t jc = (int64_t)rc - 1;
+    uint32_t spins = 0;
+    while (jc >= 0) {
+        const uint64_t v = __hip_atomic_load(A.status + word((uint32_t)jc), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t f = v >> 62;
+        if (f == 0) {
+            if (++spins > (1u << 26)) { // never expected: earlier tickets always run
+                atomicOr(A.err, 1);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            continue;
+        }
+        pre += v & LB_V;
+        if (f == 2)
+            break;
+        jc--;
+    }
+    __hip_atomic_store(st, LB_P | ((pre + agg) & LB_V), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    return pre;
+}
+
+// The P2 column of chunk rc (rows [r0, r0 + nr)): each thread a run of rows.
+template <int MODE>
+__device__ __forceinline__ void scan_p2(const pc_scan_args &A, uint32_t tk, uint32_t rc,
+                                        uint64_t r0, uint32_t nr, uint64_t *s_pre, pc_s128 *scr)
+{
+    uint64_t *const scr64 = reinterpret_cast<uint64_t *>(scr);
+    const uint32_t per = (nr + SCAN_T - 1) / SCAN_T;
+    const uint32_t i0 = min(nr, threadIdx.x * per), i1 = min(nr, i0 + per);
+    uint64_t agg = 0;
+    for (uint32_t i = i0; i < i1; i++)
+        agg += A.cntP[r0 + i];
+    uint64_t tot;
+    uint64_t run = pc_block_excl_scan<SCAN_T>(agg, scr64, &tot);
+    if (threadIdx.x == 0)
+        *s_pre = scan_look_back(A, A.status + (uint64_t)tk * SCAN_T, rc, tot, [&](uint32_t jc) {
+            return (uint64_t)(A.blkoff[jc + 1] - 1) * SCAN_T;
+        });
+    __syncthreads();
+    run += A.carry_in[A.nb] + *s_pre; // the carry at the thread's first row
+    pc_s128 acc = 0;
+    for (uint32_t i = i0; i < i1; i++) {
+        if (MODE == PC_MODE_TALLY)
+            acc += (pc_s128)A.wP[r0 + i] * (pc_s128)run;
+        else
+            A.carryP[r0 + i] = run;
+        run += A.cntP[r0 + i];
+    }
+    if (rc == A.nchunk - 1 && threadIdx.x == 0)
+        A.carry_out[A.nb] = A.carry_in[A.nb] + *s_pre + tot;
+    if (MODE == PC_MODE_TALLY) {
+        acc = pc_block_sum128<SCAN_T>(acc, scr);
+        if (threadIdx.x == 0)
+            pc_atomic_add128(&A.sums->p2_dot, acc);
+    }
+}
+
 template <int MODE> __global__ __launch_bounds__(SCAN_T) void k_scan(pc_scan_args A)
 {
+    __shared__ uint64_t s_pre;
     __shared__ uint32_t s_ticket, s_chunk;
     __shared__ uint64_t s_off[SCAN_RMAX + 1];
     __shared__ pc_s128 scr[SCAN_T / 64];
@@ -1337,6 +1401,10 @@ template <int MODE> __global__ __launch_bounds__(SCAN_T) void k_scan(pc_scan_arg
     const uint32_t cb = tk - A.blkoff[rc];
     const uint64_t r0 = (uint64_t)rc * A.rows_per_chunk;
     const uint32_t nr = (uint32_t)min<uint64_t>(A.rows_per_chunk, A.nrows - r0);
+    if (cb + 1 == A.blkoff[rc + 1] - A.blkoff[rc]) {
+        scan_p2<MODE>(A, tk, rc, r0, nr, &s_pre, scr);
+        return;
+    }
     for (uint32_t i = threadIdx.x; i <= nr; i += SCAN_T)
         s_off[i] = A.row_off[r0 + i];
     __syncthreads();
@@ -1392,34 +1460,10 @@ template <int MODE> __global__ __launch_bounds__(SCAN_T) void k_scan(pc_scan_arg
         }
         // look-back words: one per (ticket, thread); chunk rc - 1 holds this
         // column in its block cb
-        uint64_t *st = A.status + (uint64_t)tk * SCAN_T + threadIdx.x;
-        if (rc == 0) {
-            __hip_atomic_store(st, LB_P | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(st, LB_A | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t jc = (int64_t)rc - 1;
-            uint32_t spins = 0;
-            while (jc >= 0) {
-                const uint64_t w = ((uint64_t)A.blkoff[jc] + cb) * SCAN_T + threadIdx.x;
-                const uint64_t v =
-                    __hip_atomic_load(A.status + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t f = v >> 62;
-                if (f == 0) {
-                    if (++spins > (1u << 26)) { // never expected: earlier tickets always run
-                        atomicOr(A.err, 1);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                    continue;
-                }
-                pre += v & LB_V;
-                if (f == 2)
-                    break;
-                jc--;
-            }
-            __hip_atomic_store(st, LB_P | ((pre + agg) & LB_V), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
+        pre = scan_look_back(A, A.status + (uint64_t)tk * SCAN_T + threadIdx.x, rc, agg,
+                             [&](uint32_t jc) {
+                                 return ((uint64_t)A.blkoff[jc] + cb) * SCAN_T + threadIdx.x;
+                             });
     }
     pc_s128 dh = 0;
     if (act) {
@@ -1440,42 +1484,7 @@ template <int MODE> __global__ __launch_bounds__(SCAN_T) void k_scan(pc_scan_arg
     if (MODE == PC_MODE_TALLY) {
         dh = pc_block_sum128<SCAN_T>(dh, scr);
         if (threadIdx.x == 0)
-            A.part_hard[tk] = dh;
-    }
-}
-
-// The P2 column: carry = carry_in + sum of cntP over the rows above, and
-// sum wP * carry (PC_MODE_TALLY) or every carry (PC_MODE_COUNT); one
-// workgroup, each thread a run of consecutive rows.
-#define SCANP_T 1024
-template <int MODE> __global__ __launch_bounds__(SCANP_T) void k_scan_p2(pc_scan_args A)
-{
-    __shared__ uint64_t scr[SCANP_T / 64];
-    __shared__ pc_s128 scr128[SCANP_T / 64];
-    const uint64_t per = (A.nrows + SCANP_T - 1) / SCANP_T;
-    const uint64_t r0 = min<uint64_t>(A.nrows, threadIdx.x * per), r1 = min(A.nrows, r0 + per);
-    uint64_t agg = 0;
-    for (uint64_t r = r0; r < r1; r++)
-        agg += A.cntP[r];
-    uint64_t tot;
-    uint64_t carry = A.carry_in[A.nb] + pc_block_excl_scan<SCANP_T>(agg, scr, &tot);
-    pc_s128 acc = 0;
-    for (uint64_t r = r0; r < r1; r++) {
-        if (MODE == PC_MODE_TALLY) {
-            const int32_t w = A.wP[r];
-            if (w)
-                acc += (pc_s128)w * (pc_s128)carry;
-        } else {
-            A.carryP[r] = carry;
-        }
-        carry += A.cntP[r];
-    }
-    if (threadIdx.x == 0)
-        A.carry_out[A.nb] = A.carry_in[A.nb] + tot;
-    if (MODE == PC_MODE_TALLY) {
-        acc = pc_block_sum128<SCANP_T>(acc, scr128);
-        if (threadIdx.x == 0)
-            *A.part_p2 = acc;
+            pc_atomic_add128(&A.sums->hard_dot, dh);
     }
 }
 
@@ -1486,15 +1495,10 @@ hipError_t pc_launch_scan(const pc_scan_args &A, int mode, hipStream_t s)
     if (A.rows_per_chunk == 0 || A.rows_per_chunk > SCAN_RMAX ||
         (uint64_t)A.nchunk * A.rows_per_chunk < A.nrows)
         return hipErrorInvalidValue;
-    if (mode == PC_MODE_TALLY) {
-        if (A.nticket)
-            k_scan<PC_MODE_TALLY><<<A.nticket, SCAN_T, 0, s>>>(A);
-        k_scan_p2<PC_MODE_TALLY><<<1, SCANP_T, 0, s>>>(A);
-    } else {
-        if (A.nticket)
-            k_scan<PC_MODE_COUNT><<<A.nticket, SCAN_T, 0, s>>>(A);
-        k_scan_p2<PC_MODE_COUNT><<<1, SCANP_T, 0, s>>>(A);
-    }
+    if (mode == PC_MODE_TALLY)
+        k_scan<PC_MODE_TALLY><<<A.nticket, SCAN_T, 0, s>>>(A);
+    else
+        k_scan<PC_MODE_COUNT><<<A.nticket, SCAN_T, 0, s>>>(A);
     return hipGetLastError();
 }
 

@@ -225,12 +225,6 @@ static hipError_t scan_excl(T *data, uint64_t n, T *tmp, T *total, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t pc_launch_scan_u64(uint64_t *data, uint64_t n, uint64_t *tmp, uint64_t *total,
-                              hipStream_t s)
-{
-    return scan_excl<uint64_t>(data, n, tmp, total, s);
-}
-
 // tab[e].y = number of odd primes in entries < e; primes[] filled in order,
 // the primes of entries e >= 2^26 (above 2^32) into primes_hi[k - k32], k32
 // the index of the first of them.
