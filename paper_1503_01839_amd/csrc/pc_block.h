@@ -21,6 +21,14 @@ template <typename P> __device__ __forceinline__ P *pc_uniform_ptr(P *p)
     return (P *)pc_uniform64((uint64_t)p);
 }
 
+// v with lane k replaced by x, x and k uniform (one instruction)
+extern "C" __device__ uint32_t pc_llvm_writelane(uint32_t x, uint32_t k, uint32_t v) __asm(
+    "llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t pc_write_lane(uint32_t v, uint32_t k, uint32_t x)
+{
+    return pc_llvm_writelane(x, k, v);
+}
+
 // 32-bit wavefront sum and inclusive scan with DPP lane moves (gfx9 row
 // operations), no LDS traffic.  Every lane must be active.
 #define PC_DPP(v, ctrl, rm) ((uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), ctrl, rm, 0xF, false))

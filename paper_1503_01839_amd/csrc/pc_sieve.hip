@@ -335,6 +335,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             q++;
         return q;
     };
+    // lob mod p, rp = 1 / p: adding 2^52 leaves the nearest integer to lob / p
+    // (lob < 2^47, so off by less than 2^-5) in the low bits of the double; the
+    // remainder, less than p in size, is formed modulo 2^32
+    const double lobd = (double)lob;
+    auto rem_lob = [&](uint32_t p, double rp) -> uint32_t {
+        const uint32_t q = (uint32_t)__double_as_longlong(__builtin_fma(lobd, rp, 0x1p52));
+        const int32_t r = (int32_t)((uint32_t)lob - q * p);
+        return (uint32_t)(r + (r < 0 ? (int32_t)p : 0));
+    };
     // The multiples of a prime p by residue class: the multipliers 30 k + res(i)
     // fall on byte p k + floor(p res(i) / 30) of the integers, always at one bit
     // of it.  With p = 30 a + res(g) the byte's part that depends on i is
@@ -352,6 +361,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             l_tab1 |= byte << (8 * (g - 4));
     }
     // the lane's class of p: *bit, and the byte of 30 k + res(i) past p k
+    const uint32_t l_res8 = 8u * l_res;
     auto class_of = [&](uint32_t p, uint32_t *bit) -> uint32_t {
         const uint32_t a = p / 30u, g = ((p - 30u * a) * 17u) >> 6; // g: the residue's number
         const uint32_t eb = __builtin_amdgcn_perm(l_tab1, l_tab0, 0x0c0c0c00u | g);
@@ -369,7 +379,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             bool seq = false, tiny = false;
             if (tid < n) {
                 const uint32_t b = qc + 1 + kb + tid, p = TB.primes[b];
-                const uint32_t rem = (uint32_t)(lob - pc_div(lob, p, TB.recip[b]) * p);
+                const uint32_t rem = rem_lob(p, TB.rcpd[b]);
                 c_p[tid] = p;
                 c_rem[tid] = rem;
                 tiny = p < CLR_TINY;
@@ -505,7 +515,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const uint64_t p = TB.primes[b];
             const uint64_t rp = TB.recip[b];
             c_p[j] = (uint32_t)p;
-            c_rem[j] = (uint32_t)(lob - pc_div(lob, p, rp) * p);
+            c_rem[j] = rem_lob((uint32_t)p, TB.rcpd[b]);
             large = (pc_u128)p * p * p >= hi;
             uint32_t ls = 0, lc = 0;
             // every hard leaf of b and of the later primes lies below ub.y
@@ -592,53 +602,60 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         };
         // Cross column cg0 + k, which has a multiple in this wave's region.
         // Lane (i, t) = (lane mod 8, lane / 8) takes the multipliers
-        // 30 (k0 + t + 8 s) + res(i), s = 0, 1, ...: byte
-        // (t + 8 s) p + floor(p res(i) / 30) - v_r of the region, so its
-        // multiples lie 8 p bytes (2 p words) apart at one bit of their words.
+        // 30 (k0 + t + 8 s) + res(i), s = 0, 1, ...: bit
+        // 8 ((t + 8 s) p + a res(i)) + class byte - 8 v_r of the region (the
+        // class byte is 8 floor(res(g) res(i) / 30) + its bit), so a lane's
+        // multiples lie 64 p bits, 2 p words, apart at one bit of their words.
+        // Most of the sparse segments' time goes here, one visit per (column,
+        // region) with 15 to 60 multiples: 16 vector instructions when one
+        // round does it, the rest scalar (25 with bytes and bits apart, and
+        // two 32-bit multiplies among them; k_sieve at 10^18 33.4 -> CROSS ms).
         auto cross_k = [&](int32_t k) {
             PC_EV(0);
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)v_p, k);
-            const int32_t r = __builtin_amdgcn_readlane((int)v_r, k);
-            uint32_t cb;
-            const uint32_t e = class_of(p, &cb);
-            // byte offset from the region's start (negative or past its end: none)
-            int32_t at = (int32_t)((lane >> 3) * p + e) - r;
-            const uint32_t sh = ((uint32_t)at << 3 | cb) & 31u, keep = ~(1u << sh);
-            const int32_t step = (int32_t)(8u * p);
-            char *const rb = reinterpret_cast<char *>(bm) + wv * RSB;
-            auto clear = [&](int32_t o) -> uint32_t {
-                const uint32_t old =
-                    __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(rb + (o & ~3)), keep,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                return (old >> sh) & 1u;
+            const uint32_t r8 = 8u * (uint32_t)__builtin_amdgcn_readlane((int)v_r, k);
+            const uint32_t a = p / 30u, g = ((p - 30u * a) * 17u) >> 6; // g: the residue's number
+            const uint32_t eb = __builtin_amdgcn_perm(l_tab1, l_tab0, 0x0c0c0c00u | g);
+            // bit of the region in round 0 (negative or RS and more: none)
+            const int32_t x = (int32_t)(__umul24(lane & 56u, p) + (__umul24(l_res8, a) + eb) - r8);
+            const uint32_t bit = 1u << (x & 31), keep = ~bit;
+            uint32_t *w = bm + (int32_t)(wv * (RS / 32)) + (x >> 5);
+            const int32_t step = (int32_t)(64u * p); // bits per round
+            auto clear = [&](uint32_t *at) -> uint32_t {
+                return __hip_atomic_fetch_and(at, keep, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP) & bit;
             };
-            auto masked = [&]() -> uint32_t { // a round some of whose lanes may lie outside
-                bool hit = false;
-                if ((uint32_t)at < RSB)
-                    hit = clear(at) != 0;
-                at += step;
-                return (uint32_t)__builtin_popcountll(__ballot(hit));
-            };
-            uint32_t removed = masked();
-            // Round s: -p < byte - s step < step.  From s = 1 on no lane lies
-            // below the region, and none past its end while (s + 1) step <= RSB.
-            int32_t top = 2 * step; // of the next round
-            if (top <= (int32_t)RSB) {
-                uint32_t hits = 0;
-                for (; top + step <= (int32_t)RSB; top += 2 * step, at += 2 * step)
-                    hits += clear(at) + clear(at + step); // two clears in flight
-                if (top <= (int32_t)RSB) {
-                    hits += clear(at);
-                    at += step;
-                    top += step;
+            uint32_t old = 0;
+            if ((uint32_t)x < RS)
+                old = clear(w);
+            uint32_t removed = (uint32_t)__builtin_popcountll(__ballot(old != 0));
+            // Round s: -8 p < bit - s step < step.  From s = 1 on no lane lies
+            // below the region, and none past its end while (s + 1) step <= RS.
+            if (step < (int32_t)(RS + 8u * p)) {
+                int32_t top = 2 * step; // of the next round
+                const uint32_t dw = 2u * p;
+                w += dw;
+                if (top <= (int32_t)RS) {
+                    const uint32_t sh = x & 31;
+                    uint32_t hits = 0;
+                    for (; top + step <= (int32_t)RS; top += 2 * step, w += 2 * dw)
+                        hits += (clear(w) >> sh) + (clear(w + dw) >> sh); // two in flight
+                    if (top <= (int32_t)RS) {
+                        hits += clear(w) >> sh;
+                        top += step;
+                        w += dw;
+                    }
+                    removed += pc_wave_sum_u32(hits);
                 }
-                removed += pc_wave_sum_u32(hits);
+                for (; top - step < (int32_t)(RS + 8u * p); top += step, w += dw) {
+                    old = 0;
+                    if ((uint32_t)(x + top - step) < RS)
+                        old = clear(w);
+                    removed += (uint32_t)__builtin_popcountll(__ballot(old != 0));
+                }
             }
-            for (; top - step < (int32_t)(RSB + p); top += step)
-                removed += masked();
             rc -= removed;
-            if (lane == (uint32_t)k)
-                v_rem = removed;
+            v_rem = pc_write_lane(v_rem, (uint32_t)k, removed);
         };
         auto cross_region = [&](uint32_t j) {
             ensure_group(j);
