@@ -29,11 +29,9 @@ __global__ __launch_bounds__(BT) void k_s1_b(pc_tables T, const pc_query *Qs, pc
     uint32_t q, lb, nlb;
     pc_blk_of(B, &q, &lb, &nlb);
     const pc_query &Q = Qs[q];
-    const uint32_t pcc = T.primes[Q.c];
     pc_s128 acc = 0;
-    unsigned long long terms = 0;
-    for (uint64_t n = 1 + (uint64_t)lb * BT + threadIdx.x; n <= Q.y; n += (uint64_t)nlb * BT)
-        terms += pc_s1_item(T, Q, pcc, n, &acc);
+    unsigned long long terms =
+        pc_s1_items(T, Q, (uint64_t)lb * BT + threadIdx.x, (uint64_t)nlb * BT, &acc);
     acc = pc_block_sum128<BT>(acc, scr);
     terms = pc_block_sum<BT>(terms, scr64);
     if (threadIdx.x == 0) {

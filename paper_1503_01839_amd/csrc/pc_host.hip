@@ -116,8 +116,9 @@ struct Tables {
     uint64_t k32 = ~0ull;  // index of the first prime above 2^32 (in primes_hi), if covered
     DevBuf recip, rcpd;
     uint64_t recip_n = 0;
-    DevBuf mulpf;
+    DevBuf mulpf, mulpfw;
     uint64_t y_limit = 0;
+    uint64_t w_limit = 0; // mulpfw covers the m <= w_limit prime to 2 .. 13
     DevBuf pattern[kWheelC + 1], phitab[kWheelC + 1], wres[kWheelC + 1];
     bool wheel_ok[kWheelC + 1] = {};
     uint32_t pattern_bits[kWheelC + 1] = {}, Qc[kWheelC + 1] = {}, phiQ[kWheelC + 1] = {};
@@ -479,14 +480,32 @@ pc_tables tables_view(uint32_t c)
     v.rcpd = ptr<double>(T.rcpd);
     v.pitab = ptr<uint2>(T.pitab);
     v.mulpf = ptr<int32_t>(T.mulpf);
+    v.mulpfw = ptr<int32_t>(T.mulpfw);
     v.pattern = ptr<uint32_t>(T.pattern[c]);
     v.phitab = ptr<uint32_t>(T.phitab[c]);
     v.wres = ptr<uint32_t>(T.wres[c]);
     v.pattern_bits = T.pattern_bits[c];
     v.Qc = T.Qc[c];
     v.phiQ = T.phiQ[c];
-    v.rphiQ = 1.0f / (float)T.phiQ[c];
     return v;
+}
+
+// mu*lpf in the wheel's order up to y (after ensure_mulpf(y)).
+void ensure_mulpfw(uint64_t y)
+{
+    Tables &T = g_T;
+    if (T.w_limit >= y)
+        return;
+    ensure_wheel(kWheelC);
+    const uint64_t Y = T.y_limit;
+    // the integers <= Y prime to 2 .. 13: whole periods, then the residues
+    uint64_t n = Y / T.Qc[kWheelC] * T.phiQ[kWheelC];
+    for (uint64_t r = 1; r <= Y % T.Qc[kWheelC]; r++)
+        n += r % 2 && r % 3 && r % 5 && r % 7 && r % 11 && r % 13;
+    ensure(T.mulpfw, n * 4, "mu*lpf table by the wheel");
+    hipck(pc_launch_mulpfw(tables_view(kWheelC), n, ptr<int32_t>(T.mulpfw), g_stream),
+          "mu*lpf table by the wheel");
+    T.w_limit = Y;
 }
 
 // Marks every table unbuilt, so that the next call that needs one builds it
@@ -499,7 +518,7 @@ void drop_tables(bool release)
     if (release) {
         DevBuf *all[] = {&T.base, &T.nbase_d, &T.pitab, &T.primes, &T.primes_hi, &T.cnt_tmp,
                          &T.scan_tmp, &T.recip,
-                         &T.rcpd, &T.mulpf, &T.lk_in, &T.lk_out, &T.chk};
+                         &T.rcpd, &T.mulpf, &T.mulpfw, &T.lk_in, &T.lk_out, &T.chk};
         for (DevBuf *b : all)
             dfree(*b);
         for (int c = 0; c <= kWheelC; c++) {
@@ -521,7 +540,7 @@ void drop_tables(bool release)
     for (int c = 0; c <= kWheelC; c++)
         T.wheel_ok[c] = false;
     T.base_ok = false;
-    T.pi_limit = T.nprimes = T.recip_n = T.y_limit = 0;
+    T.pi_limit = T.nprimes = T.recip_n = T.y_limit = T.w_limit = 0;
     T.k32 = ~0ull;
     T.pi_host_max = 0;
 }
@@ -793,6 +812,8 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     ensure_mulpf(y);
     ensure_recip(a + 1);
     ensure_wheel(c);
+    if (c == kWheelC)
+        ensure_mulpfw(y);
     hipck(hipStreamSynchronize(g_stream), "sync");
     const double ms_tables = ms_since(t0);
 
@@ -1794,6 +1815,7 @@ std::vector<BatchQuery> plan_queries(const uint64_t *xs, size_t n, double alpha,
         ensure_mulpf(Y.ymax);
         ensure_recip(amax + 1);
         ensure_wheel(kWheelC);
+        ensure_mulpfw(Y.ymax);
         hipck(hipStreamSynchronize(g_stream), "sync");
     }
     return big;
@@ -2057,7 +2079,7 @@ void run_batch_noalloc(const uint64_t *d_xs, size_t n, uint64_t *d_out, hipStrea
     hipck(hipMemcpyAsync(xs.data(), d_xs, n * 8, hipMemcpyDeviceToHost, st), "D2H");
     hipck(hipStreamSynchronize(st), "hipStreamSynchronize");
     const QueryYs Y = query_ys(xs.data(), n, 0.0);
-    if (T.pi_limit < std::max<uint64_t>(Y.need, 1024) + 1 || T.y_limit < Y.ymax)
+    if (T.pi_limit < std::max<uint64_t>(Y.need, 1024) + 1 || T.w_limit < Y.ymax)
         fail(PC_ERANGE, "the device tables do not cover these queries: call "
                         "pc_workspace_bytes (or any batch) with them first");
     // pi at the planning points, staged in the scratch array

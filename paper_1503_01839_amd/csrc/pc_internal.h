@@ -27,6 +27,7 @@ struct pc_tables {
     const double *rcpd;     // rcpd[k] = 1/p_k correctly rounded, k <= n_recip
     const uint2 *pitab;     // pi table, see pc_pi_lookup
     const int32_t *mulpf;   // mu(n)*lpf(n) for n <= ymax; INT32_MAX at n = 1; 0 if mu = 0
+    const int32_t *mulpfw;  // the same of the k-th integer prime to 2 .. 13 (pc_wheel_m), in order
     const uint32_t *pattern; // pre-sieve bits for p_4..p_c (8 bits per 30 integers), period
                             // pattern_bits (+64 bits)
     const uint32_t *phitab; // phi(r, c) for r < Q_c
@@ -34,7 +35,6 @@ struct pc_tables {
     uint32_t pattern_bits;  // 8 prod_{4 <= i <= c} p_i
     uint32_t Qc;            // prod_{1 <= i <= c} p_i
     uint32_t phiQ;          // phi(Q_c, c)
-    float rphiQ;            // 1 / phi(Q_c, c)
 };
 
 struct pc_sums;
@@ -161,6 +161,7 @@ hipError_t pc_launch_recip(const uint32_t *primes, uint64_t *recip, double *rcpd
                            hipStream_t s);
 hipError_t pc_launch_mulpf(const uint32_t *primes, uint32_t nsmall, uint64_t ymax,
                            int32_t *mulpf, hipStream_t s);
+hipError_t pc_launch_mulpfw(const pc_tables &T, uint64_t n, int32_t *mulpfw, hipStream_t s);
 hipError_t pc_launch_count_nonzero(const int32_t *a, uint64_t n, unsigned long long *out,
                                    hipStream_t s);
 hipError_t pc_launch_wheel(uint32_t c, const uint32_t *primes, uint32_t *pattern,

@@ -12,18 +12,16 @@
 // p_1..p_c (lpf(m) > p_b > p_c implies it), numbered from 0 in increasing
 // order: candidate k is Q_c (k / phi(Q_c)) + wres[k mod phi(Q_c)], and the
 // candidates up to m number phi(m, c) = phi(Q_c) (m / Q_c) + phitab[m mod Q_c].
+// There are none unless c = 6 (with a <= 6 primes up to y, c = a and no b lies
+// between), so the wheel's numbers are constants, and the table of mu lpf is
+// kept in their order too: 64 candidates read 256 bytes in a row (of the table
+// by m they read five times the lines), and m is formed for those that pass.
+#define PC_WHEEL_Q 30030u
+#define PC_WHEEL_PHI 5760u
 __device__ __forceinline__ uint32_t pc_wheel_m(const pc_tables &T, uint32_t k)
 {
-    uint32_t q = (uint32_t)((float)k * T.rphiQ); // within one of k / phi(Q_c) (k < 2^24 phi(Q_c))
-    int32_t r = (int32_t)(k - q * T.phiQ);
-    if (r < 0) {
-        q--;
-        r += (int32_t)T.phiQ;
-    } else if (r >= (int32_t)T.phiQ) {
-        q++;
-        r -= (int32_t)T.phiQ;
-    }
-    return q * T.Qc + T.wres[r];
+    const uint32_t q = k / PC_WHEEL_PHI;
+    return q * PC_WHEEL_Q + T.wres[k - q * PC_WHEEL_PHI];
 }
 
 __device__ __forceinline__ uint64_t pc_wheel_count(const pc_tables &T, const pc_query &Q, uint64_t m)

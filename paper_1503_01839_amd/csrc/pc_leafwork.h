@@ -38,15 +38,11 @@ __device__ __forceinline__ pc_xv pc_xb_item(const pc_tables &T, const pc_query &
     return X;
 }
 
-// The S1 term of n (pcc = p_c): adds mu(n) phi(x/n, c) to *acc when n <= y is
-// squarefree with lpf(n) > p_c, and returns whether it did.
-__device__ __forceinline__ bool pc_s1_item(const pc_tables &T, const pc_query &Q, uint32_t pcc,
-                                           uint64_t n, pc_s128 *acc)
+// The S1 term mu(n) phi(x/n, c) of a squarefree n <= y with lpf(n) > p_c; v =
+// mu(n) lpf(n).
+__device__ __forceinline__ pc_s128 pc_s1_term(const pc_tables &T, const pc_query &Q, uint64_t n,
+                                              int32_t v)
 {
-    const int32_t v = T.mulpf[n];
-    const uint32_t l = v < 0 ? (uint32_t)(-v) : (uint32_t)v;
-    if (v == 0 || l <= pcc) // mu(n) = 0, or n has a prime factor <= p_c
-        return false;
     pc_s128 phi;
     if (!Q.x_hi) {
         const uint64_t u = pc_div_any(Q.x, (uint32_t)n);
@@ -59,8 +55,37 @@ __device__ __forceinline__ bool pc_s1_item(const pc_tables &T, const pc_query &Q
         const uint64_t qq = pc_div_wide32(uh, ul, (uint32_t)Q.Qc, &r); // uh < Q_c: x <= 2^72
         phi = (pc_s128)qq * T.phiQ + T.phitab[r];
     }
-    *acc += v > 0 ? phi : -phi;
-    return true;
+    return v > 0 ? phi : -phi;
+}
+
+// S1 over the items i0, i0 + stride, ...: adds to *acc, returns the terms.
+// With the whole wheel the n are the integers prime to p_1..p_6 (every one
+// squarefree counts), a fifth of all; a smaller wheel belongs to y < 13.
+__device__ __forceinline__ unsigned long long pc_s1_items(const pc_tables &T, const pc_query &Q,
+                                                          uint64_t i0, uint64_t stride,
+                                                          pc_s128 *acc)
+{
+    unsigned long long terms = 0;
+    if (Q.c == 6) {
+        const uint64_t n = pc_wheel_count(T, Q, Q.y);
+        for (uint64_t k = i0; k < n; k += stride) {
+            const int32_t v = T.mulpfw[k];
+            if (v != 0) {
+                *acc += pc_s1_term(T, Q, pc_wheel_m(T, (uint32_t)k), v);
+                terms++;
+            }
+        }
+    } else {
+        const uint32_t pcc = T.primes[Q.c];
+        for (uint64_t n = 1 + i0; n <= Q.y; n += stride) {
+            const int32_t v = T.mulpf[n];
+            if (v != 0 && (uint32_t)(v < 0 ? -v : v) > pcc) {
+                *acc += pc_s1_term(T, Q, n, v);
+                terms++;
+            }
+        }
+    }
+    return terms;
 }
 
 // pi(floor(X / p)), X in fp64 and its low word, rp = 1 / p, quotient < 2^31.
@@ -427,7 +452,7 @@ __device__ __forceinline__ void pc_easy_primes(const pc_tables &T, const pc_quer
 // once, against the b of the band.  (One item per (b, m), the table tested for
 // each, took 6.3 ms of one pi(10^18); this takes 3.4 ms beside the prime leaves.)
 template <int NT> struct pc_cand_lds {
-    uint32_t m[PC_EZ_TILE]; // m | (mu(m) > 0) << 31
+    uint32_t m[PC_EZ_TILE]; // m's wheel number | (mu(m) > 0) << 31
     uint32_t l[PC_EZ_TILE]; // lpf(m)
     uint32_t n;
 };
@@ -439,6 +464,7 @@ __device__ __forceinline__ void pc_easy_cands(const pc_tables &T, const pc_query
     const uint32_t nband = Q.a / PC_EZ_BAND + 1, lane = pc_lane();
     const uint64_t *const boff = Q.e_boff + nband;
     const uint64_t U = Q.e_total[1];
+    const uint32_t kend = (uint32_t)pc_wheel_count(T, Q, Q.y); // wheel numbers of m <= y
     for (uint64_t u = lb; u < U; u += nlb) {
         const uint32_t g = pc_uniform(pc_band_of(boff, nband, u));
         const uint32_t b0 = max(g * PC_EZ_BAND, Q.c + 1), b1 = min(g * PC_EZ_BAND + PC_EZ_BAND, Q.a);
@@ -450,8 +476,8 @@ __device__ __forceinline__ void pc_easy_cands(const pc_tables &T, const pc_query
         __syncthreads();
 #pragma unroll 4
         for (uint32_t i = 0; i < PC_EZ_TILE / NT; i++) {
-            const uint32_t m = pc_wheel_m(T, k0 + i * NT + threadIdx.x);
-            const int32_t v = m <= (uint32_t)Q.y ? T.mulpf[m] : 0;
+            const uint32_t k = k0 + i * NT + threadIdx.x;
+            const int32_t v = k < kend ? T.mulpfw[k] : 0;
             const uint32_t l = v < 0 ? (uint32_t)(-v) : (uint32_t)v;
             const bool keep = l > p0;
             const uint64_t bal = __ballot(keep);
@@ -460,7 +486,7 @@ __device__ __forceinline__ void pc_easy_cands(const pc_tables &T, const pc_query
                 at = atomicAdd(&L.n, (uint32_t)__builtin_popcountll(bal));
             at = pc_uniform(at) + (uint32_t)__builtin_popcountll(bal & ((1ull << lane) - 1));
             if (keep) {
-                L.m[at] = m | (v > 0 ? 0x80000000u : 0u);
+                L.m[at] = k | (v > 0 ? 0x80000000u : 0u);
                 L.l[at] = l;
             }
         }
@@ -468,8 +494,8 @@ __device__ __forceinline__ void pc_easy_cands(const pc_tables &T, const pc_query
         const uint32_t n = L.n;
         for (uint32_t i = threadIdx.x; (i & ~63u) < n; i += NT) {
             const bool have = i < n;
-            const uint32_t e = have ? L.m[i] : 1u, l = have ? L.l[i] : 0u;
-            const uint32_t m = e & 0x7FFFFFFFu;
+            const uint32_t e = have ? L.m[i] : 0u, l = have ? L.l[i] : 0u;
+            const uint32_t m = pc_wheel_m(T, e & 0x7FFFFFFFu);
             const double rm = pc_rcp_f64(m);
             int64_t s = 0;
             uint32_t cnt = 0;

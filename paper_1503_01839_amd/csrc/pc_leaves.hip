@@ -6,18 +6,15 @@
 #define LV_T 256
 
 // ---------------------------------------------------------------------------
-// S1: one lane per n <= y (grid-stride).
+// S1: one lane per item (grid-stride).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(LV_T) void k_s1(pc_tables T, pc_query Q)
 {
     __shared__ pc_s128 scr[LV_T / 64];
     __shared__ unsigned long long scr64[LV_T / 64];
-    const uint32_t pcc = T.primes[Q.c];
     pc_s128 acc = 0;
-    unsigned long long terms = 0;
-    const uint64_t stride = (uint64_t)gridDim.x * LV_T;
-    for (uint64_t n = 1 + (uint64_t)blockIdx.x * LV_T + threadIdx.x; n <= Q.y; n += stride)
-        terms += pc_s1_item(T, Q, pcc, n, &acc);
+    unsigned long long terms =
+        pc_s1_items(T, Q, (uint64_t)blockIdx.x * LV_T + threadIdx.x, (uint64_t)gridDim.x * LV_T, &acc);
     acc = pc_block_sum128<LV_T>(acc, scr);
     terms = pc_block_sum<LV_T>(terms, scr64);
     if (threadIdx.x == 0) {

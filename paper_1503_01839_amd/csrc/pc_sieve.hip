@@ -309,13 +309,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     uint32_t *const preq = gbuf + GCAP - T;
     auto build_preq = [&]() {
         uint32_t pq;
-        const uint32_t s = block_counts_q(&pq);
-        uint32_t tot;
-        const uint32_t ex = pc_block_excl_scan<T>(s, scr32, &tot);
+        const uint32_t n = block_counts_q(&pq), inc = pc_wave_incl_scan_u32(n);
+        const uint32_t w = tid >> 6;
+        if (lane == 63)
+            scr32[w] = inc;
+        __syncthreads(); // every wave is past what it read of pre, gbuf and scr32 before
+        uint32_t ex = inc - n;
+#pragma unroll
+        for (uint32_t i = 0; i < NWV; i++)
+            ex += i < w ? scr32[i] : 0u;
         pre[tid] = ex;
         preq[tid] = pq;
         if (tid == T - 1)
-            pre[T] = tot;
+            pre[T] = ex + n;
         __syncthreads();
     };
     // unsieved integers among bits [0, q), q <= S, against build_preq
@@ -467,11 +473,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     auto leaf_filter = [&](uint32_t j, uint32_t it, uint32_t *m, int32_t *w) -> bool {
         const uint32_t lc = c_lc[j], ls = c_ls[j];
         if (lc & PC_CAND) {
-            const uint32_t mc = pc_wheel_m(TB, ls + it);
-            const int32_t v = TB.mulpf[mc];
+            const int32_t v = TB.mulpfw[ls + it];
             const uint32_t av = v < 0 ? (uint32_t)(-v) : (uint32_t)v;
             n_cand++;
-            *m = mc;
+            *m = pc_wheel_m(TB, ls + it);
             *w = v > 0 ? -1 : 1;
             return av > c_p[j];
         }
@@ -487,15 +492,18 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // decides (an IEEE division with a 64-bit remainder takes five times the
     // instructions).
     const double qbase = 0.25 - (double)lo;
-    auto leaf_q = [&](uint32_t X, double Xd, uint32_t m, bool *ok) -> uint32_t {
+    // *bad collects quotients outside the segment (never, if the m range is
+    // right; leaf_check flags them), which are taken as its last bit here.
+    auto leaf_q = [&](uint32_t X, double Xd, uint32_t m, uint32_t *bad) -> uint32_t {
         const double t = __builtin_fma(Xd, pc_rcp_f64(m), qbase); // u - lo, raised
         uint32_t off = (uint32_t)(int32_t)t;
-        if ((int32_t)(X - ((uint32_t)lo + off) * m) < 0)
-            off--;
-        *ok = t > -1.0 && off < SPAN;
-        if (!*ok) // cannot happen if the m range is right
+        off += (uint32_t)((int32_t)(X - ((uint32_t)lo + off) * m) >> 31);
+        *bad |= off >= SPAN || !(t > -1.0) ? 1u : 0u;
+        return pc_w30_le(min(off, SPAN - 1));
+    };
+    auto leaf_check = [&](uint32_t bad) {
+        if (bad)
             atomicOr(A.err, 2);
-        return *ok ? pc_w30_le(off) : 0u;
     };
 
     const uint32_t ncross = min(col_hi, Q.nb);
@@ -827,7 +835,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         // the window from the leafy light column j0 on; returns its end
         auto gather = [&](uint32_t j0) -> uint32_t {
             PC_PH(4);
-            __syncthreads(); // every wave is past the last window's leaves
             PC_EV(2);
             g_par ^= 1;
             // the next heavy column at or after j0 ends the window
@@ -858,7 +865,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             uint32_t *const bins = g_bin + g_par * 64;
             if (tid < 64)
                 g_bin[(g_par ^ 1) * 64 + tid] = 0; // the next window's
-            uint32_t ee[SPT], bn[SPT], rk[SPT];
+            uint32_t ee[SPT], bn[SPT], rk[SPT], bad = 0;
 #pragma unroll
             for (uint32_t i = 0; i < SPT; i++) {
                 ee[i] = 0;
@@ -882,15 +889,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     uint32_t m;
                     int32_t w;
                     if (leaf_filter(a, s - oa, &m, &w)) {
-                        bool ok;
-                        const uint32_t q = leaf_q((uint32_t)Xb1[cb + a], Xd1[cb + a], m, &ok);
-                        if (ok) {
-                            ee[i] = ((a - j0) & 63u) << 22 | (q << 2) | (w < 0 ? 2u : 0u) | 1u;
-                            bn[i] = ((a - j0) >> 6) * NWV + min(q >> RSL, NWV - 1);
-                            rk[i] = atomicAdd(&bins[bn[i]], 1u);
-                            wl = w;
-                            nleaf++;
-                        }
+                        const uint32_t q = leaf_q((uint32_t)Xb1[cb + a], Xd1[cb + a], m, &bad);
+                        ee[i] = ((a - j0) & 63u) << 22 | (q << 2) | (w < 0 ? 2u : 0u) | 1u;
+                        bn[i] = ((a - j0) >> 6) * NWV + min(q >> RSL, NWV - 1);
+                        rk[i] = atomicAdd(&bins[bn[i]], 1u);
+                        wl = w;
+                        nleaf++;
                     }
                 }
                 // The wave's slots are consecutive, so its lanes hold runs of one
@@ -906,7 +910,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 if (tail && key != 0xFFFFu && run != 0)
                     atomicAdd(&c_w[key], run);
             }
-            __syncthreads();
+            leaf_check(bad);
+            __syncthreads(); // (and every wave is past the last window's leaves)
             const uint32_t n = bins[lane], inc = pc_wave_incl_scan_u32(n);
             v_bin = inc - n;
             w_used = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
@@ -942,91 +947,75 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 }
             }
         };
-        // Many leaves: the whole workgroup answers them against pre[].  Prime
-        // items are all leaves (each thread loads HU of them before it divides);
-        // each wave filters its own candidates, HU * 64 loads at a time, and
-        // packs the survivors into its 64 slots of gbuf, so the divisions and
-        // counts run on full wavefronts without workgroup barriers.
+        // Many leaves: the whole workgroup answers them against pre[].  A wave
+        // takes 64 items at a time, wave wv the pieces wv, wv + NWV, ..., each
+        // next piece's table reads in flight while one is worked off (the first
+        // one's while the counts are built).  Prime items are all leaves; the
+        // candidates that pass the table's test are packed into the wave's 64
+        // slots of gbuf, so that the divisions and counts run on full
+        // wavefronts.  Three barriers a column: a wave counts only words of its
+        // own region, so it need not wait for the others' crossings first.
         auto heavy_col = [&](uint32_t j) {
-            constexpr uint32_t HU = 2;
             PC_PH(4);
-            __syncthreads(); // every wave has crossed the columns before j
-            build_preq();
-            const uint32_t lc = c_lc[j], n = lc & ~PC_CAND, ls = c_ls[j];
+            const uint32_t lc = c_lc[j], n = lc & ~PC_CAND, ls = pc_uniform(c_ls[j]);
+            const bool cand = pc_uniform(lc) & PC_CAND;
+            const uint32_t p = c_p[j];
+            const uint32_t *const src =
+                (cand ? reinterpret_cast<const uint32_t *>(TB.mulpfw) : TB.primes) + ls;
             const uint32_t X = pc_uniform((uint32_t)Xb1[cb + j]);
             const double Xd = __longlong_as_double(
                 (long long)pc_uniform64((uint64_t)__double_as_longlong(Xd1[cb + j])));
+            uint32_t next = tid < n ? src[tid] : 0u;
+            build_preq();
             int32_t wsum = 0;
             int64_t lsum = 0;
-            auto one = [&](uint32_t m, int32_t w) {
-                bool ok;
-                const uint32_t q = leaf_q(X, Xd, m, &ok);
-                if (ok) {
-                    lsum += (int64_t)w * (int64_t)count_preq(q);
+            uint32_t bad = 0;
+            uint32_t *const slot = gbuf + wv * 64; // wheel number | (mu(m) > 0) << 31
+            uint32_t held = 0;                     // filled slots (uniform)
+            for (uint32_t base = wv * 64;; base += T) {
+                const bool more = base < n; // (uniform)
+                const uint32_t it = base + lane, v = next;
+                next = it + T < n ? src[it + T] : 0u;
+                uint32_t m = v;
+                int32_t w = 1;
+                bool have = it < n;
+                if (cand) {
+                    // squarefree (v != 0), lpf(m) > p_b
+                    const bool keep = (uint32_t)max((int32_t)v, -(int32_t)v) > p;
+                    const uint64_t bal = __ballot(keep);
+                    const uint32_t at = held + (uint32_t)__builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                    const uint32_t e = (ls + it) | ((int32_t)v > 0 ? 0x80000000u : 0u);
+                    n_cand += have ? 1u : 0u;
+                    if (keep && at < 64)
+                        slot[at] = e;
+                    held += (uint32_t)__builtin_popcountll(bal);
+                    if (held < 64 && more)
+                        continue;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    have = lane < held;
+                    const uint32_t f = have ? slot[lane] : 0u;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    if (keep && at >= 64)
+                        slot[at - 64] = e;
+                    held = held > 64 ? held - 64 : 0u;
+                    m = pc_wheel_m(TB, f & 0x7FFFFFFFu);
+                    w = (f >> 31) ? -1 : 1;
+                }
+                if (have) {
+                    const uint32_t q = leaf_q(X, Xd, m, &bad);
+                    lsum += (int64_t)(w * (int32_t)count_preq(q));
                     wsum += w;
                     nleaf++;
                 }
-            };
-            if (!(lc & PC_CAND)) {
-                for (uint32_t it0 = tid; it0 < n; it0 += HU * T) {
-                    uint32_t mm[HU];
-#pragma unroll
-                    for (uint32_t u = 0; u < HU; u++)
-                        mm[u] = it0 + u * T < n ? TB.primes[ls + it0 + u * T] : 0u;
-#pragma unroll
-                    for (uint32_t u = 0; u < HU; u++)
-                        if (it0 + u * T < n)
-                            one(mm[u], 1);
-                }
-            } else {
-                const uint32_t p = c_p[j];
-                uint32_t *const slot = gbuf + wv * 64; // this wave's slots
-                uint32_t held = 0;                     // filled slots (uniform)
-                // slot entry: m | (mu(m) > 0) << 31
-                auto drain = [&]() {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    if (lane < held) {
-                        const uint32_t e = slot[lane];
-                        one(e & 0x7FFFFFFFu, (e >> 31) ? -1 : 1);
-                    }
-                    held = 0;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                };
-                // the loop bound is uniform: drain() needs every lane of the wave
-                for (uint32_t base = wv * 64 * HU; base < n; base += HU * T) {
-                    const uint32_t it0 = base + lane;
-                    int32_t v[HU];
-                    uint32_t mm[HU];
-#pragma unroll
-                    for (uint32_t u = 0; u < HU; u++) {
-                        mm[u] = pc_wheel_m(TB, ls + it0 + u * 64);
-                        v[u] = it0 + u * 64 < n ? TB.mulpf[mm[u]] : 0;
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < HU; u++) {
-                        const uint32_t it = it0 + u * 64;
-                        n_cand += it < n ? 1u : 0u;
-                        const uint32_t av = v[u] < 0 ? (uint32_t)(-v[u]) : (uint32_t)v[u];
-                        const bool keep = av > p; // squarefree (v != 0), lpf(m) > p_b
-                        const uint64_t bal = __ballot(keep);
-                        const uint32_t k = (uint32_t)__builtin_popcountll(bal);
-                        if (held + k > 64)
-                            drain();
-                        if (keep)
-                            slot[held + (uint32_t)__builtin_popcountll(bal & ((1ull << lane) - 1))] =
-                                mm[u] | (v[u] > 0 ? 0x80000000u : 0u);
-                        held += k;
-                        if (held == 64)
-                            drain();
-                    }
-                }
-                if (held)
-                    drain();
+                if (!more)
+                    break;
             }
+            leaf_check(bad);
             acc_local += lsum;
             const uint32_t ws = pc_wave_sum_u32((uint32_t)wsum);
             if (lane == 0 && ws != 0)

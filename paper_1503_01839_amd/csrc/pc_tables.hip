@@ -10,6 +10,7 @@
 //     the integers prime to 30 and phi(r, c) for r below the primorial Q_c.
 #include "pc_block.h"
 #include "pc_internal.h"
+#include "pc_leafrange.h"
 
 // ---------------------------------------------------------------------------
 // Odd primes below 2^16, by one workgroup (enough to sieve up to 2^32).
@@ -410,6 +411,22 @@ __global__ __launch_bounds__(MF_T) void k_mulpf(const uint32_t *primes, uint32_t
         }
         out[n] = v;
     }
+}
+
+// mu lpf in the order of the wheel (pc_wheel_m).
+__global__ __launch_bounds__(256) void k_mulpfw(pc_tables T, uint32_t n, int32_t *out)
+{
+    const uint32_t k = blockIdx.x * 256 + threadIdx.x;
+    if (k < n)
+        out[k] = T.mulpf[pc_wheel_m(T, k)];
+}
+
+hipError_t pc_launch_mulpfw(const pc_tables &T, uint64_t n, int32_t *mulpfw, hipStream_t s)
+{
+    if (n == 0 || n >= (1ull << 31))
+        return hipErrorInvalidValue;
+    k_mulpfw<<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(T, (uint32_t)n, mulpfw);
+    return hipGetLastError();
 }
 
 // *out += the number of nonzero entries of a[1..n] (a consistency check of the
