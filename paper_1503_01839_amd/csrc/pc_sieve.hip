@@ -53,10 +53,9 @@ typedef uint32_t pc_quad __attribute__((ext_vector_type(4), may_alias));
 template <int T> constexpr uint32_t pc_sieve_gcap() { return 2 * T > 256 ? 2 * T : 256; }
 template <int LOG2_S, int T, int CH> constexpr int pc_sieve_waves_per_simd()
 {
-    constexpr long S = 1l << LOG2_S, NW = S / 32, NBLK = S >> 9;
-    constexpr long NWV = T / 64;
-    constexpr long lds = 4 * (NW + 16) + 4 * (NBLK + 1) + 4 * pc_sieve_gcap<T>() + 4 * 2 * 64 +
-                         2 * (CH + 2) + 24 * CH + 16 * (CH / 64) + 8 + 8 * NWV + 16 * NWV;
+    constexpr long NW = (1l << LOG2_S) / 32, NWV = T / 64;
+    constexpr long lds = 4 * (NW + 16) + 4 * (T + 1) + 4 * pc_sieve_gcap<T>() + 4 * 2 * 64 +
+                         4 * (CH + 1) + 22 * CH + 16 * (CH / 64) + 8 + 4 * NWV + 16 * NWV;
     // (the CU hands LDS out in pieces of 1280 bytes)
     constexpr long wg = 163840 / ((lds + 1279) / 1280 * 1280);
     constexpr long waves = wg * NWV < 32 ? wg * NWV : 32;
@@ -67,7 +66,7 @@ template <int LOG2_S, int T, int CH, int MODE, bool BATCH>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     pc_sieve_waves_per_simd<LOG2_S, T, CH>()))) void k_sieve(pc_sieve_args A)
 {
-    static_assert(CH == T, "one lane per column of a chunk");
+    static_assert(CH <= T && CH % 64 == 0, "at most one lane per column of a chunk");
     static_assert(T % 64 == 0, "wavefront multiples");
     constexpr uint32_t S = 1u << LOG2_S;   // integers prime to 30 (bits) per segment
     constexpr uint32_t SPAN = S / 8 * 30;  // integers it covers
@@ -83,10 +82,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     static_assert((1u << RSL) == RS && RS == 64 * BPT * 512, "a region is 64 threads' blocks");
     constexpr uint32_t GCAP = pc_sieve_gcap<T>(); // leaf items of a gather window
     constexpr uint32_t SPT = GCAP / T;            // of which each thread takes SPT
-    // more leaf items: the column is answered workgroup-wide
-    constexpr uint32_t LIGHT = 127;
+    // more leaf items: the column is answered workgroup-wide (k_sieve at 10^18:
+    // 31.3 ms from 96 items on, 30.8 from 128, 30.3 from 257, 30.7 from 449)
+    constexpr uint32_t LIGHT = GCAP / 4;
     constexpr uint32_t MG = 64 / NWV < CH / 64 ? 64 / NWV : CH / 64; // groups of 64 columns of a window
-    static_assert(64 * MG * LIGHT < 65536 && LIGHT <= GCAP, "c_off counts modulo 2^16");
+    static_assert(LIGHT <= GCAP, "a light column fits a window");
     // p >= XB_P: at most 112 consecutive multipliers k reach a wave's region, so
     // at most 31 of its multiples there are prime to 30
     constexpr uint32_t XB_P = RSI / 112 + 1;
@@ -101,15 +101,17 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // its block (rot), which keeps a wavefront's reads on distinct banks.
     __shared__ __attribute__((aligned(16))) uint32_t bm[NW + 16]; // 16 spare words: a query at
                                                                   // q = S reads past the end
-    __shared__ uint32_t pre[NBLK + 1]; // prefix of the block counts
+    __shared__ uint32_t pre[T + 1];    // prefix of the threads' counts (build_pre)
     __shared__ uint32_t gbuf[GCAP];    // gathered leaves: k << 22 | q << 2 | (mu(m) > 0) << 1 | 1
     __shared__ uint32_t g_bin[2 * 64]; // leaves per (group of columns, region) of a window (two windows)
-    __shared__ uint16_t c_off[CH + 2]; // exclusive prefix of the light columns' leaf items, mod 2^16
+    __shared__ uint32_t c_off[CH + 1]; // exclusive prefix of the light columns' leaf items
     __shared__ uint32_t c_p[CH];       // p_b
     __shared__ uint32_t c_rem[CH];     // (lo / 30) mod p_b
     __shared__ uint32_t c_ls[CH];      // first leaf item (m, or index of the prime m)
     __shared__ uint32_t c_lc[CH];      // leaf items; PC_CAND: items are candidates (pc_wheel_m)
-    __shared__ uint32_t c_new[CH];     // integers first removed by p_b in this segment
+    // integers first removed by p_b in this segment, two columns a word (p_b >=
+    // 17 removes at most 2^19 / 17; smaller p_b belong to y < 13, z < 1100)
+    __shared__ uint32_t c_new[CH / 2];
     __shared__ int32_t c_w[CH];        // sum of -mu(m) over the leaves of the column
     __shared__ uint64_t c_leafy[CH / 64];
     __shared__ uint64_t c_heavy[CH / 64];
@@ -220,57 +222,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         swap_if(r & 2u, qs[0], qs[2]);
         swap_if(r & 2u, qs[1], qs[3]);
     };
-    // unsieved integers in each of the blocks thread tid counts
-    auto block_counts = [&](uint32_t (&cnt)[BPT]) -> uint32_t {
-        if constexpr (BPT == 1) {
-            cnt[0] = quad_count(0) + quad_count(1) + quad_count(2) + quad_count(3);
-            return cnt[0];
-        } else {
-            uint32_t qs[4];
-            quarter_counts(qs);
-            cnt[0] = qs[0] + qs[1];
-            cnt[1] = qs[2] + qs[3];
-            return cnt[0] + cnt[1];
-        }
-    };
-    // pre[] = exclusive prefix of the unsieved counts of the blocks; returns
-    // the segment total.  Every thread must call it; it ends with a barrier.
-    auto build_pre = [&]() -> uint32_t {
-        uint32_t cnt[BPT];
-        const uint32_t s = block_counts(cnt);
-        uint32_t tot;
-        uint32_t ex = pc_block_excl_scan<T>(s, scr32, &tot);
-#pragma unroll
-        for (uint32_t k = 0; k < BPT; k++) {
-            pre[tid * BPT + k] = ex;
-            ex += cnt[k];
-        }
-        if (tid == 0)
-            pre[NBLK] = tot;
-        __syncthreads();
-        return tot;
-    };
-    // unsieved integers of q's block on q's side: below q when q lies in the
-    // block's lower half (*up false), at or above q otherwise; eight words
-    auto half_count = [&](uint32_t q, bool *up) -> uint32_t {
-        const uint32_t nw = (q >> 5) & 15, part = (1u << (q & 31)) - 1;
-        *up = nw >= 8;
-        const uint32_t base = (q >> BL) * 16 + (*up ? 8u : 0u), k0 = *up ? 8u : 0u;
-        const uint32_t below = *up ? 0u : ~0u, at = *up ? ~part : part, above = ~below;
-        uint32_t s = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < 8; k++) {
-            const uint32_t m = k0 + k < nw ? below : (k0 + k == nw ? at : above);
-            s += (uint32_t)__builtin_popcount(bm[base + k] & m);
-        }
-        return s;
-    };
-    // unsieved integers among bits [0, q), q <= S, against pre[]
-    auto count_pre = [&](uint32_t q) -> uint32_t {
-        bool up;
-        const uint32_t s = half_count(q, &up), blk = q >> BL;
-        return up ? pre[blk + 1] - s : pre[blk] + s;
-    };
     // A thread's own words with finer sums: their unsieved count, and in *pk
     // the prefix counts of the first one, two and three quarters (10 bits
     // each: at most 768).
@@ -304,10 +255,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return up ? through - (all - lt) : below + lt;
     };
 
-    // pre[] with the quarter prefixes of every thread's words beside it, in the
-    // half of gbuf that a heavy column leaves free
+    // pre[] = exclusive prefix of the threads' counts, with the quarter
+    // prefixes of every thread's words beside it in the half of gbuf that no
+    // leaf occupies meanwhile; returns the segment total.  Every thread must
+    // call it; a wave reads only words of its own region before the first
+    // barrier.
     uint32_t *const preq = gbuf + GCAP - T;
-    auto build_preq = [&]() {
+    auto build_pre = [&]() -> uint32_t {
         uint32_t pq;
         const uint32_t n = block_counts_q(&pq), inc = pc_wave_incl_scan_u32(n);
         const uint32_t w = tid >> 6;
@@ -323,9 +277,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         if (tid == T - 1)
             pre[T] = ex + n;
         __syncthreads();
+        return pre[T];
     };
-    // unsieved integers among bits [0, q), q <= S, against build_preq
-    auto count_preq = [&](uint32_t q) -> uint32_t {
+    // unsieved integers among bits [0, q), q <= S, against build_pre
+    auto count_pre = [&](uint32_t q) -> uint32_t {
         const uint32_t i = q / (512 * BPT);
         const uint32_t ex = pre[i];
         return q < S ? ex + quarter_count(q, preq[i], pre[i + 1] - ex) : ex;
@@ -448,7 +403,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // all of them, one in this region counts a prefix of it.
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t R0 = wv * RS, R1 = R0 + RS;
-    uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[R1 >> BL] - pre[R0 >> BL]));
+    uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[64 * wv + 64] - pre[64 * wv]));
     // unsieved integers of this wave's region below bit q of the segment (in:
     // q lies in the region or at the segment's end), from the lanes' counts c0, their exclusive
     // prefix pe and quarter prefixes pq
@@ -514,6 +469,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             s_first_large = jall;
             s_first_skip = jall;
         }
+        if (tid < CH / 2)
+            c_new[tid] = 0;
         __syncthreads();
         // --- one lane per column: first multiple, leaf range ---
         bool leafy = false, heavy = false, large = false, skip = false;
@@ -533,7 +490,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 pc_leaf_range(TB, Q, b, p, rp, lo, hi, rhi, rlo, &ls, &lc);
             c_ls[j] = ls;
             c_lc[j] = lc;
-            c_new[j] = 0;
             c_w[j] = 0;
             leafy = lc != 0;
             heavy = (lc & ~PC_CAND) > LIGHT;
@@ -544,14 +500,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         {
             uint32_t tot;
             const uint32_t ex = pc_block_excl_scan<T>(light, scr32, &tot);
-            c_off[tid] = (uint16_t)ex;
+            if (tid < CH)
+                c_off[tid] = ex;
             if (tid == T - 1)
-                c_off[T] = (uint16_t)tot;
+                c_off[CH] = tot;
         }
         {
             const uint64_t bl = __ballot(leafy), bh = __ballot(heavy), bg = __ballot(large);
             const uint64_t bs = __ballot(skip);
-            if (lane == 0) {
+            if (lane == 0 && tid < CH) {
                 c_leafy[tid >> 6] = bl;
                 c_heavy[tid >> 6] = bh;
                 if (bg)
@@ -578,7 +535,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             // (j - cg0 >= 64: reload)
         auto flush_removed = [&]() {
             if (v_rem)
-                atomicAdd(&c_new[cg0 + lane], v_rem);
+                atomicAdd(&c_new[(cg0 + lane) >> 1], v_rem << (((cg0 + lane) & 1u) * 16u));
             v_rem = 0;
         };
         auto load_group = [&](uint32_t j) { // the columns from j on
@@ -854,13 +811,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 const uint32_t col = base + lane;
                 bool ok = false;
                 if (col < lim)
-                    ok = ((c_off[col + 1] - o0) & 0xFFFFu) <= GCAP;
+                    ok = c_off[col + 1] - o0 <= GCAP;
                 const uint64_t m = __ballot(ok);
                 we = base + (uint32_t)__builtin_popcountll(m);
                 if (~m)
                     break;
             }
-            const uint32_t used = pc_uniform((c_off[we] - o0) & 0xFFFFu);
+            const uint32_t used = pc_uniform(c_off[we] - o0);
             const uint32_t h0 = we - j0 > 1 ? 1u << (31 - __builtin_clz(we - j0 - 1)) : 0u;
             uint32_t *const bins = g_bin + g_par * 64;
             if (tid < 64)
@@ -878,7 +835,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 uint32_t a = j0, oa = 0;
                 for (uint32_t h = h0; h; h >>= 1) {
                     const uint32_t c = a + h;
-                    const uint32_t o = c < we ? (c_off[c] - o0) & 0xFFFFu : 0xFFFFu;
+                    const uint32_t o = c < we ? c_off[c] - o0 : 0xFFFFu;
                     if (o <= s) {
                         a = c;
                         oa = o;
@@ -966,7 +923,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             const double Xd = __longlong_as_double(
                 (long long)pc_uniform64((uint64_t)__double_as_longlong(Xd1[cb + j])));
             uint32_t next = tid < n ? src[tid] : 0u;
-            build_preq();
+            build_pre();
             int32_t wsum = 0;
             int64_t lsum = 0;
             uint32_t bad = 0;
@@ -1008,7 +965,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 }
                 if (have) {
                     const uint32_t q = leaf_q(X, Xd, m, &bad);
-                    lsum += (int64_t)(w * (int32_t)count_preq(q));
+                    lsum += (int64_t)(w * (int32_t)count_pre(q));
                     wsum += w;
                     nleaf++;
                 }
@@ -1107,7 +1064,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         __syncthreads(); // c_new complete; every wave is past the last window
         // --- chunk results: cnt before each crossing, and w ---
         {
-            const uint32_t v = tid < jend ? c_new[tid] : 0;
+            const uint32_t v = tid < jend ? (c_new[tid >> 1] >> ((tid & 1u) * 16u)) & 0xFFFFu : 0u;
             uint32_t tot;
             const uint32_t ex = pc_block_excl_scan<T>(v, scr32, &tot);
             const uint32_t col = cb + tid;
@@ -1551,7 +1508,7 @@ hipError_t pc_launch_sieve(const pc_sieve_args &A, uint32_t seg_log2, uint32_t w
     if (seg_log2 == 18 && wg == 512)
         return launch_modes<18, 512, 512>(A, mode, batch, s);
     if (seg_log2 == 19 && wg == 512)
-        return launch_modes<19, 512, 512>(A, mode, batch, s);
+        return launch_modes<19, 512, 256>(A, mode, batch, s);
     if (seg_log2 == 19 && wg == 1024)
         return launch_modes<19, 1024, 1024>(A, mode, batch, s);
     return hipErrorInvalidValue;
