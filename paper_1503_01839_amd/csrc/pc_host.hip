@@ -248,11 +248,20 @@ void init_stream()
         hipck(hipEventCreateWithFlags(&g_join, hipEventDisableTiming), "hipEventCreate");
 }
 
-// pi at a few points, read back to the host (planning only).
+// pi at a few points (planning, and the answers below kSmallX): from the host
+// copy of the table when it covers all of them (a read takes tens of ns, so a
+// whole pi(5 * 10^5) takes 1 us), else from the device's (two copies, a launch
+// and a wait: 26 us, and the stream drained once more before each query).
 std::vector<uint64_t> lookup(const std::vector<uint64_t> &pts)
 {
     Tables &T = g_T;
     size_t n = pts.size();
+    if (std::all_of(pts.begin(), pts.end(), [&](uint64_t v) { return v <= T.pi_host_max; })) {
+        std::vector<uint64_t> out(n);
+        for (size_t i = 0; i < n; i++)
+            out[i] = pts[i] < 2 ? 0 : pc_pi_lookup(T.pi_host, pts[i]);
+        return out;
+    }
     ensure(T.lk_in, n * 8, "lookup");
     ensure(T.lk_out, n * 8, "lookup");
     hipck(hipMemcpyAsync(T.lk_in.p, pts.data(), n * 8, hipMemcpyHostToDevice, g_stream), "H2D");
@@ -332,6 +341,7 @@ void ensure_pi(uint64_t need)
             (void)hipHostFree(T.pi_host);
         T.pi_host = nullptr;
         T.pi_host_cap = 0;
+        T.pi_host_max = 0;
         if (hipHostMalloc((void **)&T.pi_host, nh * 8, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             T.pi_host = nullptr;
@@ -498,10 +508,14 @@ void ensure_mulpfw(uint64_t y)
         return;
     ensure_wheel(kWheelC);
     const uint64_t Y = T.y_limit;
-    // the integers <= Y prime to 2 .. 13: whole periods, then the residues
-    uint64_t n = Y / T.Qc[kWheelC] * T.phiQ[kWheelC];
-    for (uint64_t r = 1; r <= Y % T.Qc[kWheelC]; r++)
-        n += r % 2 && r % 3 && r % 5 && r % 7 && r % 11 && r % 13;
+    // the integers <= Y prime to 2 .. 13, over the 64 products of these primes
+    uint64_t n = 0;
+    for (uint32_t set = 0; set < 1u << kWheelC; set++) {
+        uint64_t d = 1;
+        for (uint32_t i = 0; i < kWheelC; i++)
+            d *= set >> i & 1 ? kFirstPrimes[i + 1] : 1;
+        n += __builtin_popcount(set) & 1 ? -(Y / d) : Y / d;
+    }
     ensure(T.mulpfw, n * 4, "mu*lpf table by the wheel");
     hipck(pc_launch_mulpfw(tables_view(kWheelC), n, ptr<int32_t>(T.mulpfw), g_stream),
           "mu*lpf table by the wheel");
