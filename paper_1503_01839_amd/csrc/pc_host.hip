@@ -248,20 +248,11 @@ void init_stream()
         hipck(hipEventCreateWithFlags(&g_join, hipEventDisableTiming), "hipEventCreate");
 }
 
-// pi at a few points (planning, and the answers below kSmallX): from the host
-// copy of the table when it covers all of them (a read takes tens of ns, so a
-// whole pi(5 * 10^5) takes 1 us), else from the device's (two copies, a launch
-// and a wait: 26 us, and the stream drained once more before each query).
-std::vector<uint64_t> lookup(const std::vector<uint64_t> &pts)
+// pi at a few points from the device table: two copies, a launch and a wait.
+std::vector<uint64_t> lookup_device(const std::vector<uint64_t> &pts)
 {
     Tables &T = g_T;
     size_t n = pts.size();
-    if (std::all_of(pts.begin(), pts.end(), [&](uint64_t v) { return v <= T.pi_host_max; })) {
-        std::vector<uint64_t> out(n);
-        for (size_t i = 0; i < n; i++)
-            out[i] = pts[i] < 2 ? 0 : pc_pi_lookup(T.pi_host, pts[i]);
-        return out;
-    }
     ensure(T.lk_in, n * 8, "lookup");
     ensure(T.lk_out, n * 8, "lookup");
     hipck(hipMemcpyAsync(T.lk_in.p, pts.data(), n * 8, hipMemcpyHostToDevice, g_stream), "H2D");
@@ -271,6 +262,22 @@ std::vector<uint64_t> lookup(const std::vector<uint64_t> &pts)
     std::vector<uint64_t> out(n);
     hipck(hipMemcpyAsync(out.data(), T.lk_out.p, n * 8, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipStreamSynchronize(g_stream), "sync");
+    return out;
+}
+
+// The same for planning, and for the answers below kSmallX: from the host copy
+// of the table when it covers all of them (a read takes tens of ns: a whole
+// pi(5 * 10^5) takes 0.7 us where the device's lookup took 26 us, and it waited
+// for the stream once more before each query).
+std::vector<uint64_t> lookup(const std::vector<uint64_t> &pts)
+{
+    const Tables &T = g_T;
+    for (uint64_t v : pts)
+        if (v > T.pi_host_max)
+            return lookup_device(pts);
+    std::vector<uint64_t> out(pts.size());
+    for (size_t i = 0; i < pts.size(); i++)
+        out[i] = pc_pi_lookup(T.pi_host, pts[i]);
     return out;
 }
 
@@ -2568,7 +2575,7 @@ pc_status pc_read_table(int which, uint64_t lo, uint64_t n, void *out)
             std::vector<uint64_t> pts(n);
             for (uint64_t i = 0; i < n; i++)
                 pts[i] = lo + i;
-            const std::vector<uint64_t> v = lookup(pts);
+            const std::vector<uint64_t> v = lookup_device(pts);
             memcpy(out, v.data(), n * 8);
         } else if (which == PC_TABLE_MULPF) {
             if (last > (1ull << 31) - 2)
@@ -2600,6 +2607,9 @@ pc_status pc_phi_seed(uint64_t m, uint32_t c, uint32_t b_hi, uint64_t *out)
     }
     return guarded([&] {
         init_stream();
+        // the work of an earlier query (one that failed part way too) is done
+        hipck(hipStreamSynchronize(g_stream), "sync");
+        hipck(hipStreamSynchronize(g_stream2), "sync");
         Tables &T = g_T;
         // the pi table answers every Legendre lookup (below m^(2/3)) and holds p_{b_hi + 1}
         const uint64_t r = pc_icbrt(m) + 1;
@@ -2615,19 +2625,28 @@ pc_status pc_phi_seed(uint64_t m, uint32_t c, uint32_t b_hi, uint64_t *out)
         const uint32_t nb = b_hi - c;
         QueryBufs &B = g_Q;
         ensure(B.seed_term, ((size_t)nb + 1) * 8, "seed terms");
-        ensure(B.carry_a, ((size_t)nb + 1) * 8, "carry");
-        ensure(B.err, 8, "error flag");
-        hipck(pc_launch_fill_u64(ptr<uint64_t>(B.err), 1, 0, g_stream), "fill");
+        // the error flag lies behind the seeds, so that one copy brings back both
+        const size_t n_out = ((size_t)nb + 1) * 8;
+        ensure(B.carry_a, n_out + 8, "carry");
+        uint64_t *const d_out = ptr<uint64_t>(B.carry_a);
+        hipck(pc_launch_fill_u64(d_out + nb + 1, 1, 0, g_stream), "fill");
         hipck(pc_launch_seed(tables_view(c), c, m, nb, seed_rec_cols(m, c, nb), T.pi_limit,
-                             ptr<int64_t>(B.seed_term), ptr<uint64_t>(B.carry_a),
-                             ptr<int32_t>(B.err), g_stream),
+                             ptr<int64_t>(B.seed_term), d_out,
+                             reinterpret_cast<int32_t *>(d_out + nb + 1), g_stream),
               "seeds");
         int32_t err = 0;
-        hipck(hipMemcpyAsync(out, B.carry_a.p, ((size_t)nb + 1) * 8, hipMemcpyDeviceToHost,
-                             g_stream),
-              "D2H");
-        hipck(hipMemcpyAsync(&err, B.err.p, 4, hipMemcpyDeviceToHost, g_stream), "D2H");
-        hipck(hipStreamSynchronize(g_stream), "sync");
+        if (n_out <= ((size_t)4 << 20)) { // through pinned memory (a chunk of the arena)
+            g_pin.reset();
+            char *const st = static_cast<char *>(g_pin.take(n_out + 8));
+            hipck(hipMemcpyAsync(st, d_out, n_out + 8, hipMemcpyDeviceToHost, g_stream), "D2H");
+            hipck(hipStreamSynchronize(g_stream), "sync");
+            memcpy(out, st, n_out);
+            memcpy(&err, st + n_out, 4);
+        } else {
+            hipck(hipMemcpyAsync(out, d_out, n_out, hipMemcpyDeviceToHost, g_stream), "D2H");
+            hipck(hipMemcpyAsync(&err, d_out + nb + 1, 4, hipMemcpyDeviceToHost, g_stream), "D2H");
+            hipck(hipStreamSynchronize(g_stream), "sync");
+        }
         if (err)
             fail(PC_EINTERNAL, "seeds: pi table too short, stack too deep or a negative phi");
     });
