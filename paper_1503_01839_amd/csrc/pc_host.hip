@@ -119,6 +119,7 @@ struct Tables {
     DevBuf mulpf, mulpfw;
     uint64_t y_limit = 0;
     uint64_t w_limit = 0; // mulpfw covers the m <= w_limit prime to 2 .. 13
+    DevBuf presieve;
     DevBuf pattern[kWheelC + 1], phitab[kWheelC + 1], wres[kWheelC + 1];
     bool wheel_ok[kWheelC + 1] = {};
     uint32_t pattern_bits[kWheelC + 1] = {}, Qc[kWheelC + 1] = {}, phiQ[kWheelC + 1] = {};
@@ -480,6 +481,10 @@ void ensure_wheel(uint32_t c)
     hipck(pc_launch_wheel(c, ptr<uint32_t>(T.primes), ptr<uint32_t>(T.pattern[c]), words,
                           ptr<uint32_t>(T.phitab[c]), ptr<uint32_t>(T.wres[c]), g_stream),
           "wheel");
+    if (c == kWheelC) {
+        ensure(T.presieve, pc_presieve_at(PC_PS_GROUPS), "pre-sieve patterns");
+        hipck(pc_launch_presieve(ptr<uint8_t>(T.presieve), g_stream), "pre-sieve patterns");
+    }
     T.pattern_bits[c] = period;
     T.Qc[c] = Q;
     T.phiQ[c] = phiQ;
@@ -499,6 +504,7 @@ pc_tables tables_view(uint32_t c)
     v.mulpf = ptr<int32_t>(T.mulpf);
     v.mulpfw = ptr<int32_t>(T.mulpfw);
     v.pattern = ptr<uint32_t>(T.pattern[c]);
+    v.presieve = ptr<uint8_t>(T.presieve);
     v.phitab = ptr<uint32_t>(T.phitab[c]);
     v.wres = ptr<uint32_t>(T.wres[c]);
     v.pattern_bits = T.pattern_bits[c];
@@ -539,7 +545,7 @@ void drop_tables(bool release)
     if (release) {
         DevBuf *all[] = {&T.base, &T.nbase_d, &T.pitab, &T.primes, &T.primes_hi, &T.cnt_tmp,
                          &T.scan_tmp, &T.recip,
-                         &T.rcpd, &T.mulpf, &T.mulpfw, &T.lk_in, &T.lk_out, &T.chk};
+                         &T.rcpd, &T.presieve, &T.mulpf, &T.mulpfw, &T.lk_in, &T.lk_out, &T.chk};
         for (DevBuf *b : all)
             dfree(*b);
         for (int c = 0; c <= kWheelC; c++) {

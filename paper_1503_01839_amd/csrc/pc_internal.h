@@ -30,12 +30,28 @@ struct pc_tables {
     const int32_t *mulpfw;  // the same of the k-th integer prime to 2 .. 13 (pc_wheel_m), in order
     const uint32_t *pattern; // pre-sieve bits for p_4..p_c (8 bits per 30 integers), period
                             // pattern_bits (+64 bits)
+    const uint8_t *presieve; // the multiples of 17 .. 67 (pc_presieve_*)
     const uint32_t *phitab; // phi(r, c) for r < Q_c
     const uint32_t *wres;   // the residues r < Q_c prime to p_1..p_c, ascending (phi(Q_c, c) of them)
     uint32_t pattern_bits;  // 8 prod_{4 <= i <= c} p_i
     uint32_t Qc;            // prod_{1 <= i <= c} p_i
     uint32_t phiQ;          // phi(Q_c, c)
 };
+
+// The bitmaps of the integers prime to the primes 17 .. 67 (p_7 .. p_19), in six
+// groups: byte i of group g stands for 30 i .. 30 i + 29 (pc_w30_*) and repeats
+// after the product of the group's primes; each is followed by its first four
+// bytes, so that a word is read at any byte of the period.
+constexpr uint32_t PC_PS_FIRST = 7, PC_PS_LAST = 19, PC_PS_GROUPS = 6;
+constexpr uint32_t pc_presieve_period(uint32_t g)
+{
+    return g == 0 ? 17 * 19 * 23 : g == 1 ? 29 * 31 : g == 2 ? 37 * 41 : g == 3 ? 43 * 47
+                                 : g == 4 ? 53 * 59 : 61 * 67;
+}
+constexpr uint32_t pc_presieve_at(uint32_t g) // first byte of group g (PC_PS_GROUPS: the size)
+{
+    return g == 0 ? 0 : pc_presieve_at(g - 1) + pc_presieve_period(g - 1) + 4;
+}
 
 struct pc_sums;
 
@@ -164,6 +180,7 @@ hipError_t pc_launch_mulpf(const uint32_t *primes, uint32_t nsmall, uint64_t yma
 hipError_t pc_launch_mulpfw(const pc_tables &T, uint64_t n, int32_t *mulpfw, hipStream_t s);
 hipError_t pc_launch_count_nonzero(const int32_t *a, uint64_t n, unsigned long long *out,
                                    hipStream_t s);
+hipError_t pc_launch_presieve(uint8_t *out, hipStream_t s);
 hipError_t pc_launch_wheel(uint32_t c, const uint32_t *primes, uint32_t *pattern,
                            uint32_t pattern_words, uint32_t *phitab, uint32_t *wres,
                            hipStream_t s);

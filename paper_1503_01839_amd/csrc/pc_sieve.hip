@@ -35,6 +35,7 @@
 #include "pc_block.h"
 #include "pc_internal.h"
 #include "pc_leafrange.h"
+#include <type_traits>
 
 // PC_PHASE_TRACE=1 adds per-phase tick counters to the tile trace (a
 // profiling build; the default build only records totals)
@@ -90,9 +91,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // p >= XB_P: at most 112 consecutive multipliers k reach a wave's region, so
     // at most 31 of its multiples there are prime to 30
     constexpr uint32_t XB_P = RSI / 112 + 1;
-    // columns that are only cleared (clear_columns): up to CLR_TINY by all
-    // threads together, from CLR_SEQ on by one lane each, between by eight
-    constexpr uint32_t CLR_TINY = 64, CLR_SEQ = SPAN / 60;
+    // columns that are only cleared (clear_columns): primes below 2^6 by all
+    // threads together, below 2^9 by a wavefront each, below 2^11 by half of one,
+    // from SPAN / 60 = 2^(LOG2_S - 4) on by one lane, between by eight (the
+    // primes below these: PI_TINY, PI_WAVE, PI_HALF, PI_SEQ)
+    static_assert(LOG2_S >= 15 && LOG2_S <= 19, "pi(2^11) .. pi(2^15)");
+    constexpr uint32_t PI_TINY = 18, PI_WAVE = 97, PI_HALF = 309, PI_SEQ = LOG2_S == 15   ? 309
+                                              : LOG2_S == 16 ? 564
+                                              : LOG2_S == 17 ? 1028
+                                              : LOG2_S == 18 ? 1900
+                                                             : 3512;
     static_assert(GCAP >= 2 * T, "a heavy column: 64 slots of gbuf per wave, then its quarter table");
 
     // Word w of the segment is bm[w]; no padding, so a crossing's address is
@@ -170,7 +178,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     const uint64_t rlo = lo ? pc_recip(lo) : 0;
     const uint32_t ncol = Q.ncol;
 
-    // --- pre-sieved state: the wheel pattern (p_4..p_c already crossed) ---
+    // --- pre-sieved state: the wheel pattern (p_4..p_c already crossed), and the
+    // multiples of 17 .. 67 where the tile's columns start past them: six more
+    // words each instead of 40% of the clears that the columns below 1000 take
+    // (with the clears by half wavefronts and more, k_sieve at 10^12 131 -> 111
+    // us, decompose(10^16, 4 icbrt) 4.28 -> 4.12 ms, 10^18 30.0 -> 29.5 ms) ---
+    const uint32_t col_lo = tile.col_lo, col_hi = tile.col_hi;
+    const bool ps = qc == PC_PS_FIRST - 1 && col_lo >= PC_PS_LAST - qc; // (uniform)
     {
         const uint32_t P = TB.pattern_bits;
         const uint32_t g0 = (uint32_t)((8 * lob) % P);
@@ -185,6 +199,27 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             off += step;
             if (off >= P)
                 off -= P;
+        }
+    }
+    if (ps) {
+        uint32_t off[PC_PS_GROUPS];
+#pragma unroll
+        for (uint32_t g = 0; g < PC_PS_GROUPS; g++) {
+            const uint32_t P = pc_presieve_period(g);
+            off[g] = ((uint32_t)(lob % P) + 4u * tid) % P;
+        }
+#pragma unroll 4
+        for (uint32_t w = tid; w < NW; w += T) {
+            uint32_t v = bm[w];
+#pragma unroll
+            for (uint32_t g = 0; g < PC_PS_GROUPS; g++) {
+                uint32_t x;
+                __builtin_memcpy(&x, TB.presieve + pc_presieve_at(g) + off[g], 4);
+                v &= x;
+                off[g] += 4u * T % pc_presieve_period(g);
+                off[g] -= off[g] >= pc_presieve_period(g) ? pc_presieve_period(g) : 0u;
+            }
+            bm[w] = v;
         }
     }
     for (uint32_t i = tid; i < 128; i += T)
@@ -223,26 +258,38 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         swap_if(r & 2u, qs[1], qs[3]);
     };
     // A thread's own words with finer sums: their unsieved count, and in *pk
-    // the prefix counts of the first one, two and three quarters (10 bits
-    // each: at most 768).
+    // its quarters.  A byte each while a quarter's 128 bits fit one; else the
+    // prefix counts of the first one, two and three quarters, 10 bits each.
+    constexpr bool QB = BPT == 1;
     auto block_counts_q = [&](uint32_t *pk) -> uint32_t {
         uint32_t qs[4];
         quarter_counts(qs);
+        if (QB) {
+            *pk = qs[0] | qs[1] << 8 | qs[2] << 16 | qs[3] << 24;
+            return qs[0] + qs[1] + qs[2] + qs[3];
+        }
         const uint32_t p1 = qs[0], p2 = p1 + qs[1], p3 = p2 + qs[2];
         *pk = p1 | (p2 << 10) | (p3 << 20);
         return p3 + qs[3];
     };
     // unsieved integers below q among the words of the thread that counts q's
-    // block, from their quarter prefixes pk and total tb: the half of q's
-    // quarter on q's side is read (up from the quarter's start, or down from
-    // its end)
+    // block, from their quarters pk and total tb (not read if QB): the half of
+    // q's quarter on q's side is read (up from the quarter's start, or down
+    // from its end)
     constexpr uint32_t QW = 4 * BPT, HW = QW / 2; // words of a quarter, of half of one
     auto quarter_count = [&](uint32_t q, uint32_t pk, uint32_t tb) -> uint32_t {
         const uint32_t w = (q >> 5) & (QW - 1), qq = (q >> 5) / QW & 3u;
         const uint32_t part = (1u << (q & 31u)) - 1u; // bits below q in its word
-        const uint32_t below = qq ? (pk >> (10u * (qq - 1u))) & 1023u : 0u;
-        const uint32_t through = qq < 3u ? (pk >> (10u * qq)) & 1023u : tb;
         const bool up = w >= HW;
+        uint32_t base; // the count at the quarter's start, or (up) at its end
+        if (QB) {
+            base = __builtin_amdgcn_sad_u8(pk & ((1u << 8u * qq) - 1u), 0u, 0u) +
+                   (up ? (pk >> 8u * qq) & 255u : 0u);
+        } else {
+            const uint32_t below = qq ? (pk >> (10u * (qq - 1u))) & 1023u : 0u;
+            const uint32_t through = qq < 3u ? (pk >> (10u * qq)) & 1023u : tb;
+            base = up ? through : below;
+        }
         const uint32_t *const v = bm + ((q >> 5) & ~(QW - 1)) + (up ? HW : 0u);
         const uint32_t wh = up ? w - HW : w; // q's word in the half
         uint32_t lt = 0, all = 0;            // bits of the half below q, all of them
@@ -252,7 +299,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             lt += (uint32_t)__builtin_popcount(b & (k < wh ? ~0u : k == wh ? part : 0u));
             all += (uint32_t)__builtin_popcount(b);
         }
-        return up ? through - (all - lt) : below + lt;
+        return base + lt - (up ? all : 0u);
     };
 
     // pre[] = exclusive prefix of the threads' counts, with the quarter
@@ -283,7 +330,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     auto count_pre = [&](uint32_t q) -> uint32_t {
         const uint32_t i = q / (512 * BPT);
         const uint32_t ex = pre[i];
-        return q < S ? ex + quarter_count(q, preq[i], pre[i + 1] - ex) : ex;
+        return q < S ? ex + quarter_count(q, preq[i], QB ? 0u : pre[i + 1] - ex) : ex;
     };
     // floor(e / p), e < 2^27, quotient < 2^17: the fp32 reciprocal rp of p puts
     // the estimate within one of it, one step corrects it
@@ -337,15 +384,17 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         char *const sb = reinterpret_cast<char *>(bm);
         for (uint32_t kb = k0; kb < k1; kb += CH) {
             const uint32_t n = min((uint32_t)CH, k1 - kb);
-            bool seq = false, tiny = false;
+            const uint32_t b0 = qc + 1 + kb;
+            const uint32_t ntiny = min(n, PI_TINY + 1 - min(PI_TINY + 1, b0));
+            const uint32_t nwave = min(n, PI_WAVE + 1 - min(PI_WAVE + 1, b0));
+            const uint32_t nhalf = min(n, PI_HALF + 1 - min(PI_HALF + 1, b0));
+            const uint32_t nseq = n - min(n, PI_SEQ + 1 - min(PI_SEQ + 1, b0));
             if (tid < n) {
                 const uint32_t b = qc + 1 + kb + tid, p = TB.primes[b];
                 const uint32_t rem = rem_lob(p, TB.rcpd[b]);
                 c_p[tid] = p;
                 c_rem[tid] = rem;
-                tiny = p < CLR_TINY;
-                seq = p >= CLR_SEQ;
-                if (seq) { // few multiples: one lane takes them in order
+                if (tid >= n - nseq) { // few multiples: one lane takes them in order
                     const uint32_t r30 = 30u * rem;
                     const uint32_t q = small_quot(r30, p, __builtin_amdgcn_rcpf((float)p));
                     const uint32_t j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
@@ -360,24 +409,39 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     }
                 }
             }
-            const uint32_t ntiny = (uint32_t)__syncthreads_count(tiny);
-            const uint32_t nseq = (uint32_t)__syncthreads_count(seq);
-            // the smallest: a column's multiples in turn by all threads, T / 8
-            // rounds of its eight classes side by side
-            for (uint32_t k = 0; k < ntiny; k++) {
-                const uint32_t p = pc_uniform(c_p[k]), rem = pc_uniform(c_rem[k]);
-                uint32_t bit;
-                const uint32_t e = class_of(p, &bit);
-                int32_t at = (int32_t)((tid >> 3) * p + e) - (int32_t)rem;
-                const uint32_t keep = ~(1u << ((((uint32_t)at << 3) | bit) & 31u));
-                if (at < 0) // T / 8 p bytes on: the same bit of the word
-                    at += (int32_t)(T / 8 * p);
-                for (; at < (int32_t)(SPAN / 30); at += (int32_t)(T / 8 * p))
-                    __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(sb + (at & ~3)), keep,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
+            __syncthreads();
+            // L lanes a column, L / 8 rounds of its eight classes side by side: a
+            // lane's multiples lie L / 8 p bytes apart, at one bit of their words
+            // for L >= 32 (eight lanes alone take 500 steps in turn for p = 67: 14
+            // us, where the whole tile of a small query takes 60)
+            auto by_lanes = [&](auto lanes, uint32_t k0, uint32_t k1) {
+                constexpr uint32_t L = decltype(lanes)::value;
+                for (uint32_t k = k0 + tid / L; k < k1; k += T / L) {
+                    const uint32_t p = c_p[k], step = L / 8 * p;
+                    uint32_t bit;
+                    const uint32_t e = class_of(p, &bit);
+                    int32_t at = (int32_t)(tid % L / 8 * p + e) - (int32_t)c_rem[k];
+                    const uint32_t keep = ~(1u << ((((uint32_t)at << 3) | bit) & 31u));
+                    if (at < 0)
+                        at += (int32_t)step;
+                    at &= ~3;
+                    auto clear = [&](int32_t w) {
+                        __hip_atomic_fetch_and(reinterpret_cast<uint32_t *>(sb + w), keep,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    };
+                    for (; at < (int32_t)(SPAN / 30 - min(SPAN / 30, step)); at += 2 * (int32_t)step) {
+                        clear(at);
+                        clear(at + (int32_t)step);
+                    }
+                    if (at < (int32_t)(SPAN / 30))
+                        clear(at);
+                }
+            };
+            by_lanes(std::integral_constant<uint32_t, T>{}, 0, ntiny);
+            by_lanes(std::integral_constant<uint32_t, 64>{}, ntiny, nwave);
+            by_lanes(std::integral_constant<uint32_t, 32>{}, nwave, nhalf);
             // the others: one lane per class of a column
-            for (uint32_t k = ntiny + (tid >> 3); k < n - nseq; k += T / 8) {
+            for (uint32_t k = nhalf + (tid >> 3); k < n - nseq; k += T / 8) {
                 const uint32_t p = c_p[k];
                 uint32_t bit;
                 int32_t at = (int32_t)class_of(p, &bit) - (int32_t)c_rem[k];
@@ -393,9 +457,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     };
 
     // a tile that owns the columns from col_lo on needs the earlier ones only cleared
-    const uint32_t col_lo = tile.col_lo, col_hi = tile.col_hi;
     if (col_lo)
-        clear_columns(0, col_lo);
+        clear_columns(ps ? PC_PS_LAST - qc : 0u, col_lo);
     uint32_t total = build_pre();
     PC_PH(0);
     // Wavefront wv owns bits [R0, R1).  rc = its unsieved integers, kept exact
@@ -406,13 +469,14 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     uint32_t rc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(pre[64 * wv + 64] - pre[64 * wv]));
     // unsieved integers of this wave's region below bit q of the segment (in:
     // q lies in the region or at the segment's end), from the lanes' counts c0, their exclusive
-    // prefix pe and quarter prefixes pq
+    // prefix pe and quarters pq
     auto region_count = [&](bool in, uint32_t q, uint32_t pe, uint32_t c0, uint32_t pq) -> uint32_t {
         const uint32_t d = in ? q - R0 : 0u;
         const int32_t src = (int32_t)min(d / (512 * BPT), 63u);
         uint32_t c = (uint32_t)__shfl((int)pe, src, 64);
-        const uint32_t tb = (uint32_t)__shfl((int)c0, src, 64);
         const uint32_t pk = (uint32_t)__shfl((int)pq, src, 64);
+        const uint32_t tb = QB ? __builtin_amdgcn_sad_u8(pk, 0u, 0u)
+                               : (uint32_t)__shfl((int)c0, src, 64);
         if (in) // (q = S, past the last region's last bit, counts all of it)
             c += d < RS ? quarter_count(q, pk, tb) : tb;
         return c;

@@ -528,6 +528,34 @@ hipError_t pc_launch_wheel(uint32_t c, const uint32_t *primes, uint32_t *pattern
     return hipGetLastError();
 }
 
+// One byte of pc_tables::presieve a thread.
+__global__ __launch_bounds__(256) void k_presieve(uint8_t *out)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= pc_presieve_at(PC_PS_GROUPS))
+        return;
+    constexpr uint32_t primes[PC_PS_GROUPS][3] = {{17, 19, 23}, {29, 31, 31}, {37, 41, 41},
+                                                  {43, 47, 47}, {53, 59, 59}, {61, 67, 67}};
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t g = 0; g < PC_PS_GROUPS; g++) {
+        if (i < pc_presieve_at(g) || i >= pc_presieve_at(g + 1))
+            continue;
+        const uint32_t byte = i - pc_presieve_at(g);
+        for (uint32_t b = 0; b < 8; b++) {
+            const uint32_t n = 30 * byte + pc_w30_res(b);
+            v |= (n % primes[g][0] && n % primes[g][1] && n % primes[g][2] ? 1u : 0u) << b;
+        }
+    }
+    out[i] = (uint8_t)v;
+}
+
+hipError_t pc_launch_presieve(uint8_t *out, hipStream_t s)
+{
+    k_presieve<<<(pc_presieve_at(PC_PS_GROUPS) + 255) / 256, 256, 0, s>>>(out);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Small helpers: pi at a few points; X_b = floor(x / p_b).
 // ---------------------------------------------------------------------------
