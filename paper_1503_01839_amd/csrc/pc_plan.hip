@@ -23,7 +23,9 @@
 #define PL_CROSS 240u
 #define PL_LARGE 60u
 #define PL_ANSWER 200u
-#define PL_MIN 8192u     // no tile of less work than this (unless the caller says so)
+#define PL_MIN 8192u     // no tile of less work than this (unless the caller says so) ...
+#define PL_FEW 256u      // ... where that leaves a CU without a tile: down to
+#define PL_LEAST 2048u   // this (pi(10^9) 157 -> 120 us; 10^12, 366 tiles, 211 -> 265)
 #define PL_FINE 400000u  // up to here a tile's start is more than a few percent of it
 
 namespace {
@@ -119,8 +121,10 @@ __global__ __launch_bounds__(PL_PT) void k_plan_counts(pc_plan_args A)
         s += A.work[i];
     const uint64_t total = pc_block_sum<PL_PT>(s, scr);
     uint64_t target = A.tile_work;
-    if (!target)
-        target = max(total / 4096, max(min(total / 1536, (uint64_t)PL_FINE), (uint64_t)PL_MIN));
+    if (!target) {
+        const uint64_t least = max(min(total / PL_FEW, (uint64_t)PL_MIN), (uint64_t)PL_LEAST);
+        target = max(total / 4096, max(min(total / 1536, (uint64_t)PL_FINE), least));
+    }
     target = max(target, total / A.extra + 1); // sum of ceil(work / target) <= extra + rows
     auto pieces = [&](uint32_t i) -> uint32_t {
         uint64_t k = A.tile_work == ~0ull ? 1 : (A.work[i] + target - 1) / target;
