@@ -41,15 +41,17 @@ CUS, LANES, CLOCK_HZ = 256, 64, 2.4e9
 INT_PEAK = CUS * LANES * CLOCK_HZ  # 32-bit integer lane operations per second
 
 # Algorithmic integer operations of the sieve kernel, per unit of work:
-#   crossing an odd multiple of p_b: address, mask, one LDS read-modify-write
+#   crossing a multiple of p_b prime to 30 (8 of 15 odd ones; the bitmap holds no
+#   others): address, mask, one LDS read-modify-write
 #   placing prime p_b in a segment: first multiple by multiply-high reciprocal
 #   a hard leaf or a P2 lookup: 64/32 division by reciprocal (about 12), a
 #   prefix-table read with a masked popcount (4), the signed add (2)
 OPS_CROSSING, OPS_VISIT, OPS_LEAF = 3, 8, 18
-# ... and of the easy-leaf kernel, per work item (one easy leaf, or a run of
-# them sharing pi(u)): a quotient by the fp64 reciprocal with its remainder
-# correction (about 12), a pi-table lookup (4), the signed add (2)
-OPS_EASY_ITEM = 18
+# ... and of the easy-leaf kernels, per work item (one easy leaf, or a run of
+# them sharing pi(u)): a quotient by the fp64 reciprocal (3), a pi-table lookup
+# (4), the add (1), each formed once for the two items (a single and a group
+# value) that read it
+OPS_EASY_ITEM = 4
 
 # Bounded oracle sample of the same workload (same x and y as the GPU line):
 # the special leaves of every B_STEP-th prime p_b (b = 7, 7 + B_STEP, ...)
@@ -428,7 +430,8 @@ def main():
     launches = r.sieve_launches
     avg_launch_ms = k_ms / max(launches, 1)
     visits = r.segments * (r.bmax - r.c)
-    ops = (OPS_CROSSING * r.crossings + OPS_VISIT * visits + OPS_LEAF * (r.n_hard + r.n_p2))
+    crossings = r.crossings * 8 // 15  # of the odd multiples, those prime to 30
+    ops = (OPS_CROSSING * crossings + OPS_VISIT * visits + OPS_LEAF * (r.n_hard + r.n_p2))
     ops_per_launch = ops / max(launches, 1)
     achieved = ops_per_launch / (avg_launch_ms / 1e3)
     roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": INT_PEAK / 1e12,
@@ -436,14 +439,14 @@ def main():
             "traffic": traffic_bytes(x, r.y) if x == X and default_knobs else None,
             "kernel": "k_sieve", "launches": launches, "avg_launch_ms": avg_launch_ms,
             "ops_per_launch": ops_per_launch,
-            "work": {"crossings": r.crossings, "prime_visits": visits, "hard_leaves": r.n_hard,
+            "work": {"crossings": crossings, "prime_visits": visits, "hard_leaves": r.n_hard,
                      "p2_lookups": r.n_p2,
                      "ops_per_unit": {"crossing": OPS_CROSSING, "visit": OPS_VISIT,
                                       "leaf": OPS_LEAF}}}
     # the same kernel against its LDS bound: one atomic read-modify-write per
     # crossing, at the measured rate of the crossing pattern
     lds_peak = lds_rmw_peak()
-    rmw = r.crossings / max(launches, 1)
+    rmw = crossings / max(launches, 1)
     roof_lds = None if not lds_peak else {
         "bound": "lds", "achieved": rmw / (avg_launch_ms / 1e3) / 1e12, "peak": lds_peak / 1e12,
         "unit": "T LDS RMW/s", "frac": rmw / (avg_launch_ms / 1e3) / lds_peak, "kernel": "k_sieve",
@@ -453,7 +456,7 @@ def main():
     roof_easy = {"bound": "alu", "achieved": e_ops / (e_ms / 1e3) / 1e12 if e_ms else None,
                  "peak": INT_PEAK / 1e12, "unit": "T int-ops/s",
                  "frac": e_ops / (e_ms / 1e3) / INT_PEAK if e_ms else None,
-                 "kernel": "k_easy", "launches": 1, "avg_launch_ms": e_ms,
+                 "kernel": "k_easy_primes, k_easy_cands", "launches": 2, "avg_launch_ms": e_ms,
                  "work": {"items": r.n_easy_items, "easy_leaves": r.n_easy,
                           "ops_per_item": OPS_EASY_ITEM}}
 

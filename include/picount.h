@@ -60,7 +60,7 @@ typedef struct {
     double alpha;          /* y = alpha * icbrt(x), clamped to [icbrt x, isqrt x]; 0 = tuned */
     uint32_t segment_kib;  /* LDS bitmap per sieve segment: 32 or 64                       */
     uint32_t wg_size;      /* sieve workgroup: 256|512 (32 KiB segments), 512|1024 (64)   */
-    uint32_t tile_leaves;  /* leaf items per sieve tile (hot segments split by columns); 0 = 2^22, 0xFFFFFFFF = off */
+    uint32_t tile_leaves;  /* work per sieve tile, about its leaf items (hot segments split by columns); 0 = by the launch's work, 0xFFFFFFFF = off */
     uint32_t flags;        /* PC_FLAG_* below */
     uint64_t carry_budget; /* bytes for per-(segment, prime) counts per window; 0 = auto  */
     uint32_t small_span;   /* one-wavefront segments cover [0, small_span * y); 0 = none    */
@@ -85,7 +85,7 @@ typedef struct {
     pc_i128 s1, s2_trivial, s2_easy, s2_hard, p2, phi; /* phi = S1 + S2          */
     uint64_t n_s1, n_trivial, n_easy, n_hard, n_p2;    /* term / leaf counts       */
     uint64_t segments, tiles, windows;
-    uint64_t segment_bits;          /* bits (odd integers) per workgroup segment     */
+    uint64_t segment_bits;          /* bits (integers prime to 30) per workgroup segment */
     uint64_t small_segments;        /* leading one-wavefront segments (of the total) */
     uint64_t crossings;             /* odd multiples of p_{c+1}..p_bmax below the sieve end */
     uint64_t device_bytes;          /* peak device bytes held by the library        */
@@ -109,7 +109,7 @@ typedef struct {
 /* pi(x) for 0 <= x < 2^64 (Section 1).  alpha selects y = alpha*icbrt(x)
  * (Section 2: y_max = alpha x^(1/3)), clamped to [icbrt x, isqrt x]; alpha = 0
  * picks a tuned value; alpha < 0 or NaN -> PC_EINVAL.  pi(0) = pi(1) = 0.
- * Small x (x < 2^20) is answered from the device pi table. */
+ * Small x (x < 2^20) is answered from the host copy of the pi table. */
 pc_status pc_pi_count(uint64_t x, double alpha, uint64_t *pi_out);
 
 /* As pc_pi_count with explicit knobs (cfg may be NULL) and the full
@@ -163,9 +163,9 @@ pc_status pc_pi_count_batch_ex(const uint64_t *xs, size_t n, const pc_config *cf
  *
  * pc_workspace_bytes: device bytes of workspace that
  * pc_pi_count_batch_async needs for these n queries (host array xs).  The
- * figure covers each round's uploaded arrays (query scalars, block tables
- * and sieve tiles: 16 bytes per segment of every query, a few hundred bytes
- * per query), one round arena (per-segment counts and weights of a round's
+ * figure covers each round's uploaded arrays (query scalars, block tables and
+ * row offsets: 8 bytes per segment of every query, a few hundred bytes per
+ * query), one round arena (16 bytes per sieve tile, per-segment counts and weights of a round's
  * queries, 8 bytes per segment per sieving prime, bounded by the 6 GiB round
  * budget, plus each query's per-prime arrays) and 16 bytes per query answered
  * on the host.  n = 0 gives 0.  Returns SIZE_MAX on error (xs null with

@@ -1881,7 +1881,7 @@ void run_batch(const uint64_t *xs, size_t n, const Knobs &K, double alpha, bool 
 
 // ---------------------------------------------------------------------------
 // Batches in caller memory.  The caller's workspace holds, in this order, each
-// round's uploaded arrays (query scalars, tiles, block tables, output
+// round's uploaded arrays (query scalars, row offsets, block tables, output
 // positions), the results known on the host ((position, value) pairs: x below
 // the sieve threshold, and queries too large for a round, computed windowed
 // during the call), the error flag, and one round arena that the rounds reuse

@@ -376,7 +376,7 @@ __device__ __forceinline__ uint32_t pc_band_of(const uint64_t *off, uint32_t nba
 // its own, and four table reads are in flight.
 //
 // Integer issue bounds it, and the table reads (L2-resident, u <= y) close
-// behind: one pi(10^18) takes 4.4 ms (12.2 ms with singles and groups summed
+// behind: one pi(10^18) takes 4.0 ms (4.3 beside the candidates; 12.2 with singles and groups summed
 // apart and a remainder test per quotient).
 template <int NT>
 __device__ __forceinline__ void pc_easy_primes(const pc_tables &T, const pc_query &Q, uint64_t lb,
@@ -450,7 +450,7 @@ __device__ __forceinline__ void pc_easy_primes(const pc_tables &T, const pc_quer
 // leaf of the band's first b (lpf(m) > p_b; a third of them where p_b^2 is
 // near y), packed in LDS, and then each thread takes one m, with 1/m formed
 // once, against the b of the band.  (One item per (b, m), the table tested for
-// each, took 6.3 ms of one pi(10^18); this takes 3.4 ms beside the prime leaves.)
+// each, took 6.3 ms of one pi(10^18); this takes 0.7 ms, 3.8 beside the prime leaves.)
 template <int NT> struct pc_cand_lds {
     uint32_t m[PC_EZ_TILE]; // m's wheel number | (mu(m) > 0) << 31
     uint32_t l[PC_EZ_TILE]; // lpf(m)
