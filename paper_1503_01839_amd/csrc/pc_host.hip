@@ -928,13 +928,20 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     auto leaves = [&]() {
         const hipStream_t st = early ? g_stream2 : g_stream;
         const uint32_t nblk = (uint32_t)std::clamp<uint64_t>(y / 256, 256, 4096);
+        const uint32_t ns1 = (uint32_t)std::min<uint64_t>(2048, y / 256 + 1);
+        // one launch for all three up to 512 segments (pi(10^9) 128 -> 109 us, 10^14,
+        // 365 segments, 440 -> 428; 10^15, 848, 1.00 -> 1.02 ms: there the
+        // kernels' work counts, and each apart has its own registers); a caller
+        // that reads times gets S1 and the easy leaves apart
+        if (nseg <= 512 && !want_times) {
+            hipck(hipEventRecord(g_fork, g_stream), "hipEventRecord");
+            hipck(hipStreamWaitEvent(g_stream2, g_fork, 0), "hipStreamWaitEvent");
+            hipck(pc_launch_leaves(T, Q, nblk, ns1, g_stream2), "leaves");
+            hipck(hipEventRecord(g_join, g_stream2), "hipEventRecord");
+            return;
+        }
         auto s1 = [&]() {
-            ev_s1 = timed(
-                [&] {
-                    hipck(pc_launch_s1(T, Q, (uint32_t)std::min<uint64_t>(2048, y / 256 + 1), st),
-                          "S1");
-                },
-                st);
+            ev_s1 = timed([&] { hipck(pc_launch_s1(T, Q, ns1, st), "S1"); }, st);
         };
         if (!early)
             s1();

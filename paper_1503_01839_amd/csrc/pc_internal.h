@@ -192,6 +192,9 @@ hipError_t pc_launch_lookup(const uint2 *pitab, const uint64_t *in, uint32_t n, 
 // ranges and bands) and the easy kernels use the arrays named in pc_query.
 hipError_t pc_launch_s1(const pc_tables &T, const pc_query &Q, uint32_t nblocks, hipStream_t s);
 hipError_t pc_launch_leaf_setup(const pc_tables &T, const pc_query &Q, hipStream_t s);
+// S1 and the easy leaves in one launch: 2 neasy + ns1 workgroups
+hipError_t pc_launch_leaves(const pc_tables &T, const pc_query &Q, uint32_t neasy, uint32_t ns1,
+                            hipStream_t s);
 hipError_t pc_launch_easy_cands(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
                                 hipStream_t s);
 hipError_t pc_launch_easy_primes(const pc_tables &T, const pc_query &Q, uint32_t nblocks,
