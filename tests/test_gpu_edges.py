@@ -53,3 +53,13 @@ def test_easy_ranges_over_y(pc, x):
     for y in ys:
         if lo <= y <= hi:
             check(pc, x, y)
+
+
+@pytest.mark.parametrize("alpha,apart", [(4.0, True), (5.0, False), (0.0, False)])
+def test_leaves_in_one_launch(pc, alpha, apart):
+    # S1 and the easy leaves share a launch up to 512 segments unless times are asked for
+    x = 10**14
+    print("case: leaves in one launch", alpha, flush=True)
+    r = pc.pi_count_ex(x, alpha=alpha)  # reads times: apart
+    assert (r.segments > 512) == apart
+    assert pc.pi_count(x, alpha) == r.pi == 3204941750802  # Table 1
