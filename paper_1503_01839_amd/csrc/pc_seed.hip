@@ -25,7 +25,10 @@ namespace {
 
 constexpr uint32_t SEED_T = 1024;   // threads per workgroup of the term kernel
 constexpr uint32_t SCAN_T = 1024;   // threads of the prefix-sum workgroup
-constexpr uint32_t SCAN_PER = 8;    // terms each of them takes at a time
+// terms each of them takes at a time: more loads in flight against more cache
+// lines per load (phi_seed at 3 * 10^10, 20000 columns: 1: 103 us, 2: 90, 4: 86.5,
+// 8: 91, 16: 96)
+constexpr uint32_t SCAN_PER = 4;
 // Children of a column that expand, and the first: p_i < p_b and p_i^3 <= m / p_b, so
 // p_i <= m^(1/4) <= 2^12 for m <= 2^48: fewer than pi(2^12) = 564
 constexpr uint32_t SEED_A = 568;
@@ -139,7 +142,7 @@ __device__ int64_t seed_phi(const seed_ctx &S, uint64_t v, uint32_t k, const uin
 // workgroup shares out their own children, the pairs i2 < i of the first A primes, so that no thread walks a whole child's tree.  Bound by
 // latency: a chain of a division and a pi-table read per node, up to 46 nodes
 // a pair at m = 2 * 10^10, so every column gets 16 wavefronts and reads its
-// primes from LDS (phi_seed at 2 * 10^10, 15000 columns: 300 -> 78 us; the
+// primes from LDS (phi_seed at 2 * 10^10, 15000 columns: 300 -> 76 us; the
 // triangle over all children, most of its pairs empty, took 224 us of it).
 __global__ __launch_bounds__(SEED_T) void k_seed_terms(seed_ctx S, uint64_t m, uint32_t nb,
                                                        uint32_t nrec, int64_t *term)
