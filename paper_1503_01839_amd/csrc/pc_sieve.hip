@@ -56,7 +56,7 @@ template <int LOG2_S, int T, int CH> constexpr int pc_sieve_waves_per_simd()
 {
     constexpr long NW = (1l << LOG2_S) / 32, NWV = T / 64;
     constexpr long lds = 4 * (NW + 16) + 4 * (T + 1) + 4 * pc_sieve_gcap<T>() + 4 * 2 * 64 +
-                         4 * (CH + 1) + 22 * CH + 16 * (CH / 64) + 8 + 4 * NWV + 16 * NWV;
+                         4 * (CH + 1) + (LOG2_S > 18 ? 24 : 22) * CH + 16 * (CH / 64) + 8 + 4 * NWV + 16 * NWV;
     // (the CU hands LDS out in pieces of 1280 bytes)
     constexpr long wg = 163840 / ((lds + 1279) / 1280 * 1280);
     constexpr long waves = wg * NWV < 32 ? wg * NWV : 32;
@@ -117,9 +117,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     __shared__ uint32_t c_rem[CH];     // (lo / 30) mod p_b
     __shared__ uint32_t c_ls[CH];      // first leaf item (m, or index of the prime m)
     __shared__ uint32_t c_lc[CH];      // leaf items; PC_CAND: items are candidates (pc_wheel_m)
-    // integers first removed by p_b in this segment, two columns a word (p_b >=
-    // 17 removes at most 2^19 / 17; smaller p_b belong to y < 13, z < 1100)
-    __shared__ uint32_t c_new[CH / 2];
+    // integers first removed by p_b in this segment.  A crossing removes over the
+    // whole segment, at most S / p_b of its bits, and p_b = 7 is crossed by a
+    // wheel of 3 primes: two columns share a word while S / 7 < 2^16 (2^18 / 7 =
+    // 37449; of 2^19 bits it removes 74898)
+    constexpr bool NEW16 = S / 7 < 65536;
+    __shared__ uint32_t c_new[NEW16 ? CH / 2 : CH];
     __shared__ int32_t c_w[CH];        // sum of -mu(m) over the leaves of the column
     __shared__ uint64_t c_leafy[CH / 64];
     __shared__ uint64_t c_heavy[CH / 64];
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             s_first_large = jall;
             s_first_skip = jall;
         }
-        if (tid < CH / 2)
+        if (tid < (NEW16 ? CH / 2 : CH))
             c_new[tid] = 0;
         __syncthreads();
         // --- one lane per column: first multiple, leaf range ---
@@ -598,8 +601,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         uint32_t cg0 = 0x80000000u, v_p = 1, v_r = 0, v_j = 0, v_d = RSI, v_rem = 0;
             // (j - cg0 >= 64: reload)
         auto flush_removed = [&]() {
+            const uint32_t col = cg0 + lane;
             if (v_rem)
-                atomicAdd(&c_new[(cg0 + lane) >> 1], v_rem << (((cg0 + lane) & 1u) * 16u));
+                atomicAdd(&c_new[NEW16 ? col >> 1 : col], NEW16 ? v_rem << ((col & 1u) * 16u) : v_rem);
             v_rem = 0;
         };
         auto load_group = [&](uint32_t j) { // the columns from j on
@@ -1128,7 +1132,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         __syncthreads(); // c_new complete; every wave is past the last window
         // --- chunk results: cnt before each crossing, and w ---
         {
-            const uint32_t v = tid < jend ? (c_new[tid >> 1] >> ((tid & 1u) * 16u)) & 0xFFFFu : 0u;
+            const uint32_t v = tid >= jend ? 0u
+                               : NEW16     ? (c_new[tid >> 1] >> ((tid & 1u) * 16u)) & 0xFFFFu
+                                           : c_new[tid];
             uint32_t tot;
             const uint32_t ex = pc_block_excl_scan<T>(v, scr32, &tot);
             const uint32_t col = cb + tid;
