@@ -317,6 +317,10 @@ void ensure_pi(uint64_t need)
         nent = 1ull << 26;
         covered = k2_32;
     }
+    // (each table counts as unbuilt from here until it is queued again: ensure
+    // frees the old one before it allocates, and may fail)
+    T.pi_limit = T.nprimes = T.recip_n = 0; // the primes are rebuilt too
+    T.k32 = ~0ull;
     ensure(T.pitab, nent * 8, "pi table");
     ensure(T.cnt_tmp, nent * 4, "pi counts");
     ensure(T.scan_tmp, (nent / 4096 + 2) * 4, "scan");
@@ -334,12 +338,9 @@ void ensure_pi(uint64_t need)
           "pi table");
     if (T.cnt_tmp.cap > (1ull << 30)) // up to 2^32 (256 MiB) kept for the next build
         dfree(T.cnt_tmp);
-    T.pi_limit = covered;
-    T.nprimes = lookup({covered})[0];
-    T.k32 = covered > k2_32 ? kK32 : ~0ull;
+    const uint64_t nprimes = lookup({covered})[0];
     if (covered > k2_32 && lookup({k2_32})[0] + 1 != kK32)
         fail(PC_EINTERNAL, "pi(2^32) of the device table is not 203280221");
-    T.recip_n = 0; // the primes array was rebuilt
     // the host copy answers the staircase's pi(isqrt(x / lo)): below 2^24 for
     // x < 2^64, at most 2^28 for the queries up to 2^72 (tables above 2^32)
     const uint64_t nh =
@@ -361,6 +362,9 @@ void ensure_pi(uint64_t need)
           "D2H");
     hipck(hipStreamSynchronize(g_stream), "sync");
     T.pi_host_max = 64 * nh - 1;
+    T.pi_limit = covered;
+    T.nprimes = nprimes;
+    T.k32 = covered > k2_32 ? kK32 : ~0ull;
 }
 
 // Row lengths of the count staircase of a query (x, c, nb): a hard leaf of
@@ -394,6 +398,7 @@ void ensure_recip(uint64_t kmax)
     // (the reciprocal tables cover primes below 2^32 only: p_a+1 < 2^31 for every y)
     uint64_t k = std::min<uint64_t>(std::min(T.nprimes, T.k32 - 1),
                                     std::max<uint64_t>(kmax, 2 * T.recip_n));
+    T.recip_n = 0;
     ensure(T.recip, (k + 1) * 8, "reciprocals");
     ensure(T.rcpd, (k + 1) * 8, "reciprocals");
     hipck(pc_launch_recip(ptr<uint32_t>(T.primes), ptr<uint64_t>(T.recip), ptr<double>(T.rcpd),
@@ -438,6 +443,7 @@ void ensure_mulpf(uint64_t y)
         fail(PC_ERANGE, "y beyond 2^31 - 2");
     ensure_pi(Y);
     uint64_t nsmall = lookup({pc_isqrt(Y)})[0];
+    T.y_limit = 0;
     ensure(T.mulpf, (Y + 1) * 4, "mu*lpf table");
     hipck(pc_launch_mulpf(ptr<uint32_t>(T.primes), (uint32_t)nsmall, Y, ptr<int32_t>(T.mulpf),
                           g_stream),
@@ -452,8 +458,7 @@ void ensure_mulpf(uint64_t y)
     hipck(hipMemcpyAsync(&nsq, T.chk.p, 8, hipMemcpyDeviceToHost, g_stream), "D2H");
     hipck(hipStreamSynchronize(g_stream), "sync");
     if (nsq != squarefree_count(Y)) {
-        dfree(T.mulpf);
-        T.y_limit = 0; // rebuilt by the next call that needs it
+        dfree(T.mulpf); // rebuilt by the next call that needs it
         fail(PC_EINTERNAL, "mu*lpf table: " + std::to_string(nsq) + " squarefree entries up to " +
                                std::to_string(Y) + ", expected " +
                                std::to_string(squarefree_count(Y)));
@@ -529,6 +534,7 @@ void ensure_mulpfw(uint64_t y)
             d *= set >> i & 1 ? kFirstPrimes[i + 1] : 1;
         n += __builtin_popcount(set) & 1 ? -(Y / d) : Y / d;
     }
+    T.w_limit = 0;
     ensure(T.mulpfw, n * 4, "mu*lpf table by the wheel");
     hipck(pc_launch_mulpfw(tables_view(kWheelC), n, ptr<int32_t>(T.mulpfw), g_stream),
           "mu*lpf table by the wheel");
