@@ -66,7 +66,7 @@ struct pc_query {
     uint64_t Qc, recip_Qc;
     uint32_t c, a, bmax, nb, ncol;
     uint32_t kx;            // pi(isqrt(x))
-    const uint64_t *Xb;     // Xb[b] = floor(x / p_b) modulo 2^64, 1-based, b <= a
+    const uint64_t *Xb;     // Xb[b] = floor(x / p_b) modulo 2^64, 1-based, b <= a and the sieving primes
     uint32_t *Xbh;          // its high word (above 2^64; null: every X_b < 2^64)
     uint64_t sieve_end;     // the sieve covers [0, sieve_end): segments * pc_seg_span
     uint64_t nseg;          // segments (rows of cnt and wgt when the query has one window)

@@ -14,7 +14,7 @@
 #include "pc_internal.h"
 #include "pc_leafrange.h"
 
-// X_b = floor(x / p_b) for 0 <= b <= a (X_0 = x): its low word, its high
+// X_b = floor(x / p_b), 1 <= b <= a + 1 (X_0 = x): its low word, its high
 // word (above 2^64, when Xbh is not null) and its value in fp64.
 __device__ __forceinline__ pc_xv pc_xb_item(const pc_tables &T, const pc_query &Q, uint32_t b)
 {
@@ -156,11 +156,13 @@ struct pc_setup_sums {
 __device__ __forceinline__ void pc_leaf_setup_band(const pc_tables &T, const pc_query &Q,
                                                    uint32_t b, pc_setup_sums *S)
 {
-    const bool known = b <= Q.a || b <= Q.c + Q.nb;
+    // y + 1 >= isqrt z: a sieving prime past p_a is p_{a+1} = y + 1 (z >= (y + 1)^2,
+    // so x is just below (y + 1)^3; x = 294, y = 6).  It has no leaf, but the
+    // sieve forms its range, so its X_b is set too.
     pc_xv X{};
-    if (b <= Q.a)
+    if (b <= Q.a || b <= Q.c + Q.nb)
         X = pc_xb_item(T, Q, b);
-    if (known && b > Q.c && b <= Q.c + Q.nb) { // a sieving prime (nb <= a - c: y >= isqrt z)
+    if (b > Q.c && b <= Q.c + Q.nb) { // a sieving prime
         const uint64_t p = T.primes[b], rp = T.recip[b];
         // odd multiples k p_b, k odd, below the sieve end
         S->cross += (pc_div(Q.sieve_end - 1, p, rp) + 1) / 2;
