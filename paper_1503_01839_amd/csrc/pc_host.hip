@@ -1709,6 +1709,7 @@ void submit_round(BatchSlot &sl, const Knobs &K, bool use_graph)
         if (sl.h_fin)
             (void)hipHostFree(sl.h_fin);
         sl.h_fin = nullptr;
+        sl.h_fin_cap = 0;
         hipck(hipHostMalloc((void **)&sl.h_fin, nq * sizeof(pc_final)), "hipHostMalloc");
         sl.h_fin_cap = nq;
     }
@@ -1751,8 +1752,8 @@ void submit_round(BatchSlot &sl, const Knobs &K, bool use_graph)
     sl.busy = true;
 }
 
-// After the slot's event: results to out[], graph released, slot free.
-void collect_round(BatchSlot &sl, uint64_t *out)
+// The round's graph released, the slot free.
+void slot_idle(BatchSlot &sl)
 {
     if (sl.exec)
         (void)hipGraphExecDestroy(sl.exec);
@@ -1761,6 +1762,12 @@ void collect_round(BatchSlot &sl, uint64_t *out)
     sl.exec = nullptr;
     sl.graph = nullptr;
     sl.busy = false;
+}
+
+// After the slot's event: results to out[], slot free.
+void collect_round(BatchSlot &sl, uint64_t *out)
+{
+    slot_idle(sl);
     if (*sl.h_err)
         fail(PC_EINTERNAL, "a leaf or P2 quotient fell outside its segment (batch)");
     for (size_t i = 0; i < sl.R.size(); i++) {
@@ -1867,6 +1874,12 @@ void run_batch(const uint64_t *xs, size_t n, const Knobs &K, double alpha, bool 
     const std::vector<BatchQuery> big = plan_queries(xs, n, alpha, out);
     // rounds in input order, each within the carry budget
     BatchSlot &sl = g_slot;
+    if (!sl.R.empty()) { // left by a call that failed part way: positions in its results
+        hipck(hipStreamSynchronize(g_stream), "sync");
+        slot_idle(sl);
+        sl.R.clear();
+        sl.bytes = 0;
+    }
     auto flush = [&]() {
         if (sl.R.empty())
             return;
