@@ -2666,21 +2666,28 @@ pc_status pc_phi_seed(uint64_t m, uint32_t c, uint32_t b_hi, uint64_t *out)
                              ptr<int64_t>(B.seed_term), d_out,
                              reinterpret_cast<int32_t *>(d_out + nb + 1), g_stream),
               "seeds");
+        // out is written once the flag is known to be clear
         int32_t err = 0;
+        const char *st = nullptr;
         if (n_out <= ((size_t)4 << 20)) { // through pinned memory (a chunk of the arena)
             g_pin.reset();
-            char *const st = static_cast<char *>(g_pin.take(n_out + 8));
-            hipck(hipMemcpyAsync(st, d_out, n_out + 8, hipMemcpyDeviceToHost, g_stream), "D2H");
+            char *const pin = static_cast<char *>(g_pin.take(n_out + 8));
+            hipck(hipMemcpyAsync(pin, d_out, n_out + 8, hipMemcpyDeviceToHost, g_stream), "D2H");
             hipck(hipStreamSynchronize(g_stream), "sync");
-            memcpy(out, st, n_out);
-            memcpy(&err, st + n_out, 4);
+            memcpy(&err, pin + n_out, 4);
+            st = pin;
         } else {
-            hipck(hipMemcpyAsync(out, d_out, n_out, hipMemcpyDeviceToHost, g_stream), "D2H");
             hipck(hipMemcpyAsync(&err, d_out + nb + 1, 4, hipMemcpyDeviceToHost, g_stream), "D2H");
             hipck(hipStreamSynchronize(g_stream), "sync");
         }
         if (err)
             fail(PC_EINTERNAL, "seeds: pi table too short, stack too deep or a negative phi");
+        if (st) {
+            memcpy(out, st, n_out);
+        } else {
+            hipck(hipMemcpyAsync(out, d_out, n_out, hipMemcpyDeviceToHost, g_stream), "D2H");
+            hipck(hipStreamSynchronize(g_stream), "sync");
+        }
     });
 }
 

@@ -152,6 +152,13 @@ hipError_t pc_launch_batch_finish(const pc_query *Q, const uint32_t *, const uin
     }
     return hipSuccess;
 }
+hipError_t pc_launch_seed(const pc_tables &, uint32_t, uint64_t, uint32_t nb, uint32_t, uint64_t, int64_t *,
+                          uint64_t *out, int32_t *err, hipStream_t)
+{
+    std::fill(out, out + nb + 1, 77);
+    *err |= 16; // an inconsistency found on the device
+    return hipSuccess;
+}
 // --- and those that no case looks at ---
 #define NOP(name, ...) hipError_t name(__VA_ARGS__) { return hipSuccess; }
 using PT = const pc_tables &;
@@ -170,7 +177,6 @@ NOP(pc_launch_plan, const pc_plan_args &, hipStream_t)
 NOP(pc_launch_sieve, const pc_sieve_args &, U, U, int, hipStream_t)
 NOP(pc_launch_sieve_tiny, PT, PQ, hipStream_t)
 NOP(pc_launch_scan, const pc_scan_args &, int, hipStream_t)
-NOP(pc_launch_seed, PT, U, uint64_t, U, U, uint64_t, int64_t *, uint64_t *, int32_t *, hipStream_t)
 NOP(pc_launch_combine, const pc_sums *, PQ, uint64_t, const int32_t *, pc_back *, hipStream_t)
 NOP(pc_launch_batch_setup, PT, const pc_query *, UP, UP, U, UP, UP, U, U, hipStream_t)
 NOP(pc_launch_batch_easy, PT, const pc_query *, UP, UP, U, hipStream_t)
@@ -266,6 +272,16 @@ static void case_batch()
     }
 }
 
+// Seeds that the device found inconsistent are not written out.
+static void case_seeds()
+{
+    for (uint32_t b_hi : {1000u, 600000u}) { // through pinned memory, and past it (4 MiB)
+        std::vector<uint64_t> out(b_hi - 5, 1);
+        CHECK(pc_phi_seed(1000000, 6, b_hi, out.data()) == PC_EINTERNAL, "b_hi %u: status", b_hi);
+        CHECK(std::count(out.begin(), out.end(), 1) == (long)out.size(), "b_hi %u: written", b_hi);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string c = argc > 1 ? argv[1] : "";
@@ -273,6 +289,8 @@ int main(int argc, char **argv)
         case_tables();
     else if (c == "batch")
         case_batch();
+    else if (c == "seeds")
+        case_seeds();
     else
         CHECK(false, "no such case");
     if (!g_fails)

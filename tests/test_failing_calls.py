@@ -22,7 +22,7 @@ def exe(tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("case", ["tables", "batch"])
+@pytest.mark.parametrize("case", ["tables", "batch", "seeds"])
 def test_next_call_after_a_failure(exe, case):
     r = subprocess.run([exe, case], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "OK" in r.stdout, r.stdout + r.stderr
