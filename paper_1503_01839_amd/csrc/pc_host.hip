@@ -793,17 +793,21 @@ uint64_t planned_rows(uint64_t y, uint64_t z, uint64_t base, uint64_t span, uint
     return std::min(rows, std::max<uint64_t>(n, rows <= 4096 ? rows : 0));
 }
 
-// How many tiles cutting may add to a launch (pc_plan_args::extra): at least
-// twice the launch's work over the least work of a tile, 8192, by a rough
-// count of it (300 items per unit of y, 440 per stored cell), so that the
-// launch carries few empty tiles.
+// How many tiles cutting may add to a launch (pc_plan_args::extra), by a rough
+// count of the launch's work (300 items per unit of y, 440 per stored cell): one
+// per 4096 of it, or per tile_work if the caller asks for smaller tiles.  The
+// launch carries as many empty tiles as it leaves unused (2^17 of them, whatever
+// the query, made a caller's tile_leaves cost 100 us and more: pi(10^9) at 2^16
+// 322 -> 162 us).
 uint32_t plan_extra(uint64_t ysum, uint64_t cells, uint64_t tile_work)
 {
     if (tile_work == ~0ull)
         return 1;
-    if (tile_work)
-        return 1u << 17;
-    return (uint32_t)std::clamp<uint64_t>((300 * ysum + 440 * cells) / 4096, 64, 4096);
+    const uint64_t work = 300 * ysum + 440 * cells;
+    const uint64_t by_rule = std::clamp<uint64_t>(work / 4096, 64, 4096);
+    if (!tile_work)
+        return (uint32_t)by_rule;
+    return (uint32_t)std::clamp<uint64_t>(work / tile_work, by_rule, 1u << 17);
 }
 
 // the caller's tile_leaves as pc_plan_args::tile_work

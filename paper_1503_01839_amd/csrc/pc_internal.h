@@ -223,7 +223,7 @@ struct pc_plan_args {
     const pc_query *Qs;
     const uint32_t *order, *pfx_plan, *pfx_rest;
     uint64_t seg_first, lo_base, seg_base; // as pc_sieve_args
-    uint64_t tile_work; // work of a tile; 0: by the launch's work, ~0: no cuts
+    uint64_t tile_work; // at most this work a tile; 0: by the launch's work alone, ~0: no cuts
     uint64_t *work;     // np: estimated work
     uint2 *cut;         // np: tiles, the first one's index
     uint32_t *nplanned; // tiles of the planned rows

@@ -124,11 +124,10 @@ __global__ __launch_bounds__(PL_PT) void k_plan_counts(pc_plan_args A)
     for (uint32_t i = t; i < A.np; i += PL_PT)
         s += A.work[i];
     const uint64_t total = pc_block_sum<PL_PT>(s, scr);
-    uint64_t target = A.tile_work;
-    if (!target) {
-        const uint64_t least = max(min(total / PL_FEW, (uint64_t)PL_MIN), (uint64_t)PL_LEAST);
-        target = max(total / 4096, max(min(total / 1536, (uint64_t)PL_FINE), least));
-    }
+    const uint64_t least = max(min(total / PL_FEW, (uint64_t)PL_MIN), (uint64_t)PL_LEAST);
+    uint64_t target = max(total / 4096, max(min(total / 1536, (uint64_t)PL_FINE), least));
+    if (A.tile_work) // a caller's bound: tiles of less, not of more than the rule's (2^22,
+        target = min(target, A.tile_work); // taken as it is, left pi(10^12) in one tile a row: 2.51 ms)
     target = max(target, total / A.extra + 1); // sum of ceil(work / target) <= extra + rows
     auto pieces = [&](uint32_t i) -> uint32_t {
         uint64_t k = A.tile_work == ~0ull ? 1 : (A.work[i] + target - 1) / target;
