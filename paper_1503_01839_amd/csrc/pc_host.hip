@@ -190,16 +190,6 @@ struct PinnedArena {
 };
 PinnedArena g_pin;
 
-// n bytes from host memory src to device memory dst, queued on s through the arena
-void h2d(void *dst, const void *src, size_t n, hipStream_t s, const char *what)
-{
-    if (n == 0)
-        return;
-    void *st = g_pin.take(n);
-    memcpy(st, src, n);
-    hipck(hipMemcpyAsync(dst, st, n, hipMemcpyHostToDevice, s), what);
-}
-
 // n bytes from device memory src into host memory dst, through the arena;
 // waits for s
 void d2h_sync(void *dst, const void *src, size_t n, hipStream_t s, const char *what)
@@ -1049,15 +1039,12 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     FILE *trace_file = nullptr;
     if (const char *tp = std::getenv("PICOUNT_TILE_TRACE"))
         trace_file = std::fopen(tp, "a");
-    std::vector<pc_tile> tiles_a;
-    uint64_t ntiles_a = 0;
     uint64_t *cin = ptr<uint64_t>(B.carry_a), *cout = ptr<uint64_t>(B.carry_b);
     const int bflag = K.batch ? 0 : 0x100;
     bool first_window = true;
     if (c < 3) { // y < 5: the bitmap needs 2, 3 and 5 in the wheel; z < 32 here
         ev_sieve.push_back(
             timed([&] { hipck(pc_launch_sieve_tiny(T, Q, g_stream), "sieve"); }));
-        ntiles_a = 1;
     }
     for (uint64_t wi = 0; wi < (c < 3 ? 0 : nwin); wi++) {
         // seeded windows need nothing from each other: they run last to first
@@ -1107,44 +1094,43 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
             hipck(pc_launch_prep(P, g_stream), "plan");
         }
         // rows [r0, min(r1, nA)) are small segments, the rest workgroup segments
-        tiles_a.clear();
-        for (uint64_t r = r0; r < std::min(r1, nA); r++)
-            tiles_a.push_back(pc_tile{(uint32_t)r, 0, Q.ncol, 0});
-        size_t tiles_b = 0;
-        if (r1 > nA) {
-            const uint64_t b0 = std::max(r0, nA), lo0 = baseB + (b0 - nA) * spanB;
+        const uint64_t rA = std::min(r1, std::max(r0, nA)); // the first workgroup segment
+        auto plan = [&](DevBuf &tiles, uint64_t first, uint64_t end, uint64_t base, uint64_t seg_base,
+                        uint32_t log2s) -> uint32_t {
+            if (first == end)
+                return 0;
+            const uint64_t span = pc_seg_span(log2s), n = end - first;
             pc_plan_args P{};
             P.T = T;
             P.Qs = ptr<pc_query>(B.qdev);
-            P.seg_first = b0;
-            P.lo_base = baseB;
-            P.seg_base = nA;
+            P.seg_first = first;
+            P.lo_base = base;
+            P.seg_base = seg_base;
             P.tile_work = plan_tile_work(K);
             P.nq = 1;
-            P.np = (uint32_t)planned_rows(y, z, lo0, spanB, r1 - b0);
-            P.nrest = (uint32_t)(r1 - b0 - P.np);
+            P.np = (uint32_t)planned_rows(y, z, base + (first - seg_base) * span, span, n);
+            P.nrest = (uint32_t)(n - P.np);
             P.extra = plan_extra(y, max_cells, P.tile_work);
             P.ntiles = P.np + P.nrest + P.extra;
-            P.seg_log2 = K.seg_log2;
-            tiles_b = P.ntiles;
+            P.seg_log2 = log2s;
             ensure(B.work, (size_t)P.np * 16, "tile plan");
-            ensure(B.tiles, tiles_b * sizeof(pc_tile), "tiles");
+            ensure(tiles, (size_t)P.ntiles * sizeof(pc_tile), "tiles");
             P.work = ptr<uint64_t>(B.work);
             P.cut = reinterpret_cast<uint2 *>(P.work + P.np);
             P.tile_count = ptr<uint32_t>(B.err) + 1;
             P.nplanned = ptr<uint32_t>(B.err) + 2;
-            P.tiles = ptr<pc_tile>(B.tiles);
+            P.tiles = ptr<pc_tile>(tiles);
             hipck(pc_launch_plan(P, g_stream), "tile plan");
-        }
-        ntiles_a += tiles_a.size();
-        ensure(B.tiles_a, tiles_a.size() * sizeof(pc_tile), "tiles");
-        h2d(B.tiles_a.p, tiles_a.data(), tiles_a.size() * sizeof(pc_tile), g_stream, "tiles");
+            return P.ntiles;
+        };
+        const uint32_t tiles_a = plan(B.tiles_a, r0, rA, 0, 0, K.hot_log2);
+        const uint32_t tiles_b = plan(B.tiles, rA, r1, baseB, nA, K.seg_log2);
         auto sieve_args = [&](bool small) {
             pc_sieve_args A{};
             A.T = T;
             A.Qs = ptr<pc_query>(B.qdev);
             A.tiles = ptr<pc_tile>(small ? B.tiles_a : B.tiles);
-            A.ntiles = (uint32_t)(small ? tiles_a.size() : tiles_b);
+            A.ntiles = small ? tiles_a : tiles_b;
             A.seg0 = r0;
             A.lo_base = small ? 0 : baseB;
             A.seg_base = small ? 0 : nA;
@@ -1237,7 +1223,7 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     const pc_sums &hs = g_back->sums;
     const double ms_sieve = ms_since(t2);
     const int32_t err = g_back->err[0];
-    const uint64_t ntiles_total = ntiles_a + (uint32_t)g_back->err[1];
+    const uint64_t ntiles_total = c < 3 ? 1 : (uint32_t)g_back->err[1];
     if (err & 1)
         fail(PC_EINTERNAL, "look-back scan did not complete");
     if (err & 8)
