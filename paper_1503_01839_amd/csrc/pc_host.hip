@@ -789,11 +789,13 @@ uint64_t planned_rows(uint64_t y, uint64_t z, uint64_t base, uint64_t span, uint
 // launch carries as many empty tiles as it leaves unused (2^17 of them, whatever
 // the query, made a caller's tile_leaves cost 100 us and more: pi(10^9) at 2^16
 // 322 -> 162 us).
+uint64_t rough_work(uint64_t y, uint64_t cells) { return 300 * y + 440 * cells; }
+
 uint32_t plan_extra(uint64_t ysum, uint64_t cells, uint64_t tile_work)
 {
     if (tile_work == ~0ull)
         return 1;
-    const uint64_t work = 300 * ysum + 440 * cells;
+    const uint64_t work = rough_work(ysum, cells);
     const uint64_t by_rule = std::clamp<uint64_t>(work / 4096, 64, 4096);
     if (!tile_work)
         return (uint32_t)by_rule;
@@ -1539,15 +1541,24 @@ void plan_round(const std::vector<BatchQuery> &R, const Knobs &K, RoundPlan &P)
     P.np = P.nrest = 0;
     uint64_t ysum = 0, cells = 0;
     std::vector<uint32_t> pp{0}, pr{0};
+    for (uint32_t i = 0; i < nq; i++) {
+        ysum += R[i].y;
+        cells += P.cells[i];
+    }
     for (uint32_t i : order) {
         const BatchQuery &b = R[i];
-        const uint64_t n = planned_rows(b.y, b.z, 0, pc_seg_span(kBatchLog2S), b.nseg);
+        // a query of one row, and of less work than one of the 768 workgroups' share
+        // of the round, has nothing to gain from a cut, and many of them cost the
+        // planner a workgroup each (16384 queries of 10^6.1 .. 10^7: 7.40 -> 7.21 ms, 1024
+        // of them 752 -> 700 us; of several rows cuts do pay: 1024 queries of 10^11 ..
+        // 10^12 without them 7.62 ms, 6.21 with)
+        const bool whole = plan_tile_work(K) == 0 && b.nseg == 1 &&
+                           768 * rough_work(b.y, P.cells[i]) <= rough_work(ysum, cells);
+        const uint64_t n = whole ? 0 : planned_rows(b.y, b.z, 0, pc_seg_span(kBatchLog2S), b.nseg);
         P.np += (uint32_t)n;
         P.nrest += (uint32_t)(b.nseg - n);
         pp.push_back(P.np);
         pr.push_back(P.nrest);
-        ysum += b.y;
-        cells += P.cells[i];
     }
     P.t_ord = P.blk.size();
     P.blk.insert(P.blk.end(), order.begin(), order.end());

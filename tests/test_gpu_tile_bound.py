@@ -18,3 +18,17 @@ def test_a_large_bound_changes_nothing(pc, x):
     assert small.pi == r.pi and small.tiles >= r.tiles
     off = pc.pi_count_ex(x, tile_leaves=OFF)
     assert (off.pi, off.tiles) == (r.pi, r.segments)
+
+
+@pytest.mark.parametrize("n_small,large", [(40, []), (1500, []), (900, [10**12 + 39]),
+                                           (200, [10**11, 10**13, 10**14])])
+def test_rounds_of_whole_and_cut_queries(pc, n_small, large):
+    # one-row queries below a workgroup's share of the round are not planned
+    import random
+    print("case: mixed round", n_small, large, flush=True)
+    rng = random.Random(n_small)
+    xs = [int(10 ** rng.uniform(6.1, 9.0)) for _ in range(n_small)] + large
+    rng.shuffle(xs)
+    got = list(pc.pi_count_batch(xs))
+    assert got == [pc.pi_count(x) for x in xs]
+    assert list(pc.pi_count_batch(xs, tile_leaves=1 << 12)) == got
