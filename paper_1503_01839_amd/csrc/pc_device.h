@@ -135,6 +135,48 @@ __device__ __forceinline__ bool pc_quot_in(uint64_t n, double nd, uint32_t d, ui
     return q >= 0 && (uint32_t)q < span;
 }
 
+// u - base for u = floor(n / m), given n modulo 2^32, its value nd in fp64,
+// base modulo 2^32 and base4 = 1/4 - base; m < 2^31, u < 2^48, base < 2^48.
+// 1/m is off by a few units of 2^-53 (pc_rcp_f64) and nd by 2^-53 of itself, so
+// the estimate is off by less than u 2^-50 <= 1/4; raised by 1/4 its floor is u
+// or u + 1, and the remainder n - q m, in [-m, m), is its low 32 bits read as a
+// signed number: their sign decides.  *in: u lies in [base, base + span), span
+// <= 2^21 (else the result says nothing).
+__device__ __forceinline__ uint32_t pc_quot_off(uint32_t n, double nd, uint32_t m, uint32_t base,
+                                                double base4, uint32_t span, bool *in)
+{
+    const double t = __builtin_fma(nd, pc_rcp_f64(m), base4); // u - base, raised
+    uint32_t off = (uint32_t)(int32_t)t;
+    off += (uint32_t)((int32_t)(n - (base + off) * m) >> 31);
+    *in = off < span && t > -1.0;
+    return off;
+}
+
+// floor(e / p) for e < 2^30, p <= 2^24 and a quotient below 2^17, rp = 1 / p in
+// fp32, off by at most one unit: the estimate is off by less than 2^-22 of the
+// quotient, so its floor is within one, and one step corrects it.
+PC_HD uint32_t pc_quot_near(uint32_t e, uint32_t p, float rp)
+{
+    uint32_t q = (uint32_t)((float)e * rp);
+    const int32_t r = (int32_t)(e - q * p);
+    if (r < 0)
+        q--;
+    else if (r >= (int32_t)p)
+        q++;
+    return q;
+}
+
+// n mod p for n < 2^47, p < 2^31, nd = (double)n, rp = 1 / p: adding 2^52 leaves
+// the nearest integer to n / p (off by less than 2^-5 before it is rounded) in
+// the low bits of the double; the remainder, less than p in size, is formed
+// modulo 2^32.
+PC_HD uint32_t pc_rem_near(uint64_t n, double nd, uint32_t p, double rp)
+{
+    const uint32_t q = (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma(nd, rp, 0x1p52));
+    const int32_t r = (int32_t)((uint32_t)n - q * p);
+    return (uint32_t)(r + (r < 0 ? (int32_t)p : 0));
+}
+
 // Exact floor(n / d) for any n < 2^64, 1 <= d < 2^32: fp64 estimate, one
 // exact refinement of the remainder, then a final one-step correction.
 PC_HD uint64_t pc_div_any(uint64_t n, uint32_t d)

@@ -335,26 +335,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         const uint32_t ex = pre[i];
         return q < S ? ex + quarter_count(q, preq[i], QB ? 0u : pre[i + 1] - ex) : ex;
     };
-    // floor(e / p), e < 2^27, quotient < 2^17: the fp32 reciprocal rp of p puts
-    // the estimate within one of it, one step corrects it
-    auto small_quot = [](uint32_t e, uint32_t p, float rp) -> uint32_t {
-        uint32_t q = (uint32_t)((float)e * rp);
-        const int32_t r = (int32_t)(e - q * p);
-        if (r < 0)
-            q--;
-        else if (r >= (int32_t)p)
-            q++;
-        return q;
-    };
-    // lob mod p, rp = 1 / p: adding 2^52 leaves the nearest integer to lob / p
-    // (lob < 2^47, so off by less than 2^-5) in the low bits of the double; the
-    // remainder, less than p in size, is formed modulo 2^32
     const double lobd = (double)lob;
-    auto rem_lob = [&](uint32_t p, double rp) -> uint32_t {
-        const uint32_t q = (uint32_t)__double_as_longlong(__builtin_fma(lobd, rp, 0x1p52));
-        const int32_t r = (int32_t)((uint32_t)lob - q * p);
-        return (uint32_t)(r + (r < 0 ? (int32_t)p : 0));
-    };
+    auto rem_lob = [&](uint32_t p, double rp) -> uint32_t { return pc_rem_near(lob, lobd, p, rp); };
     // The multiples of a prime p by residue class: the multipliers 30 k + res(i)
     // fall on byte p k + floor(p res(i) / 30) of the integers, always at one bit
     // of it.  With p = 30 a + res(g) the byte's part that depends on i is
@@ -399,7 +381,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 c_rem[tid] = rem;
                 if (tid >= n - nseq) { // few multiples: one lane takes them in order
                     const uint32_t r30 = 30u * rem;
-                    const uint32_t q = small_quot(r30, p, __builtin_amdgcn_rcpf((float)p));
+                    const uint32_t q = pc_quot_near(r30, p, __builtin_amdgcn_rcpf((float)p));
                     const uint32_t j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
                     uint32_t gap = __builtin_amdgcn_alignbit(PC_W30_GAPS, PC_W30_GAPS,
                                                              4u * ((j * 17u >> 6) & 7u));
@@ -507,20 +489,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         return true;
     };
     // q = bits of the segment up to u = floor(X_b / m), u in [lo, hi); X is X_b
-    // modulo 2^32 and Xd its value in fp64.  1/m is the hardware's fp64
-    // estimate refined to a few units of 2^-53, so Xd / m is off by less than
-    // u 2^-50 <= 1/4 (u < 2^48); raised by 1/4 its floor is u or u + 1, and the
-    // remainder X_b - q m, in [-m, m), m < 2^31, is its low 32 bits: their sign
-    // decides (an IEEE division with a 64-bit remainder takes five times the
-    // instructions).
+    // modulo 2^32 and Xd its value in fp64 (an IEEE division with a 64-bit
+    // remainder takes five times the instructions of pc_quot_off).
     const double qbase = 0.25 - (double)lo;
     // *bad collects quotients outside the segment (never, if the m range is
     // right; leaf_check flags them), which are taken as its last bit here.
     auto leaf_q = [&](uint32_t X, double Xd, uint32_t m, uint32_t *bad) -> uint32_t {
-        const double t = __builtin_fma(Xd, pc_rcp_f64(m), qbase); // u - lo, raised
-        uint32_t off = (uint32_t)(int32_t)t;
-        off += (uint32_t)((int32_t)(X - ((uint32_t)lo + off) * m) >> 31);
-        *bad |= off >= SPAN || !(t > -1.0) ? 1u : 0u;
+        bool in;
+        const uint32_t off = pc_quot_off(X, Xd, m, (uint32_t)lo, qbase, SPAN, &in);
+        *bad |= in ? 0u : 1u;
         return pc_w30_le(min(off, SPAN - 1));
     };
     auto leaf_check = [&](uint32_t bad) {
@@ -618,9 +595,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     const uint32_t p = c_p[j + lane];
                     const uint32_t e = c_rem[j + lane] + wv * RSB;
                     const float rp = __builtin_amdgcn_rcpf((float)p);
-                    const uint32_t r = e - small_quot(e, p, rp) * p;
+                    const uint32_t r = e - pc_quot_near(e, p, rp) * p;
                     // the least multiplier that reaches the region: ceil(30 r / p)
-                    const uint32_t r30 = 30u * r, q = small_quot(r30, p, rp);
+                    const uint32_t r30 = 30u * r, q = pc_quot_near(r30, p, rp);
                     v_p = p;
                     v_r = r;
                     v_j = pc_w30_next(q + (q * p != r30 ? 1u : 0u));
@@ -738,7 +715,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 // its start: multipliers k <= (n + 30 v_r) / p, less those before v_j
                 const uint32_t k0 = v_j == 31u ? 8u : v_j * 17u >> 6;
                 auto multiples_to = [&](uint32_t n) -> uint32_t {
-                    return pc_w30_le(small_quot(n + 30u * v_r, p, rp)) - k0;
+                    return pc_w30_le(pc_quot_near(n + 30u * v_r, p, rp)) - k0;
                 };
                 for (uint32_t s = es0; s < es1; s += 64) {
                     const uint32_t e = s + lane < es1 ? gbuf[s + lane] : 0u;
