@@ -135,14 +135,14 @@ struct Tables {
 };
 Tables g_T;
 
-// Pinned host memory for the plan copies of one query (row offsets, scan
-// blocks, tile lists, the tile planner's reads): a copy from pageable memory
-// goes through the runtime's staging at a few GB/s, one from here at the
-// link's rate.  Each copy takes its own stretch, which stays untouched until
-// the next query resets the arena after synchronising the library stream, so
-// a copy that the stream reaches late still reads what was written for it.
-// The chunks are kept from one query to the next, up to 64 MiB (a query near
-// 2^72 plans hundreds of MiB of tiles; that memory goes back after it).
+// Pinned host memory for one query: what k_prep reads in place (row offsets, scan
+// blocks, the query itself) and what comes back through a copy at the link's
+// rate (window seeds; a pageable copy goes through the runtime's staging at a few
+// GB/s).  Each use takes its own stretch, which stays untouched until the next
+// query resets the arena after synchronising the library stream, so a kernel
+// that the stream reaches late still reads what was written for it.  The chunks
+// are kept from one query to the next, up to 64 MiB (a query near 2^72 has tens
+// of MiB of row offsets; beyond the bound the memory goes back after it).
 struct PinnedArena {
     struct Chunk {
         char *p;
@@ -189,18 +189,6 @@ struct PinnedArena {
     }
 };
 PinnedArena g_pin;
-
-// n bytes from device memory src into host memory dst, through the arena;
-// waits for s
-void d2h_sync(void *dst, const void *src, size_t n, hipStream_t s, const char *what)
-{
-    if (n == 0)
-        return;
-    void *st = g_pin.take(n);
-    hipck(hipMemcpyAsync(st, src, n, hipMemcpyDeviceToHost, s), what);
-    hipck(hipStreamSynchronize(s), "sync");
-    memcpy(dst, st, n);
-}
 
 // The columns j >= 1 whose seed term at m expands by eq. (4.1): those with
 // p_{c+j}^3 <= m, pi(icbrt m) - c of them (icbrt m <= 2^16 for m <= 2^48).
@@ -922,8 +910,9 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     hipck(pc_launch_leaf_setup(T, Q, g_stream), "leaf setup");
     // S1 and the easy leaves touch nothing the sieve writes.  Of a large query
     // they and the sieve each keep every CU busy, so they start once the last
-    // sieve window is queued and delay none of its launches: S1, then the candidates
-    // (table reads) beside the prime leaves (integer issue) on the second stream.  Of a small one (the GPU mostly waits) all of them start at
+    // sieve window is queued and delay none of its launches: S1, then the
+    // candidates (table reads) beside the prime leaves (integer issue) on the
+    // second stream.  Of a small one (the GPU mostly waits) all of them start at
     // once, on the second stream.
     const bool early = nseg <= 4096;
     size_t ev_s1 = 0, ev_easy = 0;

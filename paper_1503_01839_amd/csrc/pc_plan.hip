@@ -29,7 +29,9 @@
 #define PL_ANSWER 200u
 #define PL_MIN 8192u     // no tile of less work than this (unless the caller says so) ...
 #define PL_FEW 256u      // ... where that leaves a CU without a tile: down to
-#define PL_LEAST 2048u   // this (pi(10^9) 157 -> 120 us; 10^12, 366 tiles, 211 -> 265)
+#define PL_LEAST 2048u   // this (pi(10^9) 157 -> 120 us).  A launch with a tile for every
+                         // CU stays at PL_MIN: at 10^12, 366 tiles of it, tiles down to
+                         // this took 265 us where those take 211
 #define PL_FINE 400000u  // up to here a tile's start is more than a few percent of it
 
 namespace {

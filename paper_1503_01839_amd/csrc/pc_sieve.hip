@@ -95,10 +95,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
     // threads together, below 2^9 by a wavefront each, below 2^11 by half of one,
     // from SPAN / 60 = 2^(LOG2_S - 4) on by one lane, between by eight (the
     // primes below these: PI_TINY, PI_WAVE, PI_HALF, PI_SEQ)
-    static_assert(LOG2_S >= 15 && LOG2_S <= 19, "pi(2^11) .. pi(2^15)");
+    static_assert(LOG2_S == 15 || LOG2_S == 16 || LOG2_S == 18 || LOG2_S == 19,
+                  "pi(2^11), pi(2^12), pi(2^14), pi(2^15)");
     constexpr uint32_t PI_TINY = 18, PI_WAVE = 97, PI_HALF = 309, PI_SEQ = LOG2_S == 15   ? 309
                                               : LOG2_S == 16 ? 564
-                                              : LOG2_S == 17 ? 1028
                                               : LOG2_S == 18 ? 1900
                                                              : 3512;
     static_assert(GCAP >= 2 * T, "a heavy column: 64 slots of gbuf per wave, then its quarter table");
@@ -1569,10 +1569,6 @@ hipError_t pc_launch_sieve(const pc_sieve_args &A, uint32_t seg_log2, uint32_t w
         return launch_modes<15, 64, 64>(A, mode, batch, s);
     if (seg_log2 == 16 && wg == 64)
         return launch_modes<16, 64, 64>(A, mode, batch, s);
-    if (seg_log2 == 16 && wg == 128)
-        return launch_modes<16, 128, 128>(A, mode, batch, s);
-    if (seg_log2 == 17 && wg == 256)
-        return launch_modes<17, 256, 256>(A, mode, batch, s);
     if (seg_log2 == 18 && wg == 256)
         return launch_modes<18, 256, 256>(A, mode, batch, s);
     if (seg_log2 == 18 && wg == 512)
