@@ -913,8 +913,10 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     // sieve window is queued and delay none of its launches: S1, then the
     // candidates (table reads) beside the prime leaves (integer issue) on the
     // second stream.  Of a small one (the GPU mostly waits) all of them start at
-    // once, on the second stream.
-    const bool early = nseg <= 4096;
+    // once, on the second stream.  The line by segments, at once / after the
+    // sieve: 848 (10^15) 1.00 / 1.00 ms; 1764 1.64 / 1.55; 2952 (10^16) 2.78 /
+    // 2.67; 9132 (10^17) 9.57 / 9.43; 28258 (10^18) 35.8 / 34.5.
+    const bool early = nseg <= 1024;
     size_t ev_s1 = 0, ev_easy = 0;
     auto leaves = [&]() {
         const hipStream_t st = early ? g_stream2 : g_stream;
