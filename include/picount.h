@@ -62,7 +62,8 @@ typedef struct {
     uint32_t wg_size;      /* sieve workgroup: 256|512 (32 KiB segments), 512|1024 (64)   */
     uint32_t tile_leaves;  /* most work of a sieve tile, about its leaf items (hot segments split by columns; less where the launch's work is small); 0 = by the launch's work, 0xFFFFFFFF = off */
     uint32_t flags;        /* PC_FLAG_* below */
-    uint64_t carry_budget; /* bytes for per-(segment, prime) counts per window; 0 = auto  */
+    uint64_t carry_budget; /* bound on the bytes of per-(segment, prime) counts per window, of
+                              which a window takes at most 8/15; 0 = auto (6 GiB)         */
     uint32_t small_span;   /* one-wavefront segments cover [0, small_span * y); 0 = none    */
     uint32_t small_kib;    /* size of those segments: 4 or 8 KiB; 0 = auto                  */
 } pc_config;
@@ -92,8 +93,8 @@ typedef struct {
     uint32_t sieve_launches, scan_launches;
     /* ms_total, ms_tables, ms_sieve: host wall clock of the call, of the table
      * build and from the sieve's start to the result.  ms_leaves: GPU time from
-     * the start of S1 to the end of the easy leaves, which run on a second
-     * stream concurrently with the sieve. */
+     * the start of S1 to the end of the easy leaves: up to 1024 segments they
+     * run on a second stream beside the sieve, else after it. */
     double ms_total, ms_tables, ms_leaves, ms_sieve;
     double ms_k_sieve, ms_k_scan, ms_k_easy, ms_k_s1;  /* kernel time, HIP events     */
     uint64_t n_easy_items;          /* work items of the easy-leaf kernels: a candidate m,
@@ -124,7 +125,7 @@ pc_status pc_pi_count_ex(uint64_t x, const pc_config *cfg, pc_result *res);
  * quotient, every x / p of P2 and every segment bound stays below 2^64; X_b,
  * S1's x / n and the sums are taken in 128 bits; the pi table reaches
  * isqrt(x) <= 2^36 with the primes above 2^32 held as 64-bit values (about
- * 50 GB of device memory at 2^72, the stored counts cut into 6 GiB windows). */
+ * 50 GB of device memory at 2^72, the stored counts cut into windows of 3.2 GiB). */
 pc_status pc_pi_count_wide(uint64_t x_lo, uint64_t x_hi, const pc_config *cfg, pc_result *res);
 
 /* Hard special-leaf sum S2h = -sum over hard leaves of mu(m) phi(u, b-1),

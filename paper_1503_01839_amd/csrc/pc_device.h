@@ -70,7 +70,8 @@ __device__ __forceinline__ double pc_rcp_f64(uint32_t d)
 // floor(n / d) for 1 <= d < 2^32 when the quotient is known to be below
 // 2^32 - 1; nd = (double)n.  The estimate is raised by 2^-10, more than its
 // error (2^-17 here), so the truncation is floor(n/d) or one above it, and
-// only the sign of the remainder needs testing.
+// only the sign of the remainder needs testing.  (The general form of
+// pc_quot31; the leaf kernels' divisors are below 2^31 and take that.)
 __device__ __forceinline__ uint32_t pc_quot32(uint64_t n, double nd, uint32_t d)
 {
     const uint32_t q = (uint32_t)__builtin_fma(nd, pc_rcp_f64(d), 0x1p-10);

@@ -978,8 +978,9 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     {
         uint64_t cells = 0, rows = 0;
         for (uint64_t r = 0; r < nseg; r++) {
-            // (the budget's unit is a row of 2 integers per bit: a query is cut
-            // into the same windows whatever a segment's bits stand for)
+            // (the budget's unit is a row of 2 integers per bit, so that a budget
+            // cuts a query into the windows that it cut an odd-only bitmap's rows
+            // into: of 15/4 integers per bit they take 8/15 of it)
             if (rows && ((cells + rowlen[r]) * per_cell + (rows + 1) * per_row) / 8 * 15 >
                             K.carry_budget) {
                 win_start.push_back(r);
@@ -1482,7 +1483,7 @@ void plan_round(const std::vector<BatchQuery> &R, const Knobs &K, RoundPlan &P)
     P.o_sums = take(nq * sizeof(pc_sums));
     P.o_et = take(nq * 32);
     P.o_fin = take(nq * sizeof(pc_final));
-    // each query's count staircase (rows of 2S integers from 0)
+    // each query's count staircase (rows of pc_seg_span integers from 0)
     P.roff.clear();
     P.o_roff.resize(nq);
     P.cells.resize(nq);
