@@ -934,7 +934,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
         // fill one to three pieces of up to 32.  Where z is small all leaves fall into
         // the first region, and reading every piece for every column took longer than
         // the crossings (batches of 4096 queries of 10^6.1 .. 10^8: 2.57 -> 2.08 ms,
-        // of 10^8 .. 10^9: 3.73 -> 3.03; one pi(10^18) 34.6 -> 34.4).
+        // of 10^8 .. 10^9: 3.73 -> 3.03; one pi(10^18) 34.6 -> 34.3).  A single piece
+        // is looked up alike: a test for it costs the sparse segments more (one
+        // pi(10^18) 34.5 ms, pi(2^66) 531 ms against 527).
         uint32_t *const cpiece = pre + 64 * wv;
         static_assert(GCAP <= 64 * 32, "a bit per piece");
         auto find_pieces = [&](uint32_t s0, uint32_t s1) {
@@ -952,8 +954,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             PC_EV(1);
             bool have = false;
             uint32_t pe = 0, pc0 = 0, pq = 0; // the lanes' counts, as in xbatch
-            for (uint32_t pieces = s1 - s0 > 64 ? pc_uniform(cpiece[k]) : 1u; pieces;
-                 pieces &= pieces - 1) {
+            for (uint32_t pieces = pc_uniform(cpiece[k]); pieces; pieces &= pieces - 1) {
                 const uint32_t s = s0 + 64u * (uint32_t)__builtin_ctz(pieces);
                 const uint32_t e = s == s0 ? e0 : s + lane < s1 ? gbuf[s + lane] : 0u;
                 const uint32_t q = (e >> 2) & 0xFFFFFu;
@@ -1066,7 +1067,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 const uint64_t own = s0 < s1 ? __ballot(sm && c_lc[sm ? col : cg0] != 0) : 0;
                 const uint64_t crs = __ballot(sm && v_d < RSI);
                 uint64_t todo = own | crs;
-                if (own && s1 - s0 > 64)
+                if (own)
                     find_pieces(s0, s1);
                 while (todo) {
                     const int32_t k = (int32_t)__builtin_ctzll(todo);
