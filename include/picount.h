@@ -93,8 +93,8 @@ typedef struct {
     uint32_t sieve_launches, scan_launches;
     /* ms_total, ms_tables, ms_sieve: host wall clock of the call, of the table
      * build and from the sieve's start to the result.  ms_leaves: GPU time from
-     * the start of S1 to the end of the easy leaves: up to 1024 segments they
-     * run on a second stream beside the sieve, else after it. */
+     * the start of S1 to the end of the easy leaves, which run on a second
+     * stream beside the sieve, or after it where they hold much of the work. */
     double ms_total, ms_tables, ms_leaves, ms_sieve;
     double ms_k_sieve, ms_k_scan, ms_k_easy, ms_k_s1;  /* kernel time, HIP events     */
     uint64_t n_easy_items;          /* work items of the easy-leaf kernels: a candidate m,

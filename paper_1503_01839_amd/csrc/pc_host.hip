@@ -914,15 +914,20 @@ void run_query(pc_u128 x, uint64_t y, const Knobs &K, pc_result *res, bool want_
     Q.e_lim = ptr<uint2>(B.e_lim);
     Q.e_total = reinterpret_cast<uint64_t *>(sums + 1);
     hipck(pc_launch_leaf_setup(T, Q, g_stream), "leaf setup");
-    // S1 and the easy leaves touch nothing the sieve writes.  Of a large query
-    // they and the sieve each keep every CU busy, so they start once the last
-    // sieve window is queued and delay none of its launches: S1, then the
-    // candidates (table reads) beside the prime leaves (integer issue) on the
-    // second stream.  Of a small one (the GPU mostly waits) all of them start at
-    // once, on the second stream.  The line by segments, at once / after the
-    // sieve: 848 (10^15) 1.00 / 1.00 ms; 1764 1.64 / 1.55; 2952 (10^16) 2.78 /
-    // 2.67; 9132 (10^17) 9.57 / 9.43; 28258 (10^18) 35.8 / 34.5.
-    const bool early = nseg <= 1024;
+    // S1 and the easy leaves touch nothing the sieve writes.  Where their work is
+    // small beside the sieve's they start with it, on the second stream, and fill
+    // what it leaves idle.  Where it is not, both keep every CU busy and the sieve's
+    // tiles would wait: they start once the last sieve window is queued, S1, then
+    // the candidates (table reads) beside the prime leaves (integer issue) on the
+    // second stream.  Their work goes with y, the sieve's with the segments; at
+    // once / after the sieve by y per segment (ms): 158 (10^15, alpha 4) 1.18 / 1.24,
+    // 292 (10^16, 8) 3.21 / 3.31, 542 (10^17, 16) 10.05 / 10.22, 810 (3 10^16, 16)
+    // 5.00 / 4.88, 1168 (10^16, 16) 2.77 / 2.64, 1274 (10^18, 36) 35.6 / 34.3.  A few
+    // segments leave CUs idle whatever y is (636 and 2515 of y each, 0.97 / 1.00; 882
+    // and 3924, 1.51 / 1.52; 1323 and 1744, 1.47 / 1.45), and past y = 2^27, where the
+    // mu lpf table outgrows the last cache, at once loses at any ratio (2^66, 540,
+    // 534 / 527; 2^68, 340, 1419 / 1407).
+    const bool early = nseg <= 1024 || (y / 640 < nseg && y < 1ull << 27);
     size_t ev_s1 = 0, ev_easy = 0;
     auto leaves = [&]() {
         const hipStream_t st = early ? g_stream2 : g_stream;
