@@ -927,19 +927,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
             PC_PH(2);
             return we;
         };
-        // For each column of the group the pieces of 64 of this wave's leaves [s0,
-        // s1) that hold leaves of it, a bit each, in the wave's words of pre (which
-        // nothing reads between build_pre and the next one).  A column's leaves lie
-        // side by side but for the order of the waves that put them there, so they
-        // fill one to three pieces of up to 32.  Where z is small all leaves fall into
-        // the first region, and reading every piece for every column took longer than
-        // the crossings (batches of 4096 queries of 10^6.1 .. 10^8: 2.57 -> 2.08 ms,
-        // of 10^8 .. 10^9: 3.73 -> 3.03; one pi(10^18) 34.6 -> 34.3).  A single piece
-        // is looked up alike: a test for it costs the sparse segments more (one
-        // pi(10^18) 34.5 ms, pi(2^66) 531 ms against 527).
+        // For each column of the group (one a lane) the pieces of 64 of this wave's
+        // leaves [s0, s1) that hold leaves of it, a bit each, gathered in the wave's
+        // words of pre (which nothing reads between build_pre and the next one).  A
+        // column's leaves lie side by side but for the order of the waves that put
+        // them there, so they fill one to three pieces of up to 32.  Where z is small
+        // all leaves fall into the first region, and reading every piece for every
+        // column took longer than the crossings (batches of 4096 queries of 10^6.1 ..
+        // 10^8: 2.57 -> 2.08 ms, of 10^8 .. 10^9: 3.73 -> 3.03; one pi(10^18) 34.7 ->
+        // 34.3).  Bins of a single piece go the same way: a test for them costs the
+        // sparse segments more (one pi(10^18) 34.5 ms, pi(2^66) 531 ms against 525).
         uint32_t *const cpiece = pre + 64 * wv;
         static_assert(GCAP <= 64 * 32, "a bit per piece");
-        auto find_pieces = [&](uint32_t s0, uint32_t s1) {
+        auto find_pieces = [&](uint32_t s0, uint32_t s1) -> uint32_t {
             cpiece[lane] = 0;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             for (uint32_t s = s0, bit = 1; s < s1; s += 64, bit <<= 1)
@@ -947,14 +947,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                     __hip_atomic_fetch_or(cpiece + (gbuf[s + lane] >> 22), bit, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            return cpiece[lane];
         };
         // The leaves of column cg0 + k among this wave's [s0, s1) (e0: the
-        // first 64 of them, one a lane): a prefix of the region for each.
-        auto answer = [&](uint32_t k, uint32_t s0, uint32_t s1, uint32_t e0) {
+        // first 64 of them, one a lane; pieces: find_pieces' word of the column): a
+        // prefix of the region for each.
+        auto answer = [&](uint32_t k, uint32_t s0, uint32_t s1, uint32_t e0, uint32_t pieces) {
             PC_EV(1);
             bool have = false;
             uint32_t pe = 0, pc0 = 0, pq = 0; // the lanes' counts, as in xbatch
-            for (uint32_t pieces = pc_uniform(cpiece[k]); pieces; pieces &= pieces - 1) {
+            for (; pieces; pieces &= pieces - 1) {
                 const uint32_t s = s0 + 64u * (uint32_t)__builtin_ctz(pieces);
                 const uint32_t e = s == s0 ? e0 : s + lane < s1 ? gbuf[s + lane] : 0u;
                 const uint32_t q = (e >> 2) & 0xFFFFFu;
@@ -1067,13 +1069,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(
                 const uint64_t own = s0 < s1 ? __ballot(sm && c_lc[sm ? col : cg0] != 0) : 0;
                 const uint64_t crs = __ballot(sm && v_d < RSI);
                 uint64_t todo = own | crs;
-                if (own)
-                    find_pieces(s0, s1);
+                const uint32_t v_piece = own ? find_pieces(s0, s1) : 0u;
                 while (todo) {
                     const int32_t k = (int32_t)__builtin_ctzll(todo);
                     todo &= todo - 1;
                     if ((own >> k) & 1)
-                        answer((uint32_t)k, s0, s1, e0);
+                        answer((uint32_t)k, s0, s1, e0,
+                               (uint32_t)__builtin_amdgcn_readlane((int)v_piece, k));
                     if ((crs >> k) & 1)
                         cross_k(k);
                 }
