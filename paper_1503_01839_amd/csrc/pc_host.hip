@@ -1544,18 +1544,22 @@ void plan_round(const std::vector<BatchQuery> &R, const Knobs &K, RoundPlan &P)
     P.np = P.nrest = 0;
     uint64_t ysum = 0, cells = 0;
     std::vector<uint32_t> pp{0}, pr{0};
+    uint64_t nrows = 0;
     for (uint32_t i = 0; i < nq; i++) {
         ysum += R[i].y;
         cells += P.cells[i];
+        nrows += R[i].nseg;
     }
     for (uint32_t i : order) {
         const BatchQuery &b = R[i];
         // a query of one row, and of less work than one of the 768 workgroups' share
-        // of the round, has nothing to gain from a cut, and many of them cost the
-        // planner a workgroup each (16384 queries of 10^6.1 .. 10^7: 7.40 -> 7.21 ms, 1024
-        // of them 752 -> 700 us; of several rows cuts do pay: 1024 queries of 10^11 ..
-        // 10^12 without them 7.62 ms, 6.21 with)
-        const bool whole = plan_tile_work(K) == 0 && b.nseg == 1 &&
+        // of a round that has rows for them all, has nothing to gain from a cut, and
+        // many of them cost the planner a workgroup each (16384 queries of 10^6.1 ..
+        // 10^7: 7.40 -> 7.21 ms, 1024 of them 752 -> 700 us; of several rows cuts do
+        // pay: 1024 queries of 10^11 .. 10^12 without them 7.62 ms, 6.21 with; and so
+        // they do in a round of fewer rows: 132 queries of 10^8 .. 10^10.7 582 us
+        // without, 463 with)
+        const bool whole = plan_tile_work(K) == 0 && nrows >= 768 && b.nseg == 1 &&
                            768 * rough_work(b.y, P.cells[i]) <= rough_work(ysum, cells);
         const uint64_t n = whole ? 0 : planned_rows(b.y, b.z, 0, pc_seg_span(kBatchLog2S), b.nseg);
         P.np += (uint32_t)n;
